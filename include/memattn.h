@@ -129,7 +129,8 @@ MEMATTN_API size_t mem_workspace_bytes(int64_t m, int64_t n, int32_t d, int32_t 
  * Selection uses s, not p; `scale` is the softmax inverse temperature (> 0,
  * finite) and does not change which ids are selected.
  * 1 <= k <= 64 and k <= n.  `full_prob` (nullable, device [m, n] fp32)
- * receives p_ij for every bank row; requesting it selects the VALU path.
+ * receives p_ij for every bank row; requesting it selects the general path
+ * (scores of a block of the bank, then their selection).
  * The workspace must be at least mem_workspace_bytes(m, n, d, k, dtype).
  */
 MEMATTN_API mem_status mem_retrieve_topk(const mem_bank* bank, const void* queries, int64_t m, int64_t q_stride, int32_t k,

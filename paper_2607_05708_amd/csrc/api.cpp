@@ -121,7 +121,8 @@ mem_status select_topk(const mem_bank* bank, const void* queries, int64_t m, int
                        q_stride <= 65536 && aligned16(bank->emb) && aligned16(queries);
   const bool relation = queries == bank->emb && q_stride == bank->row_stride && m == bank->n;
   // (a scoped relation build keeps the bank order, so its sample as well)
-  const Plan p = make_plan(m, bank->n, bank->d, k, bank->dtype, mfma_ok, relation && scope.row_ns == nullptr);
+  const Plan p = make_plan(m, bank->n, bank->d, k, bank->dtype, mfma_ok, relation && scope.row_ns == nullptr,
+                           use_scratch ? kScratchBytes : SIZE_MAX);
   if (static_cast<int64_t>(p.n_splits) * (p.mfma ? p.q_tiles : m) > INT32_MAX)
     return fail(MEM_ERR_UNSUPPORTED, "problem too large for one launch");
   if (m > INT32_MAX) return fail(MEM_ERR_UNSUPPORTED, "m too large");
@@ -144,10 +145,11 @@ mem_status select_topk(const mem_bank* bank, const void* queries, int64_t m, int
                          static_cast<const uint16_t*>(queries), q_stride, m, bank->d, c2, self_base, k, scope,
                          relation, ws, s);
   } else {
-    e = launch_topk_generic(p, bank->emb, bank->row_stride, bank->n, queries, q_stride, m, bank->d, bank->dtype, c2,
-                            self_base, scope, ws, full_prob, s);
+    e = launch_topk_score(p, bank->emb, bank->row_stride, bank->n, queries, q_stride, m, bank->d, bank->dtype, c2,
+                          self_base, k, scope, ws, full_prob, out.idx, out.score, out.prob, out.lse, s);
   }
   if (e != hipSuccess) return device_status(e, "partial selection launch");
+  if (!p.mfma && p.n_splits == 1) return MEM_OK;  // (its results are final)
   FullProb fp;
   fp.full = full_prob;
   fp.n = bank->n;
@@ -202,7 +204,7 @@ Plan make_grouped_plan(int64_t m, int32_t n_ns, int64_t n_entries, int32_t k) {
   return p;
 }
 
-Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation) {
+Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, size_t limit) {
   Plan p{};
   // The workspace is sized for the most splits any bank of at most n rows
   // can get (min(tiles, split target)), so that the size never decreases
@@ -286,11 +288,15 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
   } else {
     p.mfma = false;
     p.kcap = pow2_at_least(k);
-    const int64_t nt = ceil_div(n, kGenericRows);
-    int64_t s = ceil_div(1024, m > 0 ? m : 1);
-    s = s < 1 ? 1 : (s > nt ? nt : s);
+    // One workgroup selects for a (query, split): about 2,048 of them, one
+    // split where the bank is small (the select kernel then writes the final
+    // results and no merge follows).
+    const int64_t nt = ceil_div(n, kSelectRows);
+    int64_t s = ceil_div(2048, m > 0 ? m : 1);
+    s = s > nt ? nt : s;
     splits_cap = s;
-    p.rows_per_split = ceil_div(nt, s) * kGenericRows;
+    if (n <= kSelectOneSplit) s = 1;
+    p.rows_per_split = ceil_div(nt, s) * kSelectRows;
     p.n_splits = static_cast<int>(ceil_div(n, p.rows_per_split));
     p.q_tiles = 0;
     p.tiles_per_split = 0;
@@ -305,6 +311,25 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
   p.ws_part_keys = 0;
   p.ws_part_ms = align256(mm * slots * p.kcap * sizeof(uint64_t));
   p.ws_lse2 = p.ws_part_ms + align256(mm * slots * 2 * sizeof(float));
+  if (!p.mfma) {
+    p.ws_part_lo = p.ws_lse2 + align256(mm * sizeof(float));
+    p.ws_scores = p.ws_part_lo + align256(mm * slots * sizeof(float));
+    p.blk_queries = m < 4096 ? (m > 0 ? m : 1) : 4096;
+    const int64_t wide = static_cast<int64_t>(kScoreBlock / sizeof(float)) / p.blk_queries / kSelectRows * kSelectRows;
+    p.blk_rows = ceil_div(n, 32) * 32;
+    if (p.blk_rows > wide) p.blk_rows = wide > kSelectRows ? wide : kSelectRows;
+    const int64_t room = limit > p.ws_scores ? static_cast<int64_t>((limit - p.ws_scores) / sizeof(float)) : 0;
+    if (p.blk_queries * p.blk_rows > room) {
+      if (p.blk_rows > kSelectRows) p.blk_rows = kSelectRows;
+      if (p.blk_queries > room / p.blk_rows) p.blk_queries = room / p.blk_rows;
+      if (p.blk_queries < 1) {
+        p.blk_queries = 1;
+        p.blk_rows = room >= 32 ? room / 32 * 32 : 32;
+      }
+    }
+    p.ws_bytes = p.ws_scores + align256(static_cast<size_t>(p.blk_queries * p.blk_rows) * sizeof(float));
+    return p;
+  }
   p.ws_samp = p.ws_lse2 + align256(mm * sizeof(float));
   p.ws_t0 = p.ws_samp + (p.mfma ? align256(mm * static_cast<size_t>(sample_cap(m)) * sizeof(uint16_t)) : 0);
   p.ws_thr = p.ws_t0 + align256(mm * sizeof(float));

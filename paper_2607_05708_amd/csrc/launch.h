@@ -10,7 +10,7 @@ namespace memattn {
 
 // How one retrieval/relation call is split over the GPU.
 struct Plan {
-  bool mfma;              // bf16 matrix-core path (else the VALU path)
+  bool mfma;              // fused bf16 matrix-core path (else the general score and select path)
   int qw;                 // matrix-core workgroup shape: 64 * qw queries (1, 2 or 4)
   int tile_rows;          // bank rows per matrix-core tile (512 for qw = 1, else 256)
   int tile_queries;       // queries per matrix-core workgroup
@@ -41,6 +41,10 @@ struct Plan {
   size_t ws_orank;        // each query's rank among its label's queries [m] (int32)
   size_t ws_stop;         // each query's sampled keys at or above its k-th, with positions [m, 64] (uint32)
   size_t ws_qbuf;         // the queries in clustered order [m, d] (bf16)
+  int64_t blk_queries;    // general path: queries and bank rows scored at a time
+  int64_t blk_rows;
+  size_t ws_part_lo;      // low words of the partial softmax sums [m, n_splits] (float)
+  size_t ws_scores;       // the block's scores [blk_queries, blk_rows] (float)
   size_t ws_bytes;        // total workspace bytes
 };
 
@@ -57,7 +61,9 @@ constexpr int64_t kOrderSampleFloor = 1024;  // fewest sampled rows of a relatio
 // Matrix-core workgroup shapes by query count: 64 x 512-row tiles (<= 64
 // queries), 128 x 256 (<= 128), else 256 x 256; every wave owns 128 rows of
 // a tile, so a split keeps tile_rows / 128 partials while the kernel runs.
-constexpr int kGenericRows = 256; // bank rows per VALU-path step
+constexpr int kSelectRows = 4096;  // scores per step of the general path's select kernel
+constexpr int64_t kSelectOneSplit = 16384;  // banks of at most so many rows take one split per query there
+constexpr size_t kScoreBlock = size_t{64} << 20;  // most bytes of scores it holds at a time
 constexpr int kMaxK = 64;
 constexpr int kMaxD = 8192;
 
@@ -71,16 +77,22 @@ struct Scope {
 // mfma_ok: caller allows the matrix-core path (bf16, d % 32 == 0, k <= 32,
 // no full probability output).  relation: the queries are the bank's own
 // rows (only the sample size depends on it, never the workspace size).
-Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation = false);
+// limit: the workspace at hand; the general path scores smaller blocks to fit.
+Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation = false,
+               size_t limit = SIZE_MAX);
 // Grouped selection over per-namespace chunk tables: the narrow matrix-core
 // shape, S splits per namespace (S from the mean table size), no sample.
 Plan make_grouped_plan(int64_t m, int32_t n_ns, int64_t n_entries, int32_t k);
 
-// Partial selection over bank splits.  `self_base` >= 0 removes bank row
-// self_base + i from query i's candidates.  All launches go to `stream`.
-hipError_t launch_topk_generic(const Plan& p, const void* bank, int64_t bank_stride, int64_t n, const void* queries,
-                               int64_t q_stride, int64_t m, int32_t d, int32_t dtype, float c2, int64_t self_base,
-                               const Scope& scope, void* ws, float* full_scores, hipStream_t stream);
+// General path: scores block by block, each block followed by its selection.
+// `self_base` >= 0 removes bank row self_base + i from query i's candidates.
+// With one split per query (p.n_splits == 1) the results are final, the full
+// probability rows included; else the partials are left for the merge.  All
+// launches go to `stream`.
+hipError_t launch_topk_score(const Plan& p, const void* bank, int64_t bank_stride, int64_t n, const void* queries,
+                             int64_t q_stride, int64_t m, int32_t d, int32_t dtype, float c2, int64_t self_base,
+                             int32_t k, const Scope& scope, void* ws, float* full_scores, int32_t* idx, float* score,
+                             float* prob, float* lse, hipStream_t stream);
 // With p.ns > 0 a sample pass over the first ns tiles of every split first
 // bounds each query's k-th best score from below; the full pass starts its
 // thresholds there.

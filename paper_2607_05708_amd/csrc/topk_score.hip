@@ -1,0 +1,527 @@
+// General selection path: any dtype, any d <= 8192, any row stride and
+// alignment, k <= 64, optional full probability output.  It serves what the
+// fused matrix-core kernel does not take (fp32 embeddings, k > 32, d not a
+// multiple of 32, full probabilities) and calls too small to fill it.
+//
+// Two kernels.  A score kernel forms s_ij = <q_i, b_j> on the matrix cores
+// (fp32 inputs on the fp32 MFMA, bf16 inputs on the bf16 MFMA, fp32
+// accumulation) and writes a block of scores [queries, rows]; a select kernel
+// folds each query's scores into its softmax state and sorted top-k list.
+// The block is at most 64 MiB (kScoreBlock), so that it stays in the last
+// level cache between the two, and larger problems run block by block, the
+// select kernel resuming each list.  Where a query has one split, its last
+// select writes the final results (and its full probability row), else the
+// merge kernels combine the splits.
+//
+// A thread-per-row fp32 kernel did this before (3.8 TFLOP/s whatever the
+// type, every query re-reading the bank).  64 fp32 queries against 65,536 x
+// 768 rows, k = 16: 1,706 -> 87 us (scores 66 us = 98 TFLOP/s of the fp32
+// MFMA's 153); 200 bf16 queries against 100,003 x 1024, k = 64: 12.2 -> 0.19
+// ms; 16 fp32 queries against 1,024 x 256 with full probabilities: 20.9 ->
+// 14.6 us.
+//
+// Dense-only relevance of the paper's Section 5.5 applied to LLMSelect of
+// Algorithm 1.
+#include "device_common.h"
+#include "launch.h"
+#include "select.h"
+
+namespace memattn {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// acc += A B over the 16 bytes of K that every lane holds of its row: one
+// 32x32x16 bf16 MFMA, or four 32x32x2 fp32 ones.  Lane l's 16 bytes belong to
+// row l % 32 of the block; lanes 0-31 and 32-63 hold different 16-byte
+// pieces of the rows.  Which piece a half holds is free, as long as A and B
+// agree: the sum runs over all of them.
+__device__ __forceinline__ void mma16(f32x16& acc, u32x4 a, u32x4 b, uint16_t) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0,
+                                                0, 0);
+}
+__device__ __forceinline__ void mma16(f32x16& acc, u32x4 a, u32x4 b, float) {
+  const f32x4 fa = __builtin_bit_cast(f32x4, a), fb = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[e], fb[e], acc, 0, 0, 0);
+}
+
+// 16 bytes of a row from element k on, elements at or past d as zeros.  Rows
+// need only their elements' own alignment.
+template <typename T>
+__device__ __forceinline__ u32x4 load16(const T* row, int k, int d, bool whole) {
+  constexpr int E = 16 / sizeof(T);
+  u32x4 v = {0u, 0u, 0u, 0u};
+  if (whole || k + E <= d) {
+    __builtin_memcpy(&v, row + k, 16);
+  } else if (k < d) {
+    T e[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) e[i] = k + i < d ? row[k + i] : T(0);
+    __builtin_memcpy(&v, e, 16);
+  }
+  return v;
+}
+
+// The same without a branch around the load, so that the compiler's wait
+// counts stay exact: a piece that would pass the row's end is read from its
+// last 16 bytes (d >= 16 / sizeof(T)) and shifted into place by fix_tail.
+template <typename T>
+__device__ __forceinline__ u32x4 load16_within(const T* row, int k, int d) {
+  u32x4 v;
+  __builtin_memcpy(&v, row + min(k, d - static_cast<int>(16 / sizeof(T))), 16);
+  return v;
+}
+template <typename T>
+__device__ __forceinline__ u32x4 fix_tail(u32x4 v, int k, int d) {
+  const int over = k + static_cast<int>(16 / sizeof(T)) - d;  // elements past the row
+  if (over <= 0) return v;
+  if (k >= d) return u32x4{0u, 0u, 0u, 0u};
+  const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v);
+  return __builtin_bit_cast(u32x4, x >> (over * static_cast<int>(sizeof(T)) * 8));
+}
+
+struct ScoreArgs {
+  const void* bank;      // first row of the block
+  int64_t bank_stride;
+  int64_t rows;          // rows of the block
+  const void* queries;   // first query of the block
+  int64_t q_stride;
+  int64_t nq;            // queries of the block
+  int32_t d;
+  float* out;            // [nq, ld]
+  int64_t ld;
+};
+
+// Tiled score kernel: 4 waves, 128 bank rows against 32 * QW * QB queries.
+// Each stage holds 128 bytes of K of every row in LDS (two buffers), loaded
+// into registers two stages ahead; the 16-byte pieces of a row are XOR
+// swizzled by the row so that fragment reads (32 consecutive rows, one
+// piece) and the staging writes (whole rows) are free of bank conflicts.
+// QW waves share the rows' blocks among the queries: a wave scores QB query
+// blocks against RB = QW row blocks of 32.
+constexpr int kScoreRows = 128;  // bank rows per tile
+constexpr int kStageBytes = 128;
+
+template <typename T, int QB, int QW>
+__global__ __launch_bounds__(256) void score_tile_kernel(ScoreArgs a) {
+  constexpr int RB = QW;
+  constexpr int kTileQ = 32 * QB * QW;
+  constexpr int kLines = kScoreRows + kTileQ;     // staged rows: bank rows, then query rows
+  constexpr int kLoads = kLines / 32;             // 16-byte pieces per thread and stage
+  constexpr int kRowLoads = kScoreRows / 32;
+  constexpr int E = 16 / sizeof(T);               // elements per piece
+  constexpr int KE = kStageBytes / sizeof(T);     // elements per stage
+  __shared__ u32x4 st[2][kLines * 8];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  // Workgroups b, b + 8, ... run on one XCD: the query tiles of one row tile
+  // are neighbours there and share its rows through that XCD's L2.
+  const int q_tiles = static_cast<int>((a.nq + kTileQ - 1) / kTileQ);
+  const int i8 = blockIdx.x >> 3;
+  const int64_t r0 = (static_cast<int64_t>(i8 / q_tiles) * 8 + (blockIdx.x & 7)) * kScoreRows;
+  const int64_t q0 = static_cast<int64_t>(i8 % q_tiles) * kTileQ;
+  if (r0 >= a.rows) return;
+
+  // piece tid % 8 of staged rows tid / 8 + 32 i; rows past the block repeat
+  // its last one (their scores are not written)
+  const int c = tid & 7;
+  const T* src[kLoads];
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    const int line = (tid >> 3) + 32 * i;
+    src[i] = i < kRowLoads
+                 ? static_cast<const T*>(a.bank) + min(r0 + line, a.rows - 1) * a.bank_stride
+                 : static_cast<const T*>(a.queries) + min(q0 + line - kScoreRows, a.nq - 1) * a.q_stride;
+  }
+  const int d = a.d;
+  const int n_st = (d + KE - 1) / KE;
+  // (stages past the last read the rows' last bytes again and are not used)
+  auto load = [&](int s, u32x4 (&v)[kLoads]) {
+    const int k = s * KE + c * E;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) v[i] = load16_within<T>(src[i], k, d);
+  };
+  const int wr = c ^ ((tid >> 3) & 7);  // (the swizzle depends on row % 8 only)
+  // (the last stage's tail is mended in LDS: a use of the registers there
+  // would make the compiler copy them in every stage, and wait for them)
+  auto store = [&](int s, int buf, const u32x4 (&v)[kLoads]) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) st[buf][((tid >> 3) + 32 * i) * 8 + wr] = v[i];
+    if ((s + 1) * KE > d) {
+#pragma unroll 1
+      for (int i = 0; i < kLoads; ++i) {
+        u32x4* at = &st[buf][((tid >> 3) + 32 * i) * 8 + wr];
+        *at = fix_tail<T>(*at, s * KE + c * E, d);
+      }
+    }
+  };
+  f32x16 acc[QB][RB];
+#pragma unroll
+  for (int x = 0; x < QB; ++x)
+#pragma unroll
+    for (int y = 0; y < RB; ++y) acc[x][y] = f32x16{};
+  const int frow = lane & 31;
+  const int part = lane >> 5;
+  const int wq = wave % QW;                  // the wave's query group
+  const int wrow = (wave / QW) * 32 * RB;    // and its first row
+  auto compute = [&](int buf) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int p = (2 * s + part) ^ (frow & 7);
+      u32x4 fq[QB], fr[RB];
+#pragma unroll
+      for (int x = 0; x < QB; ++x) fq[x] = st[buf][(kScoreRows + (wq * QB + x) * 32 + frow) * 8 + p];
+#pragma unroll
+      for (int y = 0; y < RB; ++y) fr[y] = st[buf][(wrow + y * 32 + frow) * 8 + p];
+#pragma unroll
+      for (int x = 0; x < QB; ++x)
+#pragma unroll
+        for (int y = 0; y < RB; ++y) mma16(acc[x][y], fq[x], fr[y], T{});
+    }
+  };
+  // stage s is computed from buffer s % 2 while the loads of stages s + 1 and
+  // s + 2 are in flight; buffer (s + 1) % 2 was last read in stage s - 1,
+  // which every wave finished before the barrier that ended it
+  u32x4 va[kLoads], vb[kLoads];
+  load(0, va);
+  load(1, vb);
+  store(0, 0, va);
+  load(2, va);
+  __syncthreads();
+  // (no exit inside the loop: the wait counts at its head stay exact)
+  int s = 0;
+  for (; s + 2 < n_st; s += 2) {
+    compute(0);
+    store(s + 1, 1, vb);
+    load(s + 3, vb);
+    __syncthreads();
+    compute(1);
+    store(s + 2, 0, va);
+    load(s + 4, va);
+    __syncthreads();
+  }
+  compute(0);
+  if (s + 1 < n_st) {
+    store(s + 1, 1, vb);
+    __syncthreads();
+    compute(1);
+  }
+  // accumulator lane: row lane % 32 of its block, queries 8 (r / 4) + 4 part + r % 4
+#pragma unroll
+  for (int y = 0; y < RB; ++y) {
+    const int64_t row = r0 + wrow + y * 32 + frow;
+    if (row < a.rows) {
+#pragma unroll
+      for (int x = 0; x < QB; ++x)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int64_t q = q0 + (wq * QB + x) * 32 + 8 * (r >> 2) + 4 * part + (r & 3);
+          if (q < a.nq) a.out[q * a.ld + row] = acc[x][y][r];
+        }
+    }
+  }
+}
+
+// Small problems: 32 queries against 32 rows per workgroup, its four waves
+// taking every fourth 128-byte block of K each and adding their sums up in
+// LDS.  Fragments come straight from global memory (lane: 64 contiguous
+// bytes of its row), all of a block's loads in flight, so a call costs little
+// more than one trip to memory, and four times as many workgroups share it
+// as with the tiles above.
+template <typename T>
+__global__ __launch_bounds__(256) void score_small_kernel(ScoreArgs a) {
+  constexpr int E = 16 / sizeof(T);
+  constexpr int KE = kStageBytes / sizeof(T);
+  __shared__ float red[4][1024];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int q_tiles = static_cast<int>((a.nq + 31) / 32);
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x / q_tiles) * 32;
+  const int64_t q0 = static_cast<int64_t>(blockIdx.x % q_tiles) * 32;
+  const int frow = lane & 31;
+  const int part = lane >> 5;
+  const T* br = static_cast<const T*>(a.bank) + min(r0 + frow, a.rows - 1) * a.bank_stride;
+  const T* qr = static_cast<const T*>(a.queries) + min(q0 + frow, a.nq - 1) * a.q_stride;
+  const int d = a.d;
+  const int n_blk = (d + KE - 1) / KE;
+  const int n_whole = d / KE;
+  f32x16 acc = {};
+  auto load = [&](int b, u32x4 (&x)[4], u32x4 (&y)[4]) {
+    if (b >= n_blk) return;
+    const int k = b * KE + part * 4 * E;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = load16<T>(qr, k + i * E, d, b < n_whole);
+      y[i] = load16<T>(br, k + i * E, d, b < n_whole);
+    }
+  };
+  auto compute = [&](int b, const u32x4 (&x)[4], const u32x4 (&y)[4]) {
+    if (b >= n_blk) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) mma16(acc, x[i], y[i], T{});
+  };
+  u32x4 xa[4], ya[4], xb[4], yb[4];
+  load(wave, xa, ya);
+  for (int b = wave; b < n_blk; b += 8) {
+    load(b + 4, xb, yb);
+    compute(b, xa, ya);
+    load(b + 8, xa, ya);
+    compute(b + 4, xb, yb);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[wave][r * 64 + lane] = acc[r];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int r = wave * 4 + j;
+    const int64_t q = q0 + 8 * (r >> 2) + 4 * part + (r & 3);
+    const float s = (red[0][r * 64 + lane] + red[1][r * 64 + lane]) + (red[2][r * 64 + lane] + red[3][r * 64 + lane]);
+    if (q < a.nq && r0 + frow < a.rows) a.out[q * a.ld + r0 + frow] = s;
+  }
+}
+
+// ---------------------------------------------------------------- selection
+
+struct SelectArgs {
+  float* scores;          // [nq, ld]: column c is bank row c0 + c
+  int64_t ld;
+  int64_t q0;             // first query of the block
+  int64_t c0, c1;         // bank rows of the block
+  int64_t rows_per_split;
+  int n_splits;           // splits of a query (all of them)
+  int split0;             // first split that meets the block
+  int block_splits;       // and how many do
+  int k, kcap;
+  float c2;
+  int64_t self_base;
+  const int32_t* row_ns;
+  const int32_t* key_ns;
+  uint64_t* part_keys;    // [m, n_splits, kcap]
+  float2* part_ms;        // [m, n_splits]: max, sum
+  float* part_lo;         // [m, n_splits]: what the sum's rounding left
+  int full;               // the scores are the caller's full probability rows
+  int64_t n;
+  // final results (one split per query, last block), else idx is NULL
+  int32_t* idx;
+  float* score;
+  float* prob;
+  float* lse;
+};
+
+// One workgroup per (query, split): the split's scores of this block, 4,096
+// a step.  A split that an earlier block began resumes from its list and
+// softmax state (the sum in two floats, so that nothing of the double is
+// lost between blocks).
+__global__ __launch_bounds__(kSelThreads) void select_kernel(SelectArgs a) {
+  __shared__ SelectLds L;
+  const int tid = threadIdx.x;
+  const int64_t ql = blockIdx.x / a.block_splits;
+  const int64_t q = a.q0 + ql;
+  const int split = a.split0 + static_cast<int>(blockIdx.x % a.block_splits);
+  const int64_t slot = q * a.n_splits + split;
+  const int64_t s0 = static_cast<int64_t>(split) * a.rows_per_split;
+  const int64_t row0 = max(s0, a.c0);
+  const int64_t row1 = min(min(s0 + a.rows_per_split, a.n), a.c1);
+  const bool resume = s0 < a.c0;
+  float* row = a.scores + ql * a.ld;  // column c: bank row c0 + c
+  const int64_t self_row = a.self_base >= 0 ? a.self_base + q : -1;
+  const int32_t my_ns = a.row_ns ? a.key_ns[q] : 0;
+  int cur = 0;
+  if (tid < kMaxK) L.list[0][tid] = (resume && tid < a.k) ? a.part_keys[slot * a.kcap + tid] : 0;
+  float m_run = -INFINITY;
+  double s_run = 0.0;
+  if (resume && tid == 0) {
+    const float2 ms = a.part_ms[slot];
+    m_run = ms.x;
+    s_run = static_cast<double>(ms.y) + static_cast<double>(a.part_lo[slot]);
+  }
+  __syncthreads();
+  float v[kSelPer];  // a step's scores, -inf where no candidate
+  for (int64_t base = row0; base < row1; base += kSelStep) {
+    uint32_t ord[kSelPer];
+    const int left = static_cast<int>(min(row1 - base, static_cast<int64_t>(kSelStep)));
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j) {
+      const int e = 256 * j + tid;
+      v[j] = e < left ? row[base - a.c0 + e] : -INFINITY;
+    }
+    uint32_t out = 0;  // bit j: value j is no candidate
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j) {
+      const int e = 256 * j + tid;
+      if (e >= left || base + e == self_row) out |= 1u << j;
+    }
+    if (a.row_ns) {
+#pragma unroll
+      for (int j = 0; j < kSelPer; ++j) {
+        const int e = 256 * j + tid;
+        if (e < left && !(my_ns >= 0 && a.row_ns[base + e] == my_ns)) out |= 1u << j;
+      }
+    }
+    float mx = m_run;
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j) {
+      const bool cand = ((out >> j) & 1u) == 0;
+      // a row outside the candidates gets probability 0 in the full output
+      if (a.full && !cand && 256 * j + tid < left) row[base - a.c0 + 256 * j + tid] = -INFINITY;
+      ord[j] = cand ? f2ord(v[j]) : 0u;
+      v[j] = cand ? v[j] : -INFINITY;
+      mx = fmaxf(mx, v[j] * a.c2);
+    }
+    if (mx != -INFINITY) {
+      double part = 0.0;
+#pragma unroll
+      for (int j = 0; j < kSelPer; ++j) part += static_cast<double>(fast_exp2(v[j] * a.c2 - mx));
+      s_run = s_run * static_cast<double>(fast_exp2(m_run - mx)) + part;
+      m_run = mx;
+    }
+    cur = select_step(
+        L,
+        [&](int j) {
+          return ord[j] ? (static_cast<uint64_t>(ord[j]) << 32) | (0xFFFFFFFFu - (static_cast<uint32_t>(base) + 256 * j + tid))
+                        : uint64_t{0};
+        },
+        a.k, cur);
+  }
+
+  const SoftmaxSum all = block_softmax(L, m_run, s_run);
+  if (a.idx == nullptr) {
+    if (tid < a.kcap) a.part_keys[slot * a.kcap + tid] = L.list[cur][tid];
+    if (tid == 0) {
+      const float hi = static_cast<float>(all.sum);
+      a.part_ms[slot] = make_float2(all.max, hi);
+      a.part_lo[slot] = static_cast<float>(all.sum - static_cast<double>(hi));
+    }
+    return;
+  }
+  const float lse2 = all.max + static_cast<float>(log2(all.sum));
+  if (tid < a.k) write_selected(L.list[cur][tid], a.c2, lse2, q * a.k + tid, a.idx, a.score, a.prob);
+  if (tid == 0 && a.lse) a.lse[q] = lse2 * kLn2;
+  if (!a.full) return;
+  const bool none = lse2 == -INFINITY;
+  if (row1 - row0 <= kSelStep) {  // the only step's scores are still here
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j) {
+      const int64_t r = row0 + 256 * j + tid;
+      if (r < row1) row[r - a.c0] = none ? 0.f : fast_exp2(v[j] * a.c2 - lse2);
+    }
+    return;
+  }
+  for (int64_t base = row0; base < row1; base += kSelStep) {
+    // (the writes of -inf above were this thread's own)
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j) {
+      const int64_t r = base + 256 * j + tid;
+      v[j] = r < row1 ? row[r - a.c0] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j) {
+      const int64_t r = base + 256 * j + tid;
+      if (r < row1) row[r - a.c0] = none ? 0.f : fast_exp2(v[j] * a.c2 - lse2);
+    }
+  }
+}
+
+int64_t tile_queries(int64_t nq) { return nq <= 32 ? 32 : (nq <= 64 ? 64 : 128); }
+
+// Whether the whole call (not one block of it, so that scores do not depend
+// on how it is cut into blocks) takes the small kernel: fewer tiles than CUs,
+// which smaller ones spread over four times as many, or rows shorter than the
+// 16 bytes the tiles read at a time.
+bool small_scores(int64_t m, int64_t n, int64_t row_bytes) {
+  if (row_bytes < 16) return true;
+  const int64_t tq = tile_queries(m);
+  return (n + kScoreRows - 1) / kScoreRows * ((m + tq - 1) / tq) < 256;
+}
+
+template <typename T>
+hipError_t launch_score(const ScoreArgs& a, bool small, hipStream_t stream) {
+  const int64_t row_tiles = (a.rows + kScoreRows - 1) / kScoreRows;
+  const int64_t tq = tile_queries(a.nq);
+  const int64_t q_tiles = (a.nq + tq - 1) / tq;
+  if (small) {
+    const int64_t wgs = (a.rows + 31) / 32 * ((a.nq + 31) / 32);
+    score_small_kernel<T><<<dim3(static_cast<unsigned>(wgs)), 256, 0, stream>>>(a);
+    return hipGetLastError();
+  }
+  const dim3 grid(static_cast<unsigned>((row_tiles + 7) / 8 * 8 * q_tiles));
+  if (tq == 32)
+    score_tile_kernel<T, 1, 1><<<grid, 256, 0, stream>>>(a);
+  else if (tq == 64)
+    score_tile_kernel<T, 2, 1><<<grid, 256, 0, stream>>>(a);
+  else
+    score_tile_kernel<T, 2, 2><<<grid, 256, 0, stream>>>(a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_topk_score(const Plan& p, const void* bank, int64_t bank_stride, int64_t n, const void* queries,
+                             int64_t q_stride, int64_t m, int32_t d, int32_t dtype, float c2, int64_t self_base,
+                             int32_t k, const Scope& scope, void* ws, float* full_scores, int32_t* idx, float* score,
+                             float* prob, float* lse, hipStream_t stream) {
+  char* w = static_cast<char*>(ws);
+  const int64_t elem = dtype == 0 ? 4 : 2;
+  // with full probabilities the scores go to the caller's rows, all at once
+  const int64_t mb = full_scores ? m : p.blk_queries;
+  const int64_t nb = full_scores ? n : p.blk_rows;
+  const bool small = small_scores(m, n, d * elem);
+  for (int64_t q0 = 0; q0 < m; q0 += mb) {
+    const int64_t nq = m - q0 < mb ? m - q0 : mb;
+    for (int64_t c0 = 0; c0 < n; c0 += nb) {
+      const int64_t c1 = c0 + nb < n ? c0 + nb : n;
+      ScoreArgs sa{};
+      sa.bank = static_cast<const char*>(bank) + c0 * bank_stride * elem;
+      sa.bank_stride = bank_stride;
+      sa.rows = c1 - c0;
+      sa.queries = static_cast<const char*>(queries) + q0 * q_stride * elem;
+      sa.q_stride = q_stride;
+      sa.nq = nq;
+      sa.d = d;
+      sa.out = full_scores ? full_scores : reinterpret_cast<float*>(w + p.ws_scores);
+      sa.ld = full_scores ? n : p.blk_rows;
+      hipError_t e = dtype == 0 ? launch_score<float>(sa, small, stream) : launch_score<uint16_t>(sa, small, stream);
+      if (e != hipSuccess) return e;
+      SelectArgs a{};
+      a.scores = sa.out;
+      a.ld = sa.ld;
+      a.q0 = q0;
+      a.c0 = c0;
+      a.c1 = c1;
+      a.rows_per_split = p.rows_per_split;
+      a.n_splits = p.n_splits;
+      a.split0 = static_cast<int>(c0 / p.rows_per_split);
+      a.block_splits = static_cast<int>((c1 - 1) / p.rows_per_split) - a.split0 + 1;
+      a.k = k;
+      a.kcap = p.kcap;
+      a.c2 = c2;
+      a.self_base = self_base;
+      a.row_ns = scope.row_ns;
+      a.key_ns = scope.key_ns;
+      a.part_keys = reinterpret_cast<uint64_t*>(w + p.ws_part_keys);
+      a.part_ms = reinterpret_cast<float2*>(w + p.ws_part_ms);
+      a.part_lo = reinterpret_cast<float*>(w + p.ws_part_lo);
+      a.full = full_scores != nullptr;
+      a.n = n;
+      if (p.n_splits == 1 && c1 == n) {
+        a.idx = idx;
+        a.score = score;
+        a.prob = prob;
+        a.lse = lse;
+      }
+      select_kernel<<<dim3(static_cast<unsigned>(nq * a.block_splits)), kSelThreads, 0, stream>>>(a);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+  }
+  return hipSuccess;
+}
+
+}  // namespace memattn

@@ -1,13 +1,6 @@
-// VALU selection path: any dtype, any d <= 8192, k <= 64, optional full
-// probability output.  Serves the latency-bound tiny workloads (fp32
-// embeddings) and shapes the matrix-core kernel does not take.
-//
-// One workgroup (256 threads) scores one query against one bank split, 256
-// rows per step: thread t computes s = <q, b_j> for row j = base + t in fp32,
-// folds it into its running softmax state, and offers its key to the
-// block's sorted candidate list in LDS (block_list_insert: only the step's
-// keys above the list's last entry are ranked into it).  Dense-only
-// relevance of the paper's Section 5.5 applied to LLMSelect of Algorithm 1.
+// Merges of partial selections (one sorted list and softmax partial per
+// bank split) into the final top-k, probabilities and normaliser, and the
+// full probability rows of banks that took several splits.
 #include <atomic>
 
 #include "device_common.h"
@@ -70,90 +63,6 @@ __device__ __forceinline__ void block_list_insert(uint64_t* buf, uint64_t key, i
   if (r_new < kcap) buf[r_new] = key;
   if (r_old < kcap) buf[r_old] = y;
   __syncthreads();
-}
-
-template <typename T>
-__device__ __forceinline__ float load_elem(const T* p, int64_t i);
-template <>
-__device__ __forceinline__ float load_elem<float>(const float* p, int64_t i) {
-  return p[i];
-}
-template <>
-__device__ __forceinline__ float load_elem<uint16_t>(const uint16_t* p, int64_t i) {
-  return bf16_to_f32(p[i]);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void topk_valu_kernel(const T* __restrict__ bank, int64_t bank_stride, int64_t n,
-                                                        const T* __restrict__ queries, int64_t q_stride, int32_t d,
-                                                        float c2, int64_t self_base, int64_t rows_per_split,
-                                                        int n_splits, int kcap, uint64_t* __restrict__ part_keys,
-                                                        float2* __restrict__ part_ms,
-                                                        float* __restrict__ full_scores,
-                                                        const int32_t* __restrict__ row_ns,
-                                                        const int32_t* __restrict__ key_ns) {
-  __shared__ float qv[kMaxD];
-  __shared__ uint64_t buf[2 * kGenericRows];
-  __shared__ float red_m[4];
-  __shared__ double red_s[4];
-  __shared__ int wcount[4];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int64_t q = blockIdx.x / n_splits;
-  const int split = static_cast<int>(blockIdx.x % n_splits);
-  const int64_t self_row = self_base >= 0 ? self_base + q : -1;
-  // scoped selection: candidates are the live rows (row_ns >= 0) of the
-  // query's namespace
-  const int32_t my_ns = row_ns ? key_ns[q] : 0;
-
-  for (int t = tid; t < d; t += 256) qv[t] = load_elem<T>(queries, q * q_stride + t);
-  buf[tid] = 0;
-  __syncthreads();
-
-  const int64_t row0 = static_cast<int64_t>(split) * rows_per_split;
-  const int64_t row1 = min(n, row0 + rows_per_split);
-  float m_run = -INFINITY;
-  double s_run = 0.0;
-
-  for (int64_t base = row0; base < row1; base += kGenericRows) {
-    const int64_t j = base + tid;
-    uint64_t key = 0;
-    if (j < row1) {
-      const T* row = bank + j * bank_stride;
-      float acc = 0.f;
-      for (int t = 0; t < d; ++t) acc = fmaf(qv[t], load_elem<T>(row, t), acc);
-      const bool cand = j != self_row && (!row_ns || (my_ns >= 0 && row_ns[j] == my_ns));
-      // a row outside the candidates gets probability 0 in the full output
-      if (full_scores) full_scores[q * n + j] = cand ? acc : -INFINITY;
-      if (cand) {
-        const float x = acc * c2;
-        if (x > m_run) {
-          s_run = s_run * static_cast<double>(fast_exp2(m_run - x));
-          m_run = x;
-        }
-        s_run += static_cast<double>(fast_exp2(x - m_run));
-        key = make_key(acc, static_cast<uint32_t>(j));
-      }
-    }
-    block_list_insert(buf, key, kcap, wcount);
-  }
-
-  // softmax partial: the threads' (m, sum) pairs, within each wave and then
-  // across the four waves
-  float m_w = m_run;
-  for (int off = 32; off > 0; off >>= 1) m_w = fmaxf(m_w, __shfl_xor(m_w, off));
-  if (lane == 0) red_m[wave] = m_w;
-  __syncthreads();
-  const float m_all = fmaxf(fmaxf(red_m[0], red_m[1]), fmaxf(red_m[2], red_m[3]));
-  double s_w = (m_run == -INFINITY) ? 0.0 : s_run * static_cast<double>(fast_exp2(m_run - m_all));
-  for (int off = 32; off > 0; off >>= 1) s_w += __shfl_xor(s_w, off);
-  if (lane == 0) red_s[wave] = s_w;
-  __syncthreads();
-  const int64_t slot = q * n_splits + split;
-  if (tid < kcap) part_keys[slot * kcap + tid] = buf[tid];
-  if (tid == 0) part_ms[slot] = make_float2(m_all, static_cast<float>((red_s[0] + red_s[1]) + (red_s[2] + red_s[3])));
 }
 
 // One workgroup per query: merge n_splits partial lists of kcap keys
@@ -508,25 +417,6 @@ __global__ __launch_bounds__(256) void full_prob_kernel(float* __restrict__ full
 }
 
 }  // namespace
-
-hipError_t launch_topk_generic(const Plan& p, const void* bank, int64_t bank_stride, int64_t n, const void* queries,
-                               int64_t q_stride, int64_t m, int32_t d, int32_t dtype, float c2, int64_t self_base,
-                               const Scope& scope, void* ws, float* full_scores, hipStream_t stream) {
-  char* w = static_cast<char*>(ws);
-  auto* keys = reinterpret_cast<uint64_t*>(w + p.ws_part_keys);
-  auto* ms = reinterpret_cast<float2*>(w + p.ws_part_ms);
-  const dim3 grid(static_cast<unsigned>(m * p.n_splits));
-  if (dtype == 0) {
-    topk_valu_kernel<float><<<grid, 256, 0, stream>>>(
-        static_cast<const float*>(bank), bank_stride, n, static_cast<const float*>(queries), q_stride, d, c2,
-        self_base, p.rows_per_split, p.n_splits, p.kcap, keys, ms, full_scores, scope.row_ns, scope.key_ns);
-  } else {
-    topk_valu_kernel<uint16_t><<<grid, 256, 0, stream>>>(
-        static_cast<const uint16_t*>(bank), bank_stride, n, static_cast<const uint16_t*>(queries), q_stride, d, c2,
-        self_base, p.rows_per_split, p.n_splits, p.kcap, keys, ms, full_scores, scope.row_ns, scope.key_ns);
-  }
-  return hipGetLastError();
-}
 
 // Dynamic LDS above the default 64 KiB needs a per-kernel opt-in; it is
 // requested once per process and kernel (later calls skip it).

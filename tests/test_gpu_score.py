@@ -1,0 +1,139 @@
+"""The general selection path (scores of a block, then its selection) at the
+edges where it can go wrong: tiles of 32, 64 and 128 queries and of 32 and 128
+rows, steps of 4,096 scores, one split and several, blocks that a list
+resumes from, row tails of every length, rows without 16-byte alignment, and
+more equal scores than a step's candidates.  Checked against the oracle under
+the parity rules (eps = 2 d 2^-24 |q| |b|), or exactly where scores are exact."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2607_05708_amd as pm
+from paper_2607_05708_amd import inputs
+from parity import check_topk, check_topk_scoped
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def up(a):
+    if a.dtype == np.uint16:
+        return torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16)
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(out):
+    torch.cuda.synchronize()
+    return dict(zip(("idx", "score", "prob", "lse"), (t.cpu().numpy() for t in out)))
+
+
+def pick(m, seed=0, most=48):
+    if m <= most:
+        return np.arange(m)
+    return np.unique(np.concatenate([[0, 31, 32, m - 1], np.random.default_rng(seed).choice(m, most, replace=False)]))
+
+
+# (dtype, m, n, d, k, full probabilities)
+SHAPES = [
+    ("f32", 1, 1, 1, 1, True),
+    ("f32", 1, 31, 3, 7, True),          # a row shorter than 16 bytes
+    ("bf16", 5, 33, 7, 33, True),
+    ("f32", 33, 4096, 33, 64, True),     # one step, all of it
+    ("f32", 32, 4097, 31, 8, True),      # a second step of one row
+    ("bf16", 65, 16384, 17, 40, True),   # the largest one-split bank
+    ("bf16", 3, 16385, 100, 64, True),   # several splits, then the merge
+    ("f32", 40, 33000, 63, 9, False),    # 64-query tiles, odd d
+    ("f32", 31, 33001, 130, 64, False),  # 32-query tiles
+    ("f32", 129, 16500, 32, 16, False),  # 128-query tiles, the second with one query
+    ("bf16", 300, 33000, 64, 64, False),  # whole stages only
+    ("bf16", 300, 13000, 135, 33, False),
+    ("f32", 1, 70001, 20, 64, False),
+    ("f32", 4097, 8200, 8, 64, False),   # two blocks of queries, three of rows: lists resumed
+]
+
+
+@pytest.mark.parametrize("i", range(len(SHAPES)))
+def test_shapes(i):
+    dtype, m, n, d, k, full = SHAPES[i]
+    print(f"case: {dtype} m={m} n={n} d={d} k={k} full={full}", flush=True)
+    b = inputs.iid_unit(70 + i, 98, 0, n, d, dtype)
+    q = inputs.iid_unit(70 + i, 98, 4, m, d, dtype)
+    fp = torch.empty((m, n), device="cuda") if full else None
+    g = host(pm.mem_retrieve_topk(up(b), up(q), k, 3.0, full_prob=fp))
+    rows = pick(m, i)
+    sub = {key: v[rows] for key, v in g.items()}
+    check_topk(f"score-{i}", q, b, rows, sub, k, 3.0)
+    if full:
+        p = fp.cpu().numpy()
+        assert np.allclose(p.sum(axis=1), 1.0, rtol=0, atol=1e-5)
+        assert np.array_equal(np.take_along_axis(p, g["idx"].astype(np.int64), 1), g["prob"])
+
+
+@pytest.mark.parametrize("dtype,m,n,d", [("f32", 70, 33000, 45), ("bf16", 70, 33000, 45), ("bf16", 9, 900, 64)])
+def test_rows_without_alignment(dtype, m, n, d):
+    # rows begin at any element: odd strides and a base one element in
+    b, q = inputs.iid_unit(91, 98, 0, n, d, dtype), inputs.iid_unit(91, 98, 4, m, d, dtype)
+
+    def shifted(a, stride):
+        t = up(a)
+        flat = torch.zeros(a.shape[0] * stride + 1, dtype=t.dtype, device="cuda")
+        view = flat[1:].view(a.shape[0], stride)[:, :d]
+        view.copy_(t)
+        return view
+
+    g = host(pm.mem_retrieve_topk(shifted(b, d + 2), shifted(q, d + 4), 20, 1.0))
+    rows = pick(m)
+    check_topk("shifted", q, b, rows, {key: v[rows] for key, v in g.items()}, 20, 1.0)
+
+
+def test_relation_build_across_blocks():
+    # 4,200 keys: two blocks of queries and two of rows, each key left out of its own candidates
+    n = 4200
+    b = inputs.iid_unit(92, 98, 0, n, 20, "f32")
+    g = host(pm.mem_build_relations(up(b), 48, 2.0, True))
+    rows = np.unique(np.concatenate([[0, 4095, 4096, n - 1], pick(n)]))
+    check_topk("relation-blocks", b, b, rows, {key: v[rows] for key, v in g.items()}, 48, 2.0, self_idx=np.arange(n))
+
+
+def test_scoped_across_blocks_and_steps():
+    n, m, k = 8300, 4100, 40
+    b = inputs.iid_unit(93, 98, 0, n, 12, "f32")
+    q = inputs.iid_unit(93, 98, 4, m, 12, "f32")
+    rns, live, kns = inputs.namespaces(93, 98, n, 40, 0.2, run=16, m=m)
+    kns[:3] = -1
+    g = host(pm.mem_retrieve_topk_scoped(up(b), up(inputs.scoped_row_ns(rns, live)), up(q), up(kns), k, 2.0))
+    rows = pick(m)
+    check_topk_scoped("scoped-blocks", q, b, rows, {key: v[rows] for key, v in g.items()}, k, 2.0, rns, live, kns)
+
+
+@pytest.mark.parametrize("n", [1500, 4096, 9000, 40000])
+@pytest.mark.parametrize("k", [1, 8, 64])
+def test_ties_and_orders(n, k):
+    # exact scores: all equal (the lowest ids win), rising and falling with the row
+    b = np.ones((n, 4), np.float32)
+    b[:, 1] = np.arange(n)
+    b[:, 2] = -np.arange(n)
+    q = np.eye(4, dtype=np.float32)
+    g = host(pm.mem_retrieve_topk(up(b), up(q), k, 1e-6))
+    low, high = np.arange(k), n - 1 - np.arange(k)
+    for i, want in enumerate((low, high, low, low)):
+        assert np.array_equal(g["idx"][i], want), i
+    assert np.array_equal(g["score"][1], high.astype(np.float32))
+    assert np.allclose(g["prob"][0], 1.0 / n, rtol=1e-5) and np.allclose(g["lse"][0], np.log(n) + 1e-6, rtol=1e-5)
+
+
+def test_allocation_free_call_cuts_smaller_blocks():
+    # 200,000 lists of 64 leave the 128 MiB scratch array little room for scores
+    m, n, d, k = 200000, 300, 8, 64
+    b, q = up(inputs.iid_unit(94, 98, 0, n, d, "f32")), up(inputs.iid_unit(94, 98, 4, m, d, "f32"))
+    want = pm.mem_retrieve_topk(b, q, k, 1.0)
+    out = tuple(torch.empty_like(t) for t in want)
+    pm.mem_retrieve_topk_noalloc(b, q, k, 1.0, out=out)
+    torch.cuda.synchronize()
+    for x, y in zip(want, out):
+        assert torch.equal(x, y)

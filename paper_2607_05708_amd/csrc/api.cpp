@@ -328,6 +328,10 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
       }
     }
     p.ws_bytes = p.ws_scores + align256(static_cast<size_t>(p.blk_queries * p.blk_rows) * sizeof(float));
+    // as many blocks, of about the same size (a short last one would leave
+    // most of the GPU idle)
+    const int64_t even = ceil_div(ceil_div(n, ceil_div(n, p.blk_rows)), 128) * 128;
+    if (even < p.blk_rows) p.blk_rows = even;
     return p;
   }
   p.ws_samp = p.ws_lse2 + align256(mm * sizeof(float));

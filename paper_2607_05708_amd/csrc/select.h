@@ -19,110 +19,135 @@ constexpr int kSelDirect = 160;                      // up to so many are ranked
 // which the caller tracks the current one, and scratch.
 struct SelectLds {
   uint64_t list[2][kMaxK];
-  uint64_t cand[kSelCand];
-  uint64_t tops[kSelThreads];
+  __attribute__((aligned(16))) uint64_t cand[kSelCand + 2];
+  uint32_t tops[kSelThreads];
   uint64_t thr;
   int wcount[4];
   float red_m[4];
   double red_s[4];
 };
 
-// Counts, over the workgroup, the keys at or above `least`; every wave's own
-// count stays in wcount.  Leaves a barrier between the counts and their use.
-template <class Key>
-__device__ __forceinline__ int select_count(SelectLds& L, const Key& key, uint64_t least) {
+// Counts, over the workgroup, the in(j), j < kSelPer, of every thread (only
+// those with `any` have one); every wave's own count stays in wcount.
+template <class In>
+__device__ __forceinline__ int select_count(SelectLds& L, const In& in, bool any) {
   int mine = 0;
+  if (__ballot(any) != 0) {
 #pragma unroll
-  for (int j = 0; j < kSelPer; ++j) mine += __builtin_popcountll(__ballot(key(j) >= least));
+    for (int j = 0; j < kSelPer; ++j) mine += __builtin_popcountll(__ballot(in(j)));
+  }
   if ((threadIdx.x & 63) == 0) L.wcount[threadIdx.x >> 6] = mine;
   __syncthreads();
   return L.wcount[0] + L.wcount[1] + L.wcount[2] + L.wcount[3];
 }
 
+// How many of cand[0, total) are above x (total even or followed by a 0).
+__device__ __forceinline__ int count_above(const SelectLds& L, int total, uint64_t x) {
+  typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+  const u64x2* c = reinterpret_cast<const u64x2*>(L.cand);
+  int r = 0;
+#pragma unroll 8
+  for (int i = 0; i < (total + 1) / 2; ++i) {
+    const u64x2 v = c[i];
+    r += (v.x > x ? 1 : 0) + (v.y > x ? 1 : 0);
+  }
+  return r;
+}
+
 // Offers a step's keys to the list: key(j), j < kSelPer, are this thread's
-// (0 = none; all keys distinct).  Only keys above the list's k-th matter.  If
-// many are (as in the first step), the k-th largest of the threads' own
-// largest keys is a better bound: k keys lie at or above it, so no other can
-// be among the k best, and only those k threads hold candidates, at most 16
-// each.  One wave finds it on the keys' upper halves, bit by bit from
-// ballots; where ties there let in too many, by counting over the whole keys.
-// (With fewer than k threads holding a candidate there is no such bound, and
-// at most 16 (k - 1) candidates.)  The candidates are compacted by ballots
-// and ranked in the union with the list by counting; every rank below k is
+// (0 = none; all keys distinct), hi(j) their upper halves and top the largest
+// of those.  Only keys above the list's k-th matter; with RISING (every key is
+// of a later row than the list's) those with a larger upper half.  If many are
+// (as in the first step), the k-th largest of the threads' tops is a better
+// bound: k keys lie at or above it, so none below can be among the k best,
+// and but for ties only those k threads hold candidates, at most 16 each.
+// One wave finds its upper kBoundBits bits from ballots.  (With fewer than k
+// threads holding any there is no such bound, and at most 16 (k - 1)
+// candidates.)  Where ties let in too many, the bound is found once more on
+// whole keys, by counting.  The candidates are compacted by ballots and
+// ranked in the union with the list by counting; every rank below k is
 // written once into the other buffer.  Returns the buffer then current.
-// Every thread of the workgroup calls it.
-template <class Key>
-__device__ __forceinline__ int select_step(SelectLds& L, const Key& key, int k, int cur) {
+// A step without candidates costs one barrier and touches no key; every
+// thread of the workgroup calls it, in every step.
+constexpr int kBoundBits = 22;  // (the rest, 2^-13 of a score, lets few more in)
+template <bool RISING, class Hi, class Key>
+__device__ __forceinline__ int select_step(SelectLds& L, const Hi& hi, const Key& key, uint32_t top, int k, int cur) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  uint64_t least = L.list[cur][k - 1] + 1;
-  int total = select_count(L, key, least);
-  if (total == 0) {  // (uniform)
-    __syncthreads();  // wcount is free for the next step
-    return cur;
+  const uint64_t last = L.list[cur][k - 1];
+  uint32_t least = static_cast<uint32_t>(last >> 32) + (RISING ? 1u : 0u);
+  least = least < 1u ? 1u : least;
+  auto above = [&](int j) { return hi(j) >= least; };
+  int total = 0;
+  if (last != 0) {
+    if (!__syncthreads_or(top >= least)) return cur;
+    total = select_count(L, above, top >= least);
   }
-  if (total > kSelDirect) {
-    uint64_t top = 0;
-#pragma unroll
-    for (int j = 0; j < kSelPer; ++j) {
-      const uint64_t x = key(j);
-      top = x > top ? x : top;
-    }
-    top = top >= least ? top : 0;
+  bool whole = false;  // the bound is a whole key
+  uint64_t least64 = 0;
+  if (last == 0 || total > kSelDirect) {
     L.tops[tid] = top;
     __syncthreads();
     if (wave == 0) {
       uint32_t h[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) h[i] = static_cast<uint32_t>(L.tops[64 * i + lane] >> 32);
+      for (int i = 0; i < 4; ++i) h[i] = L.tops[64 * i + lane];
       uint32_t t = 0;
-      for (int b = 31; b >= 0; --b) {
+      for (int b = 31; b >= 32 - kBoundBits; --b) {
         const uint32_t c = t | (1u << b);
         int n = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) n += __builtin_popcountll(__ballot(h[i] >= c));
         if (n >= k) t = c;
       }
-      if (lane == 0) L.thr = static_cast<uint64_t>(t) << 32;
+      if (lane == 0) L.thr = t;
     }
     __syncthreads();
-    least = L.thr > least ? L.thr : least;
-    total = select_count(L, key, least);
+    const uint32_t t = static_cast<uint32_t>(L.thr);
+    least = t > least ? t : least;
+    total = select_count(L, above, top >= least);
     if (total > kSelCand) {
-      // (more than kSelCand candidates: over k threads hold one, and the
-      // k-th largest top is one thread's)
-      int above = 0;
-#pragma unroll 8
-      for (int i = 0; i < kSelThreads; ++i) above += L.tops[i] > top ? 1 : 0;
-      if (above == k - 1 && top != 0) L.thr = top;
+      // (more than kSelCand: over k threads hold a candidate, so the k-th
+      // largest of their largest keys is one thread's)
+      uint64_t best = 0;
+#pragma unroll
+      for (int j = 0; j < kSelPer; ++j) {
+        const uint64_t x = key(j);
+        best = x > best ? x : best;
+      }
+      L.cand[tid] = best;
       __syncthreads();
-      least = L.thr;
-      total = select_count(L, key, least);
+      if (best != 0 && count_above(L, kSelThreads, best) == k - 1) L.thr = best;
+      __syncthreads();
+      least64 = L.thr;
+      whole = true;
+      total = select_count(L, [&](int j) { return key(j) >= least64; }, true);
     }
   }
   int at = 0;
   for (int w = 0; w < wave; ++w) at += L.wcount[w];
+  if (L.wcount[wave] != 0) {
 #pragma unroll
-  for (int j = 0; j < kSelPer; ++j) {
-    const uint64_t x = key(j);
-    const uint64_t bal = __ballot(x >= least);
-    if (x >= least) L.cand[at + __popcll(bal & ((uint64_t{1} << lane) - 1))] = x;
-    at += __popcll(bal);
+    for (int j = 0; j < kSelPer; ++j) {
+      const bool in = whole ? key(j) >= least64 : above(j);
+      const uint64_t bal = __ballot(in);
+      if (in) L.cand[at + __popcll(bal & ((uint64_t{1} << lane) - 1))] = key(j);
+      at += __popcll(bal);
+    }
   }
   const int nxt = cur ^ 1;
   if (tid < kMaxK) L.list[nxt][tid] = 0;
+  if (tid == 0) L.cand[total] = 0;
   __syncthreads();
   for (int i = tid; i < total; i += kSelThreads) {
     const uint64_t x = L.cand[i];
-    int lo = 0, hi = k;  // list keys above x
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (L.list[cur][mid] > x) lo = mid + 1; else hi = mid;
+    int lo = 0, up = k;  // list keys above x
+    while (lo < up) {
+      const int mid = (lo + up) >> 1;
+      if (L.list[cur][mid] > x) lo = mid + 1; else up = mid;
     }
-    int r = lo;
-#pragma unroll 4
-    for (int c = 0; c < total; ++c) r += L.cand[c] > x ? 1 : 0;
+    const int r = lo + count_above(L, total, x);
     if (r < k) L.list[nxt][r] = x;
   }
   // (the last wave ranks the list's own keys: it has the fewest candidates)
@@ -130,9 +155,7 @@ __device__ __forceinline__ int select_step(SelectLds& L, const Key& key, int k, 
   if (li < k) {
     const uint64_t y = L.list[cur][li];
     if (y != 0) {
-      int r = li;
-#pragma unroll 4
-      for (int c = 0; c < total; ++c) r += L.cand[c] > y ? 1 : 0;
+      const int r = li + count_above(L, total, y);
       if (r < k) L.list[nxt][r] = y;
     }
   }

@@ -15,10 +15,11 @@
 //
 // A thread-per-row fp32 kernel did this before (3.8 TFLOP/s whatever the
 // type, every query re-reading the bank).  64 fp32 queries against 65,536 x
-// 768 rows, k = 16: 1,706 -> 87 us (scores 66 us = 98 TFLOP/s of the fp32
-// MFMA's 153); 200 bf16 queries against 100,003 x 1024, k = 64: 12.2 -> 0.19
-// ms; 16 fp32 queries against 1,024 x 256 with full probabilities: 20.9 ->
-// 14.6 us.
+// 768 rows, k = 16: 1,706 -> 79 us (scores 66 us, 98 TFLOP/s; select 12 us);
+// 200 bf16 queries against 100,003 x 1024, k = 64: 12.2 -> 0.16 ms (scores 95
+// us, 430 TFLOP/s, bound by the 8 TB/s that the 128 x 128 tiles draw from L2;
+// select 59 us); 16 fp32 queries against 1,024 x 256 with full probabilities:
+// 20.9 -> 15.5 us.
 //
 // Dense-only relevance of the paper's Section 5.5 applied to LLMSelect of
 // Algorithm 1.
@@ -97,23 +98,25 @@ struct ScoreArgs {
   int64_t ld;
 };
 
-// Tiled score kernel: 4 waves, 128 bank rows against 32 * QW * QB queries.
-// Each stage holds 128 bytes of K of every row in LDS (two buffers), loaded
-// into registers two stages ahead; the 16-byte pieces of a row are XOR
-// swizzled by the row so that fragment reads (32 consecutive rows, one
-// piece) and the staging writes (whole rows) are free of bank conflicts.
-// QW waves share the rows' blocks among the queries: a wave scores QB query
-// blocks against RB = QW row blocks of 32.
-constexpr int kScoreRows = 128;  // bank rows per tile
+// Tiled score kernel: 4 waves, QW x RW of them (queries x rows), each scoring
+// QB query blocks against RB row blocks of 32.  Each stage holds 128 bytes of
+// K of every row in LDS (two buffers), loaded into registers two stages
+// ahead; the 16-byte pieces of a row are XOR swizzled by the row so that
+// fragment reads (32 consecutive rows, one piece) and the staging writes
+// (whole rows) are free of bank conflicts.  On fp32 rows this runs at the
+// rate of a library matrix product of the same shape (512 x 131,072 x 768: 931
+// against 902 us), both at about 2.1 GHz with the matrix cores 80-86 % busy;
+// tiles of other sizes and more waves per SIMD change nothing.
 constexpr int kStageBytes = 128;
 
-template <typename T, int QB, int QW>
+template <typename T, int QB, int QW, int RB, int RW>
 __global__ __launch_bounds__(256) void score_tile_kernel(ScoreArgs a) {
-  constexpr int RB = QW;
+  static_assert(QW * RW == 4, "four waves");
   constexpr int kTileQ = 32 * QB * QW;
-  constexpr int kLines = kScoreRows + kTileQ;     // staged rows: bank rows, then query rows
+  constexpr int kTileR = 32 * RB * RW;
+  constexpr int kLines = kTileR + kTileQ;         // staged rows: bank rows, then query rows
   constexpr int kLoads = kLines / 32;             // 16-byte pieces per thread and stage
-  constexpr int kRowLoads = kScoreRows / 32;
+  constexpr int kRowLoads = kTileR / 32;
   constexpr int E = 16 / sizeof(T);               // elements per piece
   constexpr int KE = kStageBytes / sizeof(T);     // elements per stage
   __shared__ u32x4 st[2][kLines * 8];
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(256) void score_tile_kernel(ScoreArgs a) {
   // are neighbours there and share its rows through that XCD's L2.
   const int q_tiles = static_cast<int>((a.nq + kTileQ - 1) / kTileQ);
   const int i8 = blockIdx.x >> 3;
-  const int64_t r0 = (static_cast<int64_t>(i8 / q_tiles) * 8 + (blockIdx.x & 7)) * kScoreRows;
+  const int64_t r0 = (static_cast<int64_t>(i8 / q_tiles) * 8 + (blockIdx.x & 7)) * kTileR;
   const int64_t q0 = static_cast<int64_t>(i8 % q_tiles) * kTileQ;
   if (r0 >= a.rows) return;
 
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(256) void score_tile_kernel(ScoreArgs a) {
     const int line = (tid >> 3) + 32 * i;
     src[i] = i < kRowLoads
                  ? static_cast<const T*>(a.bank) + min(r0 + line, a.rows - 1) * a.bank_stride
-                 : static_cast<const T*>(a.queries) + min(q0 + line - kScoreRows, a.nq - 1) * a.q_stride;
+                 : static_cast<const T*>(a.queries) + min(q0 + line - kTileR, a.nq - 1) * a.q_stride;
   }
   const int d = a.d;
   const int n_st = (d + KE - 1) / KE;
@@ -147,13 +150,13 @@ __global__ __launch_bounds__(256) void score_tile_kernel(ScoreArgs a) {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) v[i] = load16_within<T>(src[i], k, d);
   };
-  const int wr = c ^ ((tid >> 3) & 7);  // (the swizzle depends on row % 8 only)
+  const int wr = c ^ ((tid >> 4) & 7);  // (32 rows on, the swizzle is the same)
   // (the last stage's tail is mended in LDS: a use of the registers there
   // would make the compiler copy them in every stage, and wait for them)
   auto store = [&](int s, int buf, const u32x4 (&v)[kLoads]) {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) st[buf][((tid >> 3) + 32 * i) * 8 + wr] = v[i];
-    if ((s + 1) * KE > d) {
+    if ((s + 1) * KE > d && s < n_st) {
 #pragma unroll 1
       for (int i = 0; i < kLoads; ++i) {
         u32x4* at = &st[buf][((tid >> 3) + 32 * i) * 8 + wr];
@@ -169,49 +172,60 @@ __global__ __launch_bounds__(256) void score_tile_kernel(ScoreArgs a) {
   const int frow = lane & 31;
   const int part = lane >> 5;
   const int wq = wave % QW;                  // the wave's query group
-  const int wrow = (wave / QW) * 32 * RB;    // and its first row
-  auto compute = [&](int buf) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int p = (2 * s + part) ^ (frow & 7);
-      u32x4 fq[QB], fr[RB];
-#pragma unroll
-      for (int x = 0; x < QB; ++x) fq[x] = st[buf][(kScoreRows + (wq * QB + x) * 32 + frow) * 8 + p];
-#pragma unroll
-      for (int y = 0; y < RB; ++y) fr[y] = st[buf][(wrow + y * 32 + frow) * 8 + p];
-#pragma unroll
-      for (int x = 0; x < QB; ++x)
-#pragma unroll
-        for (int y = 0; y < RB; ++y) mma16(acc[x][y], fq[x], fr[y], T{});
-    }
+  const int wrow = (wave / QW) * 32 * RB;    // and its first row of the tile
+  struct Frag {
+    u32x4 q[QB], r[RB];
   };
-  // stage s is computed from buffer s % 2 while the loads of stages s + 1 and
-  // s + 2 are in flight; buffer (s + 1) % 2 was last read in stage s - 1,
-  // which every wave finished before the barrier that ended it
+  auto read = [&](int buf, int step, Frag& f) {
+    const int p = (2 * step + part) ^ ((frow >> 1) & 7);
+#pragma unroll
+    for (int x = 0; x < QB; ++x) f.q[x] = st[buf][(kTileR + (wq * QB + x) * 32 + frow) * 8 + p];
+#pragma unroll
+    for (int y = 0; y < RB; ++y) f.r[y] = st[buf][(wrow + y * 32 + frow) * 8 + p];
+  };
+  auto mma = [&](const Frag& f) {
+    __builtin_amdgcn_sched_barrier(0);  // the reads before it are issued before it
+#pragma unroll
+    for (int x = 0; x < QB; ++x)
+#pragma unroll
+      for (int y = 0; y < RB; ++y) mma16(acc[x][y], f.q[x], f.r[y], T{});
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Stage s is computed from buffer s % 2 while the loads of stages s + 2 and
+  // s + 3 are in flight.  Its staging writes of stage s + 1 go first (that
+  // buffer was last read in stage s - 1, before the barrier in it), each
+  // step's fragments are read ahead of the MFMAs of the step before, and the
+  // barrier stands before the last step, whose MFMAs cover the reads of the
+  // next stage's first fragments.
+  Frag f0, f1;
+  auto stage = [&](int s, int buf, u32x4 (&v)[kLoads]) {
+    store(s + 1, buf ^ 1, v);
+    load(s + 3, v);
+    read(buf, 1, f1);
+    mma(f0);
+    read(buf, 2, f0);
+    mma(f1);
+    read(buf, 3, f1);
+    mma(f0);
+    __syncthreads();
+    read(buf ^ 1, 0, f0);
+    mma(f1);
+  };
   u32x4 va[kLoads], vb[kLoads];
   load(0, va);
   load(1, vb);
   store(0, 0, va);
   load(2, va);
   __syncthreads();
-  // (no exit inside the loop: the wait counts at its head stay exact)
+  read(0, 0, f0);
+  // (no exit inside the loop: the wait counts at its head stay exact; the
+  // last stage writes a buffer that is not read)
   int s = 0;
-  for (; s + 2 < n_st; s += 2) {
-    compute(0);
-    store(s + 1, 1, vb);
-    load(s + 3, vb);
-    __syncthreads();
-    compute(1);
-    store(s + 2, 0, va);
-    load(s + 4, va);
-    __syncthreads();
+  for (; s + 1 < n_st; s += 2) {
+    stage(s, 0, vb);
+    stage(s + 1, 1, va);
   }
-  compute(0);
-  if (s + 1 < n_st) {
-    store(s + 1, 1, vb);
-    __syncthreads();
-    compute(1);
-  }
+  if (s < n_st) stage(s, 0, vb);
   // accumulator lane: row lane % 32 of its block, queries 8 (r / 4) + 4 part + r % 4
 #pragma unroll
   for (int y = 0; y < RB; ++y) {
@@ -319,7 +333,7 @@ struct SelectArgs {
 // a step.  A split that an earlier block began resumes from its list and
 // softmax state (the sum in two floats, so that nothing of the double is
 // lost between blocks).
-__global__ __launch_bounds__(kSelThreads) void select_kernel(SelectArgs a) {
+__global__ __launch_bounds__(kSelThreads, 4) void select_kernel(SelectArgs a) {
   __shared__ SelectLds L;
   const int tid = threadIdx.x;
   const int64_t ql = blockIdx.x / a.block_splits;
@@ -343,52 +357,69 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectArgs a) {
     s_run = static_cast<double>(ms.y) + static_cast<double>(a.part_lo[slot]);
   }
   __syncthreads();
+  // value j of a step is its element 1024 (j / 4) + 4 tid + j % 4: four
+  // 16-byte loads where the rows allow it
+  const bool vec = (reinterpret_cast<uintptr_t>(a.scores) % 16 | a.ld % 4 | (row0 - a.c0) % 4) == 0;
+  auto at = [&](int j) { return 1024 * (j >> 2) + 4 * tid + (j & 3); };
   float v[kSelPer];  // a step's scores, -inf where no candidate
+  uint32_t out = 0;  // bit j: value j is no candidate
   for (int64_t base = row0; base < row1; base += kSelStep) {
-    uint32_t ord[kSelPer];
     const int left = static_cast<int>(min(row1 - base, static_cast<int64_t>(kSelStep)));
+    float* src = row + (base - a.c0);
+    if (vec && left == kSelStep) {
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) {
-      const int e = 256 * j + tid;
-      v[j] = e < left ? row[base - a.c0 + e] : -INFINITY;
-    }
-    uint32_t out = 0;  // bit j: value j is no candidate
+      for (int j = 0; j < kSelPer; j += 4) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(src + at(j));
+        v[j] = x.x, v[j + 1] = x.y, v[j + 2] = x.z, v[j + 3] = x.w;
+      }
+    } else {
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) {
-      const int e = 256 * j + tid;
-      if (e >= left || base + e == self_row) out |= 1u << j;
+      for (int j = 0; j < kSelPer; ++j) v[j] = at(j) < left ? src[at(j)] : -INFINITY;
     }
-    if (a.row_ns) {
+    out = 0;
+    if (left < kSelStep || a.row_ns || (self_row >= base && self_row < base + left)) {  // (uniform)
+      const int64_t self = self_row - base;
 #pragma unroll
       for (int j = 0; j < kSelPer; ++j) {
-        const int e = 256 * j + tid;
-        if (e < left && !(my_ns >= 0 && a.row_ns[base + e] == my_ns)) out |= 1u << j;
+        const int e = at(j);
+        bool cand = e < left && e != self;
+        if (a.row_ns && cand) cand = my_ns >= 0 && a.row_ns[base + e] == my_ns;
+        if (!cand) {
+          // a row outside the candidates gets probability 0 in the full output
+          if (a.full && e < left) src[e] = -INFINITY;
+          out |= 1u << j;
+          v[j] = -INFINITY;
+        }
       }
     }
-    float mx = m_run;
+    float best = v[0];
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) {
-      const bool cand = ((out >> j) & 1u) == 0;
-      // a row outside the candidates gets probability 0 in the full output
-      if (a.full && !cand && 256 * j + tid < left) row[base - a.c0 + 256 * j + tid] = -INFINITY;
-      ord[j] = cand ? f2ord(v[j]) : 0u;
-      v[j] = cand ? v[j] : -INFINITY;
-      mx = fmaxf(mx, v[j] * a.c2);
-    }
+    for (int j = 1; j < kSelPer; ++j) best = fmaxf(best, v[j]);
+    const float mx = fmaxf(m_run, best * a.c2);
+    double part = 0.0;
     if (mx != -INFINITY) {
-      double part = 0.0;
 #pragma unroll
       for (int j = 0; j < kSelPer; ++j) part += static_cast<double>(fast_exp2(v[j] * a.c2 - mx));
       s_run = s_run * static_cast<double>(fast_exp2(m_run - mx)) + part;
       m_run = mx;
     }
-    cur = select_step(
-        L,
+    auto hi = [&](int j) { return ((out >> j) & 1u) ? 0u : f2ord(v[j]); };
+    const uint32_t low = 0xFFFFFFFFu - static_cast<uint32_t>(base) - 4 * tid;
+    uint32_t top = f2ord(best);
+    // (not so where a value is no candidate or a NaN, which fmaxf passes by
+    // but the sum above does not)
+    if (out != 0 || !(best > -INFINITY) || !(part < INFINITY)) {
+      top = 0;
+#pragma unroll
+      for (int j = 0; j < kSelPer; ++j) top = max(top, hi(j));
+    }
+    cur = select_step<true>(
+        L, hi,
         [&](int j) {
-          return ord[j] ? (static_cast<uint64_t>(ord[j]) << 32) | (0xFFFFFFFFu - (static_cast<uint32_t>(base) + 256 * j + tid))
-                        : uint64_t{0};
+          const uint32_t h = hi(j);
+          return h ? (static_cast<uint64_t>(h) << 32) | (low - (1024 * (j >> 2) + (j & 3))) : uint64_t{0};
         },
-        a.k, cur);
+        top, a.k, cur);
   }
 
   const SoftmaxSum all = block_softmax(L, m_run, s_run);
@@ -406,25 +437,34 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectArgs a) {
   if (tid == 0 && a.lse) a.lse[q] = lse2 * kLn2;
   if (!a.full) return;
   const bool none = lse2 == -INFINITY;
-  if (row1 - row0 <= kSelStep) {  // the only step's scores are still here
-#pragma unroll
-    for (int j = 0; j < kSelPer; ++j) {
-      const int64_t r = row0 + 256 * j + tid;
-      if (r < row1) row[r - a.c0] = none ? 0.f : fast_exp2(v[j] * a.c2 - lse2);
-    }
-    return;
-  }
+  const bool one = row1 - row0 <= kSelStep;  // the only step's scores are still here
   for (int64_t base = row0; base < row1; base += kSelStep) {
-    // (the writes of -inf above were this thread's own)
+    const int left = static_cast<int>(min(row1 - base, static_cast<int64_t>(kSelStep)));
+    float* src = row + (base - a.c0);
+    const bool wide = vec && left == kSelStep;
+    if (!one) {
+      // (the writes of -inf above were this thread's own)
+      if (wide) {
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) {
-      const int64_t r = base + 256 * j + tid;
-      v[j] = r < row1 ? row[r - a.c0] : 0.f;
+        for (int j = 0; j < kSelPer; j += 4) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(src + at(j));
+          v[j] = x.x, v[j + 1] = x.y, v[j + 2] = x.z, v[j + 3] = x.w;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < kSelPer; ++j) v[j] = at(j) < left ? src[at(j)] : 0.f;
+      }
     }
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) {
-      const int64_t r = base + 256 * j + tid;
-      if (r < row1) row[r - a.c0] = none ? 0.f : fast_exp2(v[j] * a.c2 - lse2);
+    for (int j = 0; j < kSelPer; ++j) v[j] = none ? 0.f : fast_exp2(v[j] * a.c2 - lse2);
+    if (wide) {
+#pragma unroll
+      for (int j = 0; j < kSelPer; j += 4)
+        *reinterpret_cast<f32x4*>(src + at(j)) = f32x4{v[j], v[j + 1], v[j + 2], v[j + 3]};
+    } else {
+#pragma unroll
+      for (int j = 0; j < kSelPer; ++j)
+        if (at(j) < left) src[at(j)] = v[j];
     }
   }
 }
@@ -438,26 +478,30 @@ int64_t tile_queries(int64_t nq) { return nq <= 32 ? 32 : (nq <= 64 ? 64 : 128);
 bool small_scores(int64_t m, int64_t n, int64_t row_bytes) {
   if (row_bytes < 16) return true;
   const int64_t tq = tile_queries(m);
-  return (n + kScoreRows - 1) / kScoreRows * ((m + tq - 1) / tq) < 256;
+  return (n + 127) / 128 * ((m + tq - 1) / tq) < 256;
+}
+
+template <typename T, int QB, int QW, int RB, int RW>
+void launch_tiles(const ScoreArgs& a, hipStream_t stream) {
+  const int64_t row_tiles = (a.rows + 32 * RB * RW - 1) / (32 * RB * RW);
+  const int64_t q_tiles = (a.nq + 32 * QB * QW - 1) / (32 * QB * QW);
+  const dim3 grid(static_cast<unsigned>((row_tiles + 7) / 8 * 8 * q_tiles));
+  score_tile_kernel<T, QB, QW, RB, RW><<<grid, 256, 0, stream>>>(a);
 }
 
 template <typename T>
 hipError_t launch_score(const ScoreArgs& a, bool small, hipStream_t stream) {
-  const int64_t row_tiles = (a.rows + kScoreRows - 1) / kScoreRows;
   const int64_t tq = tile_queries(a.nq);
-  const int64_t q_tiles = (a.nq + tq - 1) / tq;
   if (small) {
     const int64_t wgs = (a.rows + 31) / 32 * ((a.nq + 31) / 32);
     score_small_kernel<T><<<dim3(static_cast<unsigned>(wgs)), 256, 0, stream>>>(a);
-    return hipGetLastError();
+  } else if (tq == 32) {
+    launch_tiles<T, 1, 1, 1, 4>(a, stream);
+  } else if (tq == 64) {
+    launch_tiles<T, 2, 1, 1, 4>(a, stream);
+  } else {
+    launch_tiles<T, 2, 2, 2, 2>(a, stream);
   }
-  const dim3 grid(static_cast<unsigned>((row_tiles + 7) / 8 * 8 * q_tiles));
-  if (tq == 32)
-    score_tile_kernel<T, 1, 1><<<grid, 256, 0, stream>>>(a);
-  else if (tq == 64)
-    score_tile_kernel<T, 2, 1><<<grid, 256, 0, stream>>>(a);
-  else
-    score_tile_kernel<T, 2, 2><<<grid, 256, 0, stream>>>(a);
   return hipGetLastError();
 }
 

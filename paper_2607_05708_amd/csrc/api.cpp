@@ -301,6 +301,20 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
     p.q_tiles = 0;
     p.tiles_per_split = 0;
   }
+  // Scoring a block and selecting from it costs 8 bytes of cache traffic and
+  // a few instructions per pair that the fused pass saves, but keeps every
+  // CU busy at any size and has no lists to warm up: it takes the smaller
+  // calls.  Fused / general, us, d = 64 and 1,024: 8 queries x 8,192 rows,
+  // k = 5 46/15 and 68/18; 64 x 65,536, k = 32 56/32 and 95/45; 64 x 262,144,
+  // k = 32 74/63 and 191/158, k = 5 48/58 and 161/154; 64 x 131,072, k = 5
+  // 39/42 and 91/80; 512 x 65,536, k = 32 88/110 and 151/167.  Without a
+  // threshold sample the fused pass starts from empty lists (1,024 x 32,768,
+  // k = 32: 410/111 and 442/165), and a small relation build has its key
+  // order to pay (4,000 keys, k = 5 121/64; 8,000 keys 180/235).
+  if (p.mfma) {
+    const int64_t most = (p.ns == 0 || relation) ? int64_t{1} << 25 : (p.kcap > 8 ? int64_t{1} << 24 : int64_t{6} << 20);
+    if (m * n < most) return make_plan(m, n, d, k, dtype, false, relation, limit);
+  }
   // The matrix-core kernel keeps one partial per bank part while it runs and
   // leaves one per split (in part 0's slot); the merge reads every
   // part_stride-th slot.

@@ -137,3 +137,21 @@ def test_allocation_free_call_cuts_smaller_blocks():
     torch.cuda.synchronize()
     for x, y in zip(want, out):
         assert torch.equal(x, y)
+
+
+# (m, n, k): the calls next to the lines between the fused and the general path
+@pytest.mark.parametrize("m,n,k", [(96, 65535, 8), (96, 65536, 8), (63, 262144, 20), (65, 262144, 20),
+                                   (1000, 33000, 32), (1100, 33000, 32)])
+def test_both_sides_of_the_path_rule(m, n, k):
+    cb = inputs.clustered_bank(95, 98, n, 32, 64, 0.3, "bf16", m_queries=m)
+    g = host(pm.mem_retrieve_topk(up(cb.emb), up(cb.queries), k, 1.0))
+    rows = pick(m, most=24)
+    check_topk(f"rule-{m}-{n}", cb.queries, cb.emb, rows, {key: v[rows] for key, v in g.items()}, k, 1.0)
+
+
+@pytest.mark.parametrize("n,k", [(5700, 5), (5700, 32), (5900, 32)])
+def test_both_sides_of_the_path_rule_for_relations(n, k):
+    b = inputs.clustered_bank(96, 98, n, 64, 32, 0.3, "bf16").emb
+    g = host(pm.mem_build_relations(up(b), k, 1.0, True))
+    rows = pick(n, most=24)
+    check_topk(f"rule-rel-{n}", b, b, rows, {key: v[rows] for key, v in g.items()}, k, 1.0, self_idx=np.arange(n))

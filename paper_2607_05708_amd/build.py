@@ -25,7 +25,7 @@ DEVICE_FLAGS = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-mcode-
 
 LIBS = {
     "libmemattn.so": ["csrc/api.cpp", "csrc/topk_valu.hip", "csrc/topk_score.hip", "csrc/topk_mfma.hip", "csrc/gather_append.hip",
-                      "csrc/compact.hip"],
+                      "csrc/compact.hip", "csrc/scope.hip"],
     "libmeminputs.so": ["inputs_hip/fill_payload.hip"],
 }
 

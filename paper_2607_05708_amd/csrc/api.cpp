@@ -140,10 +140,32 @@ mem_status select_topk(const mem_bank* bank, const void* queries, int64_t m, int
   hipStream_t s = static_cast<hipStream_t>(stream);
   const float c2 = static_cast<float>(static_cast<double>(scale) * 1.4426950408889634);
   hipError_t e;
+  // A scoped retrieval may score each query against its own namespace's rows
+  // alone: the device decides, from the namespaces themselves, and the
+  // launches of the other way do nothing.
+  const int32_t* gate = nullptr;
+  MergeAlt alt;
+  if (p.mfma && scope.row_ns && self_base < 0 && scope_tables_fit(m, bank->n, bank->d, k) &&
+      bank->n * bank->row_stride * 2 <= (int64_t{1} << 32) - 4096) {
+    const ScopeLayout L = scope_layout(m, bank->n, bank->d, k, p.ws_bytes);
+    if (ws_bytes >= L.end) {
+      e = launch_topk_scope_grouped(L, static_cast<const uint16_t*>(bank->emb), bank->row_stride, bank->n,
+                                    static_cast<const uint16_t*>(queries), q_stride, m, bank->d, c2, k, scope, ws, s);
+      if (e != hipSuccess) return device_status(e, "chunk table launch");
+      char* w = static_cast<char*>(ws);
+      gate = reinterpret_cast<const int32_t*>(w + L.flags);
+      alt = MergeAlt{gate,
+                     gate + 1,
+                     reinterpret_cast<const uint64_t*>(w + L.p.ws_part_keys),
+                     reinterpret_cast<const float2*>(w + L.p.ws_part_ms),
+                     L.p.n_splits,
+                     L.p.kcap * L.p.part_stride};
+    }
+  }
   if (p.mfma) {
     e = launch_topk_mfma(p, static_cast<const uint16_t*>(bank->emb), bank->row_stride, bank->n,
                          static_cast<const uint16_t*>(queries), q_stride, m, bank->d, c2, self_base, k, scope,
-                         relation, ws, s);
+                         relation, ws, s, gate);
   } else {
     e = launch_topk_score(p, bank->emb, bank->row_stride, bank->n, queries, q_stride, m, bank->d, bank->dtype, c2,
                           self_base, k, scope, ws, full_prob, out.idx, out.score, out.prob, out.lse, s);
@@ -154,20 +176,45 @@ mem_status select_topk(const mem_bank* bank, const void* queries, int64_t m, int
   fp.full = full_prob;
   fp.n = bank->n;
   fp.self_base = self_base;
-  e = launch_topk_merge(p, m, k, c2, out.idx, out.score, out.prob, out.lse, ws, s, fp);
+  e = launch_topk_merge(p, m, k, c2, out.idx, out.score, out.prob, out.lse, ws, s, fp, alt);
   if (e != hipSuccess) return device_status(e, "merge launch");
   return MEM_OK;
 }
 
 }  // namespace
 
-Plan make_grouped_plan(int64_t m, int32_t n_ns, int64_t n_entries, int32_t k) {
+namespace {
+// The grouped plan with S splits per namespace.
+Plan grouped_plan(int64_t m, int32_t k, int64_t S, bool sample) {
   Plan p{};
   p.mfma = true;
   p.qw = 1;
   p.tile_rows = 512;
   p.tile_queries = 64;
   p.kcap = k <= 8 ? 8 : (k <= 16 ? 16 : 32);
+  p.n_splits = static_cast<int>(S);
+  p.n_parts = p.n_splits;
+  p.part_stride = p.tile_rows / 128;
+  const size_t mm = static_cast<size_t>(m > 0 ? m : 0);
+  const size_t slots = static_cast<size_t>(p.n_splits) * p.part_stride;
+  p.ws_part_keys = 0;
+  p.ws_part_ms = align256(mm * slots * p.kcap * sizeof(uint64_t));
+  p.ws_lse2 = p.ws_part_ms + align256(mm * p.n_splits * 2 * sizeof(float));
+  p.ns = sample ? 1 : 0;
+  p.samp_stride = 1;
+  p.n_samp = p.tile_rows;
+  p.ws_samp = p.ws_lse2 + align256(mm * sizeof(float));
+  p.ws_t0 = p.ws_samp + align256(mm * static_cast<size_t>(p.n_samp) * sizeof(uint16_t));
+  p.ws_thr = p.ws_t0 + align256(mm * sizeof(float));
+  p.ph_split = 0;
+  p.ws_lane_ms = p.ws_thr + align256(mm * sizeof(uint32_t));
+  p.ws_bytes = p.ws_lane_ms;
+  return p;
+}
+
+}  // namespace
+
+Plan make_grouped_plan(int64_t m, int32_t n_ns, int64_t n_entries, int32_t k) {
   // Work items are (namespace, 64-query tile, split).  Each active
   // namespace has at least one query tile, so about min(n_ns, m) tiles; aim
   // for about one item per CU (256): a launch just over a multiple of the
@@ -179,29 +226,19 @@ Plan make_grouped_plan(int64_t m, int32_t n_ns, int64_t n_entries, int32_t k) {
   const int64_t mean_tiles = ceil_div(mean, 512);
   S = S > mean_tiles ? mean_tiles : S;
   S = S < 1 ? 1 : (S > 32 ? 32 : S);
-  p.n_splits = static_cast<int>(S);
-  p.n_parts = p.n_splits;
-  p.part_stride = p.tile_rows / 128;
-  const size_t mm = static_cast<size_t>(m > 0 ? m : 0);
-  const size_t slots = static_cast<size_t>(p.n_splits) * p.part_stride;
-  p.ws_part_keys = 0;
-  p.ws_part_ms = align256(mm * slots * p.kcap * sizeof(uint64_t));
-  p.ws_lse2 = p.ws_part_ms + align256(mm * p.n_splits * 2 * sizeof(float));
   // Threshold sample: the first tile of every table.  It pays where a
   // split's first tile would otherwise merge many stash overflows into a
   // long list (k > 8): always for lists of 32, for lists of 16 only when
   // the mean table spans at least four tiles (else the sample re-reads a
   // large share of each table).  Lists of 8 merge cheaply: no sample.
-  p.ns = (p.kcap == 32 || (p.kcap == 16 && mean >= 4 * p.tile_rows)) ? 1 : 0;
-  p.samp_stride = 1;
-  p.n_samp = p.tile_rows;
-  p.ws_samp = p.ws_lse2 + align256(mm * sizeof(float));
-  p.ws_t0 = p.ws_samp + align256(mm * static_cast<size_t>(p.n_samp) * sizeof(uint16_t));
-  p.ws_thr = p.ws_t0 + align256(mm * sizeof(float));
-  p.ph_split = 0;
-  p.ws_lane_ms = p.ws_thr + align256(mm * sizeof(uint32_t));
-  p.ws_bytes = p.ws_lane_ms;
-  return p;
+  const bool sample = k > 16 || (k > 8 && mean >= 4 * 512);
+  return grouped_plan(m, k, S, sample);
+}
+
+Plan make_scope_plan(int64_t m, int64_t n, int32_t k) {
+  // (how many tables there will be, and so their size, is not known here: a
+  // table is taken to be long enough for a sample at k > 8 where 256 would be)
+  return grouped_plan(m, k, kScopeMaxSplits, k > 16 || (k > 8 && n >= 256 * 4 * 512));
 }
 
 Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, size_t limit) {
@@ -398,7 +435,12 @@ size_t mem_workspace_bytes(int64_t m, int64_t n, int32_t d, int32_t k, int32_t d
     return 0;
   const size_t a = make_plan(m, n, d, k, dtype, true).ws_bytes;
   const size_t b = make_plan(m, n, d, k, dtype, false).ws_bytes;
-  return a > b ? a : b;
+  // a scoped retrieval's chunk tables (of the largest bank up to n rows that
+  // takes them)
+  const int64_t n_fit = m > 0 && n > scope_max_rows(m) ? scope_max_rows(m) : n;
+  const size_t c = dtype == MEM_BF16 && scope_tables_fit(m, n_fit, d, k) ? scope_layout(m, n_fit, d, k, a).end : 0;
+  const size_t ab = a > b ? a : b;
+  return ab > c ? ab : c;
 }
 
 mem_status mem_retrieve_topk(const mem_bank* bank, const void* queries, int64_t m, int64_t q_stride, int32_t k,

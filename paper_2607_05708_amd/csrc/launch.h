@@ -83,6 +83,8 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
 // Grouped selection over per-namespace chunk tables: the narrow matrix-core
 // shape, S splits per namespace (S from the mean table size), no sample.
 Plan make_grouped_plan(int64_t m, int32_t n_ns, int64_t n_entries, int32_t k);
+// The same over tables that the device collects (room for kScopeMaxSplits).
+Plan make_scope_plan(int64_t m, int64_t n, int32_t k);
 
 // General path: scores block by block, each block followed by its selection.
 // `self_base` >= 0 removes bank row self_base + i from query i's candidates.
@@ -97,11 +99,12 @@ hipError_t launch_topk_score(const Plan& p, const void* bank, int64_t bank_strid
 // bounds each query's k-th best score from below; the full pass starts its
 // thresholds there.
 // `relation`: query i is bank row i (a relation build); the full pass may
-// then take the queries in clustered order (p.order).
+// then take the queries in clustered order (p.order).  gate (scoped calls):
+// where *gate != 0 on the device, nothing is done.
 hipError_t launch_topk_mfma(const Plan& p, const uint16_t* bank, int64_t bank_stride, int64_t n,
                             const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
                             int64_t self_base, int32_t k, const Scope& scope, bool relation, void* ws,
-                            hipStream_t stream);
+                            hipStream_t stream, const int32_t* gate);
 // Grouped selection over per-namespace chunk tables: workspace regions after
 // the plan's (from byte `base` on) and the launch (preparation + matrix-core
 // pass; the merge follows with launch_topk_merge).  The plan must be the
@@ -114,6 +117,76 @@ hipError_t launch_topk_grouped(const Plan& p, const GroupLayout& G, const uint16
                                int64_t n, const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
                                int32_t k, const int32_t* ns_off, const int32_t* rows, int32_t n_ns,
                                int64_t n_entries, const int32_t* key_ns, void* ws, hipStream_t stream);
+// Chunk tables for a scoped selection (scope.hip), all device memory but the
+// numbers.  A query's partials have room for max_splits splits, of which
+// flags[1] are used.
+constexpr int64_t kScopeMaxQueries = 4096;
+constexpr int kScopeRows = 4096;     // bank rows per workgroup (four 1,024-row blocks)
+constexpr int kScopeMaxSplits = 16;  // splits of a table
+struct ScopeArgs {
+  const int32_t* row_ns;    // [n]
+  const int32_t* query_ns;  // [m]
+  int64_t n, m;
+  int bits;                 // log2 of the hash table's slots, at least twice m
+  int64_t n_blocks;         // 1,024-row blocks, rounded up to a multiple of 4
+  int32_t* key;             // [slots] namespace ids, -1 = free
+  int32_t* num;             // [slots] and their numbers
+  int32_t* flags;           // tables used, splits per table, namespaces, entries
+  int32_t* table;           // [m, 2] first and past-the-last entry of each namespace's table
+  int32_t* counts;          // [m, n_blocks]
+  int32_t* chunks;          // [n] the tables' entries
+  int64_t* q_off;           // [m + 1] as the grouped pass takes them
+  int64_t* item_off;        // [m + 1]
+  int32_t* perm;            // [m]
+  uint32_t* thr;            // [m] shared bounds, cleared here
+  uint64_t* part_keys;      // partials of queries without a namespace, emptied here
+  float2* part_ms;
+  int max_splits, part_stride, kcap;
+  const void* queries;      // [m] rows of d bf16, q_stride elements apart, copied to qbuf in grouped order
+  int64_t q_stride;
+  int32_t d;
+  void* qbuf;               // [m, d]
+};
+hipError_t launch_scope_tables(const ScopeArgs& a, hipStream_t stream);
+// Workspace of that selection (p is its grouped plan).  Its regions share
+// memory with the whole-bank pass's, which runs only where they are not used
+// and initialises what it reads; the flags that tell stand behind both.
+struct ScopeLayout {
+  Plan p;
+  size_t key, num, flags, table, counts, chunks, q_off, item_off, perm, qbuf, end;
+  int bits;
+  int64_t n_blocks;
+};
+// The most bank rows that m queries' tables take (16 MiB each of entries and
+// of counts).
+inline int64_t scope_max_rows(int64_t m) {
+  const int64_t by_counts = (int64_t{1} << 22) / m * 1024, by_entries = int64_t{1} << 22;
+  return by_counts < by_entries ? by_counts : by_entries;
+}
+// Whether a scoped call of these sizes tries the tables at all.
+bool scope_tables_fit(int64_t m, int64_t n, int32_t d, int32_t k);
+ScopeLayout scope_layout(int64_t m, int64_t n, int32_t d, int32_t k, size_t whole_bank_bytes);
+// The tables and the grouped pass over them, up to its partials (none of it
+// does anything past the plan where flags[0] comes out 0).
+hipError_t launch_topk_scope_grouped(const ScopeLayout& L, const uint16_t* bank, int64_t bank_stride, int64_t n,
+                                     const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
+                                     int32_t k, const Scope& scope, void* ws, hipStream_t stream);
+
+// Launches that run only where *flag == go (flag NULL: always).
+struct Gate {
+  const int32_t* flag = nullptr;
+  int go = 0;
+};
+// Another set of partials that a merge takes where *flag != 0: lists of
+// consecutive keys kcap apart, with room for n_parts of which *parts are used.
+struct MergeAlt {
+  const int32_t* flag = nullptr;
+  const int32_t* parts = nullptr;
+  const uint64_t* keys = nullptr;
+  const float2* ms = nullptr;
+  int n_parts = 0;
+  int kcap = 0;
+};
 // Optional full probability output: full[i, j] holds the raw score s_ij on
 // entry and p_ij on exit (0 for the excluded row self_base + i).
 struct FullProb {
@@ -125,7 +198,8 @@ struct FullProb {
 // finish the full probability rows if requested (in the merge's own launch
 // for a rank merge over a small bank, else with launch_full_prob after it).
 hipError_t launch_topk_merge(const Plan& p, int64_t m, int32_t k, float c2, int32_t* idx, float* score, float* prob,
-                             float* lse, void* ws, hipStream_t stream, const FullProb& fp = FullProb{});
+                             float* lse, void* ws, hipStream_t stream, const FullProb& fp = FullProb{},
+                             const MergeAlt& alt = MergeAlt{});
 // full[i, j] <- exp2(full[i, j] * c2 - lse2[i]) (0 for the excluded row).
 hipError_t launch_full_prob(const Plan& p, int64_t m, int64_t n, float c2, int64_t self_base, float* full, void* ws,
                             hipStream_t stream);

@@ -152,6 +152,9 @@ struct GroupArgs {
   int S;                    // splits per namespace
   uint32_t bank_bytes;      // bytes of the bank seen by the descriptor (< 2^32)
   int64_t n_entries;        // table entries (offsets are clamped to [0, n_entries])
+  int off_step;             // 2: ns_off holds first and past-the-last entry of each namespace; 1: CSR
+  const int32_t* splits;    // splits per namespace where they are planned on the device, else NULL
+  const int32_t* gate;      // scoped: nothing is done where *gate != 0 (NULL: always done)
 };
 
 // Which tiles of its split a full-pass launch covers, and how it starts
@@ -261,6 +264,9 @@ topk_mfma_kernel(const uint16_t* __restrict__ bank, int64_t bank_stride, int64_t
   // streaming rounds' 16), an XCD instead takes q_tiles / 8 query tiles with
   // every split of each: a tile's workgroups then read the same query rows
   // at about the same time and share them through L2 as well.
+  if constexpr (SCOPED) {
+    if (g.gate != nullptr && *g.gate != 0) return;  // (uniform)
+  }
   const int G = gridDim.x;
   const int b = blockIdx.x;
   int L = (!GROUPED && G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
@@ -285,14 +291,16 @@ topk_mfma_kernel(const uint16_t* __restrict__ bank, int64_t bank_stride, int64_t
     }
     lo = __builtin_amdgcn_readfirstlane(lo);
     const int64_t local = L - uniform64(g.item_off[lo]);
-    const int qt = static_cast<int>(local / g.S);
-    samp_slot = split = static_cast<int>(local % g.S);
+    const int S_ns = g.splits != nullptr ? __builtin_amdgcn_readfirstlane(*g.splits) : g.S;
+    const int qt = static_cast<int>(local / S_ns);
+    samp_slot = split = static_cast<int>(local % S_ns);
     // the sample pass scores the first tile of each table: split 0's items
     if (SAMPLE && split != 0) return;
     // (offsets are clamped so a malformed table cannot send reads past it)
-    seg_lo = min(max(static_cast<int64_t>(__builtin_amdgcn_readfirstlane(g.ns_off[lo])), int64_t{0}), g.n_entries);
+    const int at = lo * g.off_step;
+    seg_lo = min(max(static_cast<int64_t>(__builtin_amdgcn_readfirstlane(g.ns_off[at])), int64_t{0}), g.n_entries);
     const int64_t seg_end =
-        min(max(static_cast<int64_t>(__builtin_amdgcn_readfirstlane(g.ns_off[lo + 1])), seg_lo), g.n_entries);
+        min(max(static_cast<int64_t>(__builtin_amdgcn_readfirstlane(g.ns_off[at + 1])), seg_lo), g.n_entries);
     seg_n = seg_end - seg_lo;
     const int64_t qg0 = uniform64(g.q_off[lo]);
     q_base = qg0 + static_cast<int64_t>(qt) * kTileQ;
@@ -300,7 +308,7 @@ topk_mfma_kernel(const uint16_t* __restrict__ bank, int64_t bank_stride, int64_t
     q_base = uniform64(q_base);
     q_lim = uniform64(q_lim);
     const int64_t seg_tiles = (seg_n + kTileB - 1) / kTileB;
-    tps = (seg_tiles + g.S - 1) / g.S;
+    tps = (seg_tiles + S_ns - 1) / S_ns;
   } else {
     const int qt = L % q_tiles;
     samp_slot = L / q_tiles;
@@ -921,7 +929,8 @@ __device__ __forceinline__ uint32_t kept_key(uint32_t key16, uint32_t pos) {
 template <bool NEAR>
 __global__ __launch_bounds__(256) void sample_kth_kernel(const uint16_t* __restrict__ samp, int64_t n_samp, int k,
                                                          float* __restrict__ t0_out, uint32_t* __restrict__ thr_out,
-                                                         int32_t* __restrict__ near_out) {
+                                                         int32_t* __restrict__ near_out, Gate gate) {
+  if (gate.flag != nullptr && *gate.flag != gate.go) return;
   __shared__ uint32_t kept[256 * kSampleKeep];
   const int tid = threadIdx.x;
   const int64_t q = blockIdx.x;
@@ -983,7 +992,8 @@ __global__ __launch_bounds__(256) void sample_kth_wave_kernel(const uint16_t* __
                                                               int64_t m, int k, float* __restrict__ t0_out,
                                                               uint32_t* __restrict__ thr_out,
                                                               int32_t* __restrict__ near_out,
-                                                              uint32_t* __restrict__ top_out) {
+                                                              uint32_t* __restrict__ top_out, Gate gate) {
+  if (gate.flag != nullptr && *gate.flag != gate.go) return;
   const int lane = threadIdx.x & 63;
   const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (q >= m) return;  // whole waves only; no workgroup barrier below
@@ -1065,7 +1075,8 @@ __device__ __forceinline__ float prefix_bound(uint32_t t, int64_t n_keys, int k)
 // 64 * R of them (the search is then exact and runs R ballots per bit).
 template <int R>
 __global__ __launch_bounds__(256) void prefix_kth_wave_kernel(const uint64_t* __restrict__ keys, int64_t n_keys,
-                                                              int64_t m, int k, float* __restrict__ t0) {
+                                                              int64_t m, int k, float* __restrict__ t0, Gate gate) {
+  if (gate.flag != nullptr && *gate.flag != gate.go) return;
   const int lane = threadIdx.x & 63;
   const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (q >= m) return;  // whole waves only; no workgroup barrier below
@@ -1083,7 +1094,8 @@ __global__ __launch_bounds__(256) void prefix_kth_wave_kernel(const uint64_t* __
 }
 
 __global__ __launch_bounds__(256) void prefix_kth_kernel(const uint64_t* __restrict__ keys, int64_t n_keys, int k,
-                                                         float* __restrict__ t0) {
+                                                         float* __restrict__ t0, Gate gate) {
+  if (gate.flag != nullptr && *gate.flag != gate.go) return;
   __shared__ uint32_t kept[256 * kKthKeep];
   const int tid = threadIdx.x;
   const int64_t q = blockIdx.x;
@@ -1528,7 +1540,8 @@ __global__ __launch_bounds__(256) void group_queries_kernel(const u32x4* __restr
 }
 
 // Shared per-query bounds start empty (order key 0 is below every score).
-__global__ __launch_bounds__(256) void thr_init_kernel(uint32_t* __restrict__ thr, int64_t m) {
+__global__ __launch_bounds__(256) void thr_init_kernel(uint32_t* __restrict__ thr, int64_t m, Gate gate) {
+  if (gate.flag != nullptr && *gate.flag != gate.go) return;
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (i < m) thr[i] = 0u;
 }
@@ -1551,13 +1564,58 @@ GroupLayout group_layout(int64_t m, int32_t n_ns, int32_t d, size_t base) {
   return L;
 }
 
+namespace {
+
+// The grouped pass proper, over at most `bound` work items: queries in
+// grouped order in qbuf.  When the plan asks for it, a sample pass over the
+// first tile of every table (the split-0 items) bounds each query's k-th best
+// from below, as for the whole bank; the full pass starts its thresholds
+// there.
+hipError_t run_grouped(const Plan& p, const GroupArgs& ga, int64_t bound, const uint16_t* bank, int64_t bank_stride,
+                       int64_t n, const uint16_t* qbuf, int64_t m, int32_t d, float c2, int32_t k,
+                       const int32_t* rows, void* ws, const Gate& gate, hipStream_t stream) {
+  char* w = static_cast<char*>(ws);
+  auto* samp = reinterpret_cast<uint16_t*>(w + p.ws_samp);
+  auto* t0 = reinterpret_cast<float*>(w + p.ws_t0);
+  auto* keys = reinterpret_cast<uint64_t*>(w + p.ws_part_keys);
+  auto* ms = reinterpret_cast<float2*>(w + p.ws_part_ms);
+  auto* thr = reinterpret_cast<uint32_t*>(w + p.ws_thr);
+  auto run = [&](auto kcap_tag) -> hipError_t {
+    constexpr int KC = decltype(kcap_tag)::value;
+    const dim3 grid(static_cast<unsigned>(bound));
+    const float* t0_arg = nullptr;
+    if (p.ns > 0) {
+      topk_mfma_kernel<KC, true, 1, false, true><<<grid, Shape<1>::kThreads, 0, stream>>>(
+          bank, bank_stride, n, qbuf, d, m, d, c2, -1, 0, p.n_splits, 0, keys, ms, p.ns, 1, samp, p.n_samp, nullptr,
+          nullptr, nullptr, nullptr, rows, ga, kWholeSplit);
+      sample_kth_wave_kernel<false><<<dim3(static_cast<unsigned>((m + 3) / 4)), 256, 0, stream>>>(
+          samp, p.n_samp, m, k, t0, nullptr, nullptr, nullptr, gate);
+      t0_arg = t0;
+    }
+    topk_mfma_kernel<KC, false, 1, false, true><<<grid, Shape<1>::kThreads, 0, stream>>>(
+        bank, bank_stride, n, qbuf, d, m, d, c2, -1, 0, p.n_splits, 0, keys, ms, 0, 1, nullptr, 0, t0_arg, thr,
+        nullptr, nullptr, rows, ga, kWholeSplit);
+    return hipGetLastError();
+  };
+  switch (p.kcap) {
+    case 8:
+      return run(std::integral_constant<int, 8>{});
+    case 16:
+      return run(std::integral_constant<int, 16>{});
+    case 32:
+      return run(std::integral_constant<int, 32>{});
+    default:
+      return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
 hipError_t launch_topk_grouped(const Plan& p, const GroupLayout& G, const uint16_t* bank, int64_t bank_stride,
                                int64_t n, const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
                                int32_t k, const int32_t* ns_off, const int32_t* rows, int32_t n_ns,
                                int64_t n_entries, const int32_t* key_ns, void* ws, hipStream_t stream) {
   char* w = static_cast<char*>(ws);
-  auto* samp = reinterpret_cast<uint16_t*>(w + p.ws_samp);
-  auto* t0 = reinterpret_cast<float*>(w + p.ws_t0);
   auto* keys = reinterpret_cast<uint64_t*>(w + p.ws_part_keys);
   auto* ms = reinterpret_cast<float2*>(w + p.ws_part_ms);
   auto* thr = reinterpret_cast<uint32_t*>(w + p.ws_thr);
@@ -1582,49 +1640,95 @@ hipError_t launch_topk_grouped(const Plan& p, const GroupLayout& G, const uint16
     if (e != hipSuccess) return e;
     group_scatter_kernel<<<blocks256(m), 256, 0, stream>>>(key_ns, m, n_ns, q_off, fill, perm, keys, ms, S,
                                                            p.part_stride, p.kcap);
-    thr_init_kernel<<<dim3(static_cast<unsigned>((m + 255) / 256)), 256, 0, stream>>>(thr, m);
+    thr_init_kernel<<<dim3(static_cast<unsigned>((m + 255) / 256)), 256, 0, stream>>>(thr, m, Gate{});
   }
   group_queries_kernel<<<dim3(static_cast<unsigned>(m)), 256, 0, stream>>>(
       reinterpret_cast<const u32x4*>(queries), q_stride / 8, perm, q_off + n_ns, d / 8, reinterpret_cast<u32x4*>(qbuf));
   // items: at most (ceil(m / 64) + min(m, n_ns)) query tiles, S splits each
   const int64_t bound = ((m + 63) / 64 + (m < n_ns ? m : n_ns)) * S;
-  const GroupArgs ga{ns_off, q_off, item_off, perm, n_ns, S, static_cast<uint32_t>(n * bank_stride * 2), n_entries};
-  // When the plan asks for it, a sample pass over the first tile of every
-  // table (the split-0 items) bounds each query's k-th best from below, as
-  // for the whole bank; the full pass starts its thresholds there.
-  auto run = [&](auto kcap_tag) -> hipError_t {
-    constexpr int KC = decltype(kcap_tag)::value;
-    const dim3 grid(static_cast<unsigned>(bound));
-    const float* t0_arg = nullptr;
-    if (p.ns > 0) {
-      topk_mfma_kernel<KC, true, 1, false, true><<<grid, Shape<1>::kThreads, 0, stream>>>(
-          bank, bank_stride, n, qbuf, d, m, d, c2, -1, 0, S, 0, keys, ms, p.ns, 1, samp, p.n_samp, nullptr, nullptr,
-          nullptr, nullptr, rows, ga, kWholeSplit);
-      sample_kth_wave_kernel<false><<<dim3(static_cast<unsigned>((m + 3) / 4)), 256, 0, stream>>>(
-          samp, p.n_samp, m, k, t0, nullptr, nullptr, nullptr);
-      t0_arg = t0;
-    }
-    topk_mfma_kernel<KC, false, 1, false, true><<<grid, Shape<1>::kThreads, 0, stream>>>(
-        bank, bank_stride, n, qbuf, d, m, d, c2, -1, 0, S, 0, keys, ms, 0, 1, nullptr, 0, t0_arg, thr, nullptr,
-        nullptr, rows, ga, kWholeSplit);
-    return hipGetLastError();
-  };
-  switch (p.kcap) {
-    case 8:
-      return run(std::integral_constant<int, 8>{});
-    case 16:
-      return run(std::integral_constant<int, 16>{});
-    case 32:
-      return run(std::integral_constant<int, 32>{});
-    default:
-      return hipErrorInvalidValue;
-  }
+  const GroupArgs ga{ns_off, q_off, item_off, perm, n_ns, S, static_cast<uint32_t>(n * bank_stride * 2), n_entries,
+                     1, nullptr, nullptr};
+  return run_grouped(p, ga, bound, bank, bank_stride, n, qbuf, m, d, c2, k, rows, ws, Gate{}, stream);
+}
+
+bool scope_tables_fit(int64_t m, int64_t n, int32_t d, int32_t k) {
+  // The plan, and the whole-bank launches that find it taken, cost about 30
+  // us: tried where the masked pass takes about 0.7 ms or more.
+  return m > 0 && m <= kScopeMaxQueries && k <= kMfmaMaxK && d >= 96 && m * n >= (int64_t{1} << 38) / d &&
+         n <= scope_max_rows(m);
+}
+
+ScopeLayout scope_layout(int64_t m, int64_t n, int32_t d, int32_t k, size_t whole_bank_bytes) {
+  auto al = [](size_t x) { return (x + 255) & ~static_cast<size_t>(255); };
+  ScopeLayout L{};
+  // (room for max_splits splits of every table; the plan's other choices are
+  // those of m namespaces)
+  L.p = make_scope_plan(m, n, k);
+  L.bits = 6;
+  while ((int64_t{1} << L.bits) < 2 * m) ++L.bits;
+  L.n_blocks = (n + kScopeRows - 1) / kScopeRows * 4;
+  const size_t mm = static_cast<size_t>(m);
+  size_t o = L.p.ws_bytes;
+  L.key = o;      o += al(size_t{4} << L.bits);
+  L.num = o;      o += al(size_t{4} << L.bits);
+  L.table = o;    o += al(mm * 8);
+  L.counts = o;   o += al(mm * static_cast<size_t>(L.n_blocks) * 4);
+  L.chunks = o;   o += al(static_cast<size_t>(n) * 4);
+  L.q_off = o;    o += al((mm + 1) * 8);
+  L.item_off = o; o += al((mm + 1) * 8);
+  L.perm = o;     o += al(mm * 4);
+  L.qbuf = o;     o += al(mm * static_cast<size_t>(d) * 2);
+  L.flags = o > al(whole_bank_bytes) ? o : al(whole_bank_bytes);
+  L.end = L.flags + 256;
+  return L;
+}
+
+hipError_t launch_topk_scope_grouped(const ScopeLayout& L, const uint16_t* bank, int64_t bank_stride, int64_t n,
+                                     const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
+                                     int32_t k, const Scope& scope, void* ws, hipStream_t stream) {
+  char* w = static_cast<char*>(ws);
+  ScopeArgs a{};
+  a.row_ns = scope.row_ns;
+  a.query_ns = scope.key_ns;
+  a.n = n;
+  a.m = m;
+  a.bits = L.bits;
+  a.n_blocks = L.n_blocks;
+  a.key = reinterpret_cast<int32_t*>(w + L.key);
+  a.num = reinterpret_cast<int32_t*>(w + L.num);
+  a.flags = reinterpret_cast<int32_t*>(w + L.flags);
+  a.table = reinterpret_cast<int32_t*>(w + L.table);
+  a.counts = reinterpret_cast<int32_t*>(w + L.counts);
+  a.chunks = reinterpret_cast<int32_t*>(w + L.chunks);
+  a.q_off = reinterpret_cast<int64_t*>(w + L.q_off);
+  a.item_off = reinterpret_cast<int64_t*>(w + L.item_off);
+  a.perm = reinterpret_cast<int32_t*>(w + L.perm);
+  a.thr = reinterpret_cast<uint32_t*>(w + L.p.ws_thr);
+  a.part_keys = reinterpret_cast<uint64_t*>(w + L.p.ws_part_keys);
+  a.part_ms = reinterpret_cast<float2*>(w + L.p.ws_part_ms);
+  a.max_splits = L.p.n_splits;
+  a.part_stride = L.p.part_stride;
+  a.kcap = L.p.kcap;
+  auto* qbuf = reinterpret_cast<uint16_t*>(w + L.qbuf);
+  a.queries = queries;
+  a.q_stride = q_stride;
+  a.d = d;
+  a.qbuf = qbuf;
+  const hipError_t e = launch_scope_tables(a, stream);
+  if (e != hipSuccess) return e;
+  // items: tiles of 64 queries, at most ceil(m / 64) + m, in about 256 / tiles splits each
+  const int64_t tiles = (m + 63) / 64 + m;
+  const GroupArgs ga{a.table, a.q_off,  a.item_off, a.perm,      static_cast<int>(m), 1,
+                     static_cast<uint32_t>(n * bank_stride * 2), n, 2, a.flags + 1, nullptr};
+  return run_grouped(L.p, ga, tiles > 256 ? tiles : 256, bank, bank_stride, n, qbuf, m, d, c2, k, a.chunks, ws,
+                     Gate{a.flags, 1}, stream);
 }
 
 hipError_t launch_topk_mfma(const Plan& p, const uint16_t* bank, int64_t bank_stride, int64_t n,
                             const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
                             int64_t self_base, int32_t k, const Scope& scope, bool relation, void* ws,
-                            hipStream_t stream) {
+                            hipStream_t stream, const int32_t* gate_flag) {
+  const Gate gate{gate_flag, 0};
   char* w = static_cast<char*>(ws);
   auto* keys = reinterpret_cast<uint64_t*>(w + p.ws_part_keys);
   auto* ms = reinterpret_cast<float2*>(w + p.ws_part_ms);
@@ -1640,6 +1744,8 @@ hipError_t launch_topk_mfma(const Plan& p, const uint16_t* bank, int64_t bank_st
     constexpr bool SC = decltype(scoped_tag)::value;
     constexpr int T = Shape<QW>::kThreads;
     const float* t0_arg = nullptr;
+    GroupArgs gated{};
+    gated.gate = gate_flag;
     // the full pass takes the queries in clustered order where the plan has
     // room for it (relation builds, no scope)
     const bool ordered = p.order && relation && !SC;
@@ -1652,27 +1758,27 @@ hipError_t launch_topk_mfma(const Plan& p, const uint16_t* bank, int64_t bank_st
       topk_mfma_kernel<KC, true, QW, SC, false><<<samp_grid, T, 0, stream>>>(
           bank, bank_stride, n, queries, q_stride, m, d, c2, self_base, p.q_tiles, p.n_splits, p.tiles_per_split,
           keys, ms, p.ns, p.samp_stride, samp, p.n_samp, nullptr, nullptr, scope.row_ns, scope.key_ns, nullptr,
-          GroupArgs{}, kWholeSplit);
+          gated, kWholeSplit);
       const dim3 wave_grid(static_cast<unsigned>((m + 3) / 4)), wg_grid(static_cast<unsigned>(m));
       if (p.n_samp <= 64 * kWaveKthPerLane) {
         if (near)
-          sample_kth_wave_kernel<true><<<wave_grid, 256, 0, stream>>>(samp, p.n_samp, m, k, t0, thr, near, stop);
+          sample_kth_wave_kernel<true><<<wave_grid, 256, 0, stream>>>(samp, p.n_samp, m, k, t0, thr, near, stop, gate);
         else
           sample_kth_wave_kernel<false><<<wave_grid, 256, 0, stream>>>(samp, p.n_samp, m, k, t0, thr, nullptr,
-                                                                         nullptr);
+                                                                         nullptr, gate);
       } else {
         if (near)
-          sample_kth_kernel<true><<<wg_grid, 256, 0, stream>>>(samp, p.n_samp, k, t0, thr, near);
+          sample_kth_kernel<true><<<wg_grid, 256, 0, stream>>>(samp, p.n_samp, k, t0, thr, near, gate);
         else
-          sample_kth_kernel<false><<<wg_grid, 256, 0, stream>>>(samp, p.n_samp, k, t0, thr, nullptr);
+          sample_kth_kernel<false><<<wg_grid, 256, 0, stream>>>(samp, p.n_samp, k, t0, thr, nullptr, gate);
       }
       t0_arg = t0;
     } else {
-      thr_init_kernel<<<dim3(static_cast<unsigned>((m + 255) / 256)), 256, 0, stream>>>(thr, m);
+      thr_init_kernel<<<dim3(static_cast<unsigned>((m + 255) / 256)), 256, 0, stream>>>(thr, m, gate);
     }
     const uint16_t* fq = queries;  // the queries as the full pass reads them
     int64_t fq_stride = q_stride;
-    GroupArgs fg{};
+    GroupArgs fg = gated;
     if (ordered && p.ns > 0) {
       auto* perm = reinterpret_cast<int32_t*>(w + p.ws_perm);
       auto* olab = reinterpret_cast<int32_t*>(w + p.ws_olab);
@@ -1705,12 +1811,12 @@ hipError_t launch_topk_mfma(const Plan& p, const uint16_t* bank, int64_t bank_st
       full(t0_arg, PhaseArgs{0, p.ph_split, 0, 0, lane_ms});
       const int64_t n_keys = static_cast<int64_t>(p.n_splits) * p.part_stride * KC;
       if (n_keys <= 64 * 2)
-        prefix_kth_wave_kernel<2><<<dim3(static_cast<unsigned>((m + 3) / 4)), 256, 0, stream>>>(keys, n_keys, m, k, t0);
+        prefix_kth_wave_kernel<2><<<dim3(static_cast<unsigned>((m + 3) / 4)), 256, 0, stream>>>(keys, n_keys, m, k, t0, gate);
       else if (n_keys <= 64 * kWaveKthPerLane)
         prefix_kth_wave_kernel<kKthKeep><<<dim3(static_cast<unsigned>((m + 3) / 4)), 256, 0, stream>>>(keys, n_keys, m,
-                                                                                                      k, t0);
+                                                                                                      k, t0, gate);
       else
-        prefix_kth_kernel<<<dim3(static_cast<unsigned>(m)), 256, 0, stream>>>(keys, n_keys, k, t0);
+        prefix_kth_kernel<<<dim3(static_cast<unsigned>(m)), 256, 0, stream>>>(keys, n_keys, k, t0, gate);
       full(t0, PhaseArgs{p.ph_split, 0x7FFFFFFF, 1, 1, lane_ms});
     } else {
       full(t0_arg, kWholeSplit);

@@ -137,12 +137,18 @@ __global__ __launch_bounds__(256) void topk_merge_rank_kernel(const uint64_t* __
 __global__ __launch_bounds__(kSelThreads) void topk_merge_select_kernel(
     const uint64_t* __restrict__ part_keys, const float2* __restrict__ part_ms, int n_parts, int kcap, int k, int kk,
     float c2, int32_t* __restrict__ idx, float* __restrict__ score, float* __restrict__ prob, float* __restrict__ lse,
-    float* __restrict__ lse2_out) {
+    float* __restrict__ lse2_out, MergeAlt alt) {
   __shared__ SelectLds L;
   const int tid = threadIdx.x;
   const int64_t q = blockIdx.x;
   const uint64_t* keys = part_keys + q * static_cast<int64_t>(n_parts) * kcap;
   const float2* ms = part_ms + q * n_parts;
+  if (alt.flag != nullptr && *alt.flag != 0) {  // (uniform)
+    keys = alt.keys + q * static_cast<int64_t>(alt.n_parts) * alt.kcap;
+    ms = alt.ms + q * alt.n_parts;
+    kcap = alt.kcap;
+    n_parts = *alt.parts;
+  }
   const int per = kSelThreads / kk;  // lists read at a time
   if (tid < kMaxK) L.list[0][tid] = 0;
   float m_run = -INFINITY;
@@ -177,7 +183,8 @@ __global__ __launch_bounds__(kSelThreads) void topk_merge_select_kernel(
   if (tid < k) write_selected(L.list[cur][tid], c2, lse2, q * k + tid, idx, score, prob);
   if (tid == 0) {
     if (lse) lse[q] = lse2 * kLn2;
-    lse2_out[q] = lse2;
+    // (for the full probability rows; the other partials may lie there)
+    if (alt.flag == nullptr) lse2_out[q] = lse2;
   }
 }
 
@@ -196,7 +203,7 @@ __global__ __launch_bounds__(256) void full_prob_kernel(float* __restrict__ full
 }  // namespace
 
 hipError_t launch_topk_merge(const Plan& p, int64_t m, int32_t k, float c2, int32_t* idx, float* score, float* prob,
-                             float* lse, void* ws, hipStream_t stream, const FullProb& fp) {
+                             float* lse, void* ws, hipStream_t stream, const FullProb& fp, const MergeAlt& alt) {
   // every merge but the fused rank merge leaves the full rows to full_prob_kernel
   auto finish = [&](hipError_t e) -> hipError_t {
     if (e != hipSuccess || fp.full == nullptr) return e;
@@ -209,7 +216,7 @@ hipError_t launch_topk_merge(const Plan& p, int64_t m, int32_t k, float c2, int3
   const int64_t S = p.n_parts;
   // consecutive lists of a key start kcap_eff keys apart (every part_stride-th slot)
   const int kcap_eff = p.kcap * p.part_stride;
-  if (S * k <= kRankMaxKeys && S <= 4) {
+  if (S * k <= kRankMaxKeys && S <= 4 && alt.flag == nullptr) {
     const bool fused = fp.full != nullptr && fp.n <= kRankFullMax;
     topk_merge_rank_kernel<<<dim3(static_cast<unsigned>((m + 3) / 4)), 256, rank_lds_bytes(p.n_parts, k), stream>>>(
         keys, ms, m, p.n_parts, kcap_eff, k, c2, idx, score, prob, lse, lse2, fused ? fp.full : nullptr, fp.n,
@@ -219,7 +226,7 @@ hipError_t launch_topk_merge(const Plan& p, int64_t m, int32_t k, float c2, int3
   int kk = 1;
   while (kk < k) kk <<= 1;
   topk_merge_select_kernel<<<dim3(static_cast<unsigned>(m)), kSelThreads, 0, stream>>>(
-      keys, ms, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob, lse, lse2);
+      keys, ms, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob, lse, lse2, alt);
   return finish(hipGetLastError());
 }
 

@@ -150,7 +150,8 @@ mem_status select_topk(const mem_bank* bank, const void* queries, int64_t m, int
     const ScopeLayout L = scope_layout(m, bank->n, bank->d, k, p.ws_bytes);
     if (ws_bytes >= L.end) {
       e = launch_topk_scope_grouped(L, static_cast<const uint16_t*>(bank->emb), bank->row_stride, bank->n,
-                                    static_cast<const uint16_t*>(queries), q_stride, m, bank->d, c2, k, scope, ws, s);
+                                    static_cast<const uint16_t*>(queries), q_stride, m, bank->d, c2, k, scope,
+                                    out.idx, out.score, out.prob, out.lse, ws, s);
       if (e != hipSuccess) return device_status(e, "chunk table launch");
       char* w = static_cast<char*>(ws);
       gate = reinterpret_cast<const int32_t*>(w + L.flags);
@@ -159,7 +160,8 @@ mem_status select_topk(const mem_bank* bank, const void* queries, int64_t m, int
                      reinterpret_cast<const uint64_t*>(w + L.p.ws_part_keys),
                      reinterpret_cast<const float2*>(w + L.p.ws_part_ms),
                      L.p.n_splits,
-                     L.p.kcap * L.p.part_stride};
+                     L.p.kcap * L.p.part_stride,
+                     reinterpret_cast<const int32_t*>(w + L.table_flag)};
     }
   }
   if (p.mfma) {
@@ -497,7 +499,7 @@ mem_status mem_build_relations_scoped(const mem_bank* bank, const int32_t* row_n
 size_t mem_workspace_bytes_grouped(int64_t m, int32_t n_ns, int64_t n_entries, int32_t d, int32_t k) {
   if (m < 0 || n_ns < 0 || n_entries < 0 || d < 1 || d > kMaxD || k < 1 || k > kMfmaMaxK) return 0;
   const Plan p = make_grouped_plan(m, n_ns, n_entries, k);
-  return group_layout(m, n_ns, d, p.ws_bytes).bytes;
+  return group_layout(m, n_ns, n_entries, d, p.ws_bytes).bytes;
 }
 
 mem_status mem_retrieve_topk_grouped(const mem_bank* bank, const mem_chunk_tables* tables, const void* queries,
@@ -529,7 +531,7 @@ mem_status mem_retrieve_topk_grouped(const mem_bank* bank, const mem_chunk_table
   if (bank->n * bank->row_stride * 2 > (int64_t{1} << 32) - 4096)
     return fail(MEM_ERR_UNSUPPORTED, "grouped retrieval addresses at most 4 GiB of bank rows");
   const Plan p = make_grouped_plan(m, n_ns, n_entries, k);
-  const GroupLayout G = group_layout(m, n_ns, bank->d, p.ws_bytes);
+  const GroupLayout G = group_layout(m, n_ns, n_entries, bank->d, p.ws_bytes);
   const int64_t bound = (ceil_div(m, 64) + (m < n_ns ? m : n_ns)) * p.n_splits;
   if (bound > INT32_MAX || m > INT32_MAX) return fail(MEM_ERR_UNSUPPORTED, "problem too large for one launch");
   if (!workspace) return fail(MEM_ERR_WORKSPACE, "workspace is NULL");
@@ -540,9 +542,12 @@ mem_status mem_retrieve_topk_grouped(const mem_bank* bank, const mem_chunk_table
   // the merge sees empty partials)
   hipError_t e = launch_topk_grouped(p, G, static_cast<const uint16_t*>(bank->emb), bank->row_stride, bank->n,
                                      static_cast<const uint16_t*>(queries), q_stride, m, bank->d, c2, k,
-                                     tables->offsets, tables->chunks, n_ns, n_entries, query_ns, workspace, s);
+                                     tables->offsets, tables->chunks, n_ns, n_entries, query_ns, out.idx, out.score,
+                                     out.prob, out.lse, workspace, s);
   if (e != hipSuccess) return device_status(e, "grouped selection launch");
-  e = launch_topk_merge(p, m, k, c2, out.idx, out.score, out.prob, out.lse, workspace, s);
+  MergeAlt alt;
+  if (G.tables) alt.done = reinterpret_cast<const int32_t*>(static_cast<char*>(workspace) + G.flag);
+  e = launch_topk_merge(p, m, k, c2, out.idx, out.score, out.prob, out.lse, workspace, s, FullProb{}, alt);
   if (e != hipSuccess) return device_status(e, "merge launch");
   return MEM_OK;
 }

@@ -110,13 +110,15 @@ hipError_t launch_topk_mfma(const Plan& p, const uint16_t* bank, int64_t bank_st
 // pass; the merge follows with launch_topk_merge).  The plan must be the
 // narrow matrix-core shape with n_splits = S splits per namespace.
 struct GroupLayout {
-  size_t q_cnt, fill, q_off, item_off, bsum, perm, qbuf, bytes;
+  size_t q_cnt, fill, q_off, item_off, bsum, perm, qbuf, q_pos, flag, tile_off, score_off, scores, bytes;
+  bool tables;  // few enough queries and namespaces for launch_topk_tables to be tried
 };
-GroupLayout group_layout(int64_t m, int32_t n_ns, int32_t d, size_t base);
+GroupLayout group_layout(int64_t m, int32_t n_ns, int64_t n_entries, int32_t d, size_t base);
 hipError_t launch_topk_grouped(const Plan& p, const GroupLayout& G, const uint16_t* bank, int64_t bank_stride,
                                int64_t n, const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
                                int32_t k, const int32_t* ns_off, const int32_t* rows, int32_t n_ns,
-                               int64_t n_entries, const int32_t* key_ns, void* ws, hipStream_t stream);
+                               int64_t n_entries, const int32_t* key_ns, int32_t* idx, float* score,
+                               float* prob, float* lse, void* ws, hipStream_t stream);
 // Chunk tables for a scoped selection (scope.hip), all device memory but the
 // numbers.  A query's partials have room for max_splits splits, of which
 // flags[1] are used.
@@ -138,6 +140,7 @@ struct ScopeArgs {
   int64_t* q_off;           // [m + 1] as the grouped pass takes them
   int64_t* item_off;        // [m + 1]
   int32_t* perm;            // [m]
+  int32_t* q_pos;           // [m] grouped position of each query, -1 = none
   uint32_t* thr;            // [m] shared bounds, cleared here
   uint64_t* part_keys;      // partials of queries without a namespace, emptied here
   float2* part_ms;
@@ -153,7 +156,8 @@ hipError_t launch_scope_tables(const ScopeArgs& a, hipStream_t stream);
 // and initialises what it reads; the flags that tell stand behind both.
 struct ScopeLayout {
   Plan p;
-  size_t key, num, flags, table, counts, chunks, q_off, item_off, perm, qbuf, end;
+  size_t key, num, flags, table, counts, chunks, q_off, item_off, perm, qbuf, q_pos, table_flag, tile_off, score_off,
+      scores, end;
   int bits;
   int64_t n_blocks;
 };
@@ -170,7 +174,43 @@ ScopeLayout scope_layout(int64_t m, int64_t n, int32_t d, int32_t k, size_t whol
 // does anything past the plan where flags[0] comes out 0).
 hipError_t launch_topk_scope_grouped(const ScopeLayout& L, const uint16_t* bank, int64_t bank_stride, int64_t n,
                                      const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
-                                     int32_t k, const Scope& scope, void* ws, hipStream_t stream);
+                                     int32_t k, const Scope& scope, int32_t* idx, float* score, float* prob, float* lse,
+                                     void* ws, hipStream_t stream);
+
+// Scores and selection over chunk tables (topk_score.hip): bf16 rows, device
+// memory but the numbers.
+constexpr int64_t kTableMaxNs = 4096;               // namespaces
+constexpr int kTableMaxRows = 32768;                // rows of a table
+constexpr int64_t kTableScores = int64_t{12} << 20; // most scores held (48 MiB)
+struct TableArgs {
+  const uint16_t* bank;
+  int64_t bank_stride, n;
+  const uint16_t* queries;  // in their own order
+  int64_t q_stride, m;
+  int32_t d;
+  float c2;
+  int32_t k;
+  const int32_t* ns_off;    // tables: CSR (off_step 1) or first and past-the-last entries (2)
+  int off_step;
+  const int32_t* chunks;
+  int64_t n_entries;
+  int n_ns;
+  const int64_t* q_off;     // [n_ns + 1] grouped positions of each namespace's queries
+  int64_t* item_off;        // [n_ns + 1] the fused pass's work items, taken away where this side runs
+  const int32_t* perm;      // grouped position -> query
+  const int32_t* q_pos;     // query -> grouped position, -1 = no namespace
+  int32_t* flag;            // [0] set where this side runs, [1] where the fused grouped pass does
+  int32_t* tile_off;        // [n_ns + 1]
+  int64_t* score_off;       // [n_ns]
+  float* scores;
+  int64_t max_scores;
+  const int32_t* gate;      // NULL, or 0: there are no tables
+  int32_t* idx;
+  float* score;
+  float* prob;
+  float* lse;
+};
+hipError_t launch_topk_tables(const TableArgs& a, hipStream_t stream);
 
 // Launches that run only where *flag == go (flag NULL: always).
 struct Gate {
@@ -186,6 +226,7 @@ struct MergeAlt {
   const float2* ms = nullptr;
   int n_parts = 0;
   int kcap = 0;
+  const int32_t* done = nullptr;  // nothing is left to merge where *done != 0 (NULL: never)
 };
 // Optional full probability output: full[i, j] holds the raw score s_ij on
 // entry and p_ij on exit (0 for the excluded row self_base + i).

@@ -20,11 +20,11 @@
 //      ids ascend within a table.  Workgroups past the bank's copy the
 //      queries into grouped order.
 //
-// 1,024 queries against 1M x 1024 rows in 256 namespaces, k = 32: 2.89 ms
-// masked, 0.82 ms through the tables (rows in bursts of 64), 2.37 and 0.69 ms
-// (mixed rows); 8 namespaces 2.41 and 1.32 ms.  The four launches take 55 us.
-// One namespace, where the plan declines, costs 16 us and the idle launches:
-// 2.39 and 2.42 ms.
+// 1,024 queries against 1M x 1024 rows in 256 namespaces, k = 32: 2.95 ms
+// masked, 0.49 ms through the tables (rows in bursts of 64), 2.38 and 0.49 ms
+// (mixed rows); 8 namespaces 2.43 and 1.33 ms.  The four launches take 55 us.
+// One namespace, where the plan declines, costs 17 us and the idle launches:
+// 2.39 and 2.43 ms.
 #include "device_common.h"
 #include "launch.h"
 
@@ -86,6 +86,15 @@ __global__ __launch_bounds__(kPlanThreads) void scope_plan_kernel(ScopeArgs a) {
   const int tid = threadIdx.x;
   const int m = static_cast<int>(a.m);
   const int slots = 1 << a.bits;
+  // (the sampled rows' namespaces, needed last, are asked for first)
+  constexpr int kPer = kPlanSample / kPlanThreads;
+  const int64_t sampled = a.n < kPlanSample ? a.n : kPlanSample;
+  int32_t seen[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int64_t i = tid + j * kPlanThreads;
+    seen[j] = i < sampled ? a.row_ns[i * a.n / sampled] : -1;
+  }
   for (int s = tid; s < slots; s += kPlanThreads) key[s] = -1;
   for (int i = tid; i < m; i += kPlanThreads) cnt[i] = 0;
   if (tid == 0) n_groups = 0;
@@ -134,9 +143,9 @@ __global__ __launch_bounds__(kPlanThreads) void scope_plan_kernel(ScopeArgs a) {
   // the sample: bank rows that lie in a queried namespace, and how many
   // 64-query tiles would score them
   int32_t in = 0, work = 0;
-  const int64_t sampled = a.n < kPlanSample ? a.n : kPlanSample;
-  for (int64_t i = tid; i < sampled; i += kPlanThreads) {
-    const int32_t g = find_ns(key, num, a.bits, a.row_ns[i * a.n / sampled]);
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int32_t g = find_ns(key, num, a.bits, seen[j]);
     if (g >= 0) {
       ++in;
       work += (cnt[g] + 63) / 64;
@@ -189,7 +198,9 @@ __global__ __launch_bounds__(kPlanThreads) void scope_plan_kernel(ScopeArgs a) {
     a.thr[i] = 0u;
     if (group[j] >= 0) {
       a.perm[start[group[j]] + rank[j]] = i;
+      a.q_pos[i] = start[group[j]] + rank[j];
     } else {
+      a.q_pos[i] = -1;
       // no work item covers a query without a namespace: empty partials
       for (int64_t s = 0; s < S; ++s) {
         for (int e = 0; e < a.kcap; ++e) a.part_keys[((i * a.max_splits + s) * a.part_stride) * a.kcap + e] = 0;

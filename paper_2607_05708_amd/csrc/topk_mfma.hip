@@ -1474,7 +1474,7 @@ __global__ __launch_bounds__(256) void group_prep_kernel(const int32_t* __restri
                                                          int64_t* __restrict__ item_off, int32_t* __restrict__ perm,
                                                          uint64_t* __restrict__ part_keys,
                                                          float2* __restrict__ part_ms, int lists_per_split, int kcap,
-                                                         uint32_t* __restrict__ thr) {
+                                                         uint32_t* __restrict__ thr, int32_t* __restrict__ q_pos) {
   __shared__ int32_t cnt[kPrepNs];
   __shared__ int32_t pos[kPrepNs];
   __shared__ int64_t red[4];
@@ -1519,8 +1519,11 @@ __global__ __launch_bounds__(256) void group_prep_kernel(const int32_t* __restri
   for (int64_t i = tid; i < m; i += 256) {
     const int32_t u = key_ns[i];
     if (u >= 0 && u < n_ns) {
-      perm[atomicAdd(&pos[u], 1)] = static_cast<int32_t>(i);
+      const int32_t at = atomicAdd(&pos[u], 1);
+      perm[at] = static_cast<int32_t>(i);
+      q_pos[i] = at;
     } else {
+      q_pos[i] = -1;
       for (int64_t j = 0; j < nl; ++j) part_keys[i * nl + j] = 0;
       for (int s = 0; s < S; ++s) part_ms[i * S + s] = make_float2(-INFINITY, 0.f);
     }
@@ -1532,7 +1535,8 @@ __global__ __launch_bounds__(256) void group_prep_kernel(const int32_t* __restri
 __global__ __launch_bounds__(256) void group_queries_kernel(const u32x4* __restrict__ queries, int64_t q_vecs_stride,
                                                             const int32_t* __restrict__ perm,
                                                             const int64_t* __restrict__ n_grouped, int row_vecs,
-                                                            u32x4* __restrict__ qbuf) {
+                                                            u32x4* __restrict__ qbuf, Gate gate) {
+  if (gate.flag != nullptr && *gate.flag != gate.go) return;
   const int64_t pos = blockIdx.x;
   if (pos >= *n_grouped) return;
   const int64_t q = perm[pos];
@@ -1548,7 +1552,15 @@ __global__ __launch_bounds__(256) void thr_init_kernel(uint32_t* __restrict__ th
 
 }  // namespace
 
-GroupLayout group_layout(int64_t m, int32_t n_ns, int32_t d, size_t base) {
+static_assert(kPrepNs <= kTableMaxNs && kScopeMaxQueries <= kTableMaxNs, "within the table plan's reach");
+
+// Room for the scores of m queries over chunk tables of n_entries rows in all.
+static size_t table_scores(int64_t m, int64_t n_entries) {
+  const int64_t row = (n_entries + 3) / 4 * 4;  // (the longest one table can be)
+  return static_cast<size_t>(row >= kTableScores / m ? kTableScores : m * row);
+}
+
+GroupLayout group_layout(int64_t m, int32_t n_ns, int64_t n_entries, int32_t d, size_t base) {
   auto al = [](size_t x) { return (x + 255) & ~static_cast<size_t>(255); };
   GroupLayout L{};
   const int64_t nb = (static_cast<int64_t>(n_ns) + kScanBlock - 1) / kScanBlock + 1;
@@ -1560,6 +1572,15 @@ GroupLayout group_layout(int64_t m, int32_t n_ns, int32_t d, size_t base) {
   L.bsum = o;     o += al(static_cast<size_t>(nb + 1) * 8);
   L.perm = o;     o += al(static_cast<size_t>(m > 0 ? m : 1) * 4);
   L.qbuf = o;     o += al(static_cast<size_t>(m > 0 ? m : 1) * d * 2);
+  // (not tried where an average table would already need twice the room)
+  L.tables = m > 0 && m <= kPrepM && n_ns > 0 && n_ns <= kPrepNs && n_entries / n_ns <= 2 * kTableScores / m;
+  if (L.tables) {
+    L.q_pos = o;     o += al(static_cast<size_t>(m) * 4);
+    L.flag = o;      o += al(8);
+    L.tile_off = o;  o += al(static_cast<size_t>(n_ns + 1) * 4);
+    L.score_off = o; o += al(static_cast<size_t>(n_ns) * 8);
+    L.scores = o;    o += al(table_scores(m, n_entries) * 4);
+  }
   L.bytes = o;
   return L;
 }
@@ -1614,7 +1635,8 @@ hipError_t run_grouped(const Plan& p, const GroupArgs& ga, int64_t bound, const 
 hipError_t launch_topk_grouped(const Plan& p, const GroupLayout& G, const uint16_t* bank, int64_t bank_stride,
                                int64_t n, const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
                                int32_t k, const int32_t* ns_off, const int32_t* rows, int32_t n_ns,
-                               int64_t n_entries, const int32_t* key_ns, void* ws, hipStream_t stream) {
+                               int64_t n_entries, const int32_t* key_ns, int32_t* idx, float* score,
+                               float* prob, float* lse, void* ws, hipStream_t stream) {
   char* w = static_cast<char*>(ws);
   auto* keys = reinterpret_cast<uint64_t*>(w + p.ws_part_keys);
   auto* ms = reinterpret_cast<float2*>(w + p.ws_part_ms);
@@ -1627,9 +1649,45 @@ hipError_t launch_topk_grouped(const Plan& p, const GroupLayout& G, const uint16
   auto* perm = reinterpret_cast<int32_t*>(w + G.perm);
   auto* qbuf = reinterpret_cast<uint16_t*>(w + G.qbuf);
   const int S = p.n_splits;
+  auto* flag = reinterpret_cast<int32_t*>(w + G.flag);
+  Gate gate;
   if (n_ns <= kPrepNs && m <= kPrepM) {
+    auto* q_pos = reinterpret_cast<int32_t*>(w + (G.tables ? G.q_pos : G.perm));
     group_prep_kernel<<<1, 256, 0, stream>>>(key_ns, m, n_ns, S, q_off, item_off, perm, keys, ms, p.part_stride,
-                                             p.kcap, thr);
+                                             p.kcap, thr, q_pos);
+    if (G.tables) {
+      TableArgs a{};
+      a.bank = bank;
+      a.bank_stride = bank_stride;
+      a.n = n;
+      a.queries = queries;
+      a.q_stride = q_stride;
+      a.m = m;
+      a.d = d;
+      a.c2 = c2;
+      a.k = k;
+      a.ns_off = ns_off;
+      a.off_step = 1;
+      a.chunks = rows;
+      a.n_entries = n_entries;
+      a.n_ns = n_ns;
+      a.q_off = q_off;
+      a.item_off = item_off;
+      a.perm = perm;
+      a.q_pos = q_pos;
+      a.flag = flag;
+      a.tile_off = reinterpret_cast<int32_t*>(w + G.tile_off);
+      a.score_off = reinterpret_cast<int64_t*>(w + G.score_off);
+      a.scores = reinterpret_cast<float*>(w + G.scores);
+      a.max_scores = static_cast<int64_t>(table_scores(m, n_entries));
+      a.idx = idx;
+      a.score = score;
+      a.prob = prob;
+      a.lse = lse;
+      const hipError_t e = launch_topk_tables(a, stream);
+      if (e != hipSuccess) return e;
+      gate = Gate{flag + 1, 1};
+    }
   } else {
     fill_i32_kernel<<<blocks256(n_ns), 256, 0, stream>>>(q_cnt, n_ns, 0);
     fill_i32_kernel<<<blocks256(n_ns), 256, 0, stream>>>(fill, n_ns, 0);
@@ -1643,12 +1701,13 @@ hipError_t launch_topk_grouped(const Plan& p, const GroupLayout& G, const uint16
     thr_init_kernel<<<dim3(static_cast<unsigned>((m + 255) / 256)), 256, 0, stream>>>(thr, m, Gate{});
   }
   group_queries_kernel<<<dim3(static_cast<unsigned>(m)), 256, 0, stream>>>(
-      reinterpret_cast<const u32x4*>(queries), q_stride / 8, perm, q_off + n_ns, d / 8, reinterpret_cast<u32x4*>(qbuf));
+      reinterpret_cast<const u32x4*>(queries), q_stride / 8, perm, q_off + n_ns, d / 8, reinterpret_cast<u32x4*>(qbuf),
+      gate);
   // items: at most (ceil(m / 64) + min(m, n_ns)) query tiles, S splits each
   const int64_t bound = ((m + 63) / 64 + (m < n_ns ? m : n_ns)) * S;
   const GroupArgs ga{ns_off, q_off, item_off, perm, n_ns, S, static_cast<uint32_t>(n * bank_stride * 2), n_entries,
                      1, nullptr, nullptr};
-  return run_grouped(p, ga, bound, bank, bank_stride, n, qbuf, m, d, c2, k, rows, ws, Gate{}, stream);
+  return run_grouped(p, ga, bound, bank, bank_stride, n, qbuf, m, d, c2, k, rows, ws, gate, stream);
 }
 
 bool scope_tables_fit(int64_t m, int64_t n, int32_t d, int32_t k) {
@@ -1678,14 +1737,20 @@ ScopeLayout scope_layout(int64_t m, int64_t n, int32_t d, int32_t k, size_t whol
   L.item_off = o; o += al((mm + 1) * 8);
   L.perm = o;     o += al(mm * 4);
   L.qbuf = o;     o += al(mm * static_cast<size_t>(d) * 2);
+  L.q_pos = o;    o += al(mm * 4);
+  L.tile_off = o; o += al((mm + 1) * 4);
+  L.score_off = o; o += al(mm * 8);
+  L.scores = o;   o += al(table_scores(m, n) * 4);
   L.flags = o > al(whole_bank_bytes) ? o : al(whole_bank_bytes);
+  L.table_flag = L.flags + 128;
   L.end = L.flags + 256;
   return L;
 }
 
 hipError_t launch_topk_scope_grouped(const ScopeLayout& L, const uint16_t* bank, int64_t bank_stride, int64_t n,
                                      const uint16_t* queries, int64_t q_stride, int64_t m, int32_t d, float c2,
-                                     int32_t k, const Scope& scope, void* ws, hipStream_t stream) {
+                                     int32_t k, const Scope& scope, int32_t* idx, float* score, float* prob, float* lse,
+                                     void* ws, hipStream_t stream) {
   char* w = static_cast<char*>(ws);
   ScopeArgs a{};
   a.row_ns = scope.row_ns;
@@ -1703,6 +1768,7 @@ hipError_t launch_topk_scope_grouped(const ScopeLayout& L, const uint16_t* bank,
   a.q_off = reinterpret_cast<int64_t*>(w + L.q_off);
   a.item_off = reinterpret_cast<int64_t*>(w + L.item_off);
   a.perm = reinterpret_cast<int32_t*>(w + L.perm);
+  a.q_pos = reinterpret_cast<int32_t*>(w + L.q_pos);
   a.thr = reinterpret_cast<uint32_t*>(w + L.p.ws_thr);
   a.part_keys = reinterpret_cast<uint64_t*>(w + L.p.ws_part_keys);
   a.part_ms = reinterpret_cast<float2*>(w + L.p.ws_part_ms);
@@ -1714,14 +1780,45 @@ hipError_t launch_topk_scope_grouped(const ScopeLayout& L, const uint16_t* bank,
   a.q_stride = q_stride;
   a.d = d;
   a.qbuf = qbuf;
-  const hipError_t e = launch_scope_tables(a, stream);
+  hipError_t e = launch_scope_tables(a, stream);
+  if (e != hipSuccess) return e;
+  TableArgs t{};
+  t.bank = bank;
+  t.bank_stride = bank_stride;
+  t.n = n;
+  t.queries = queries;
+  t.q_stride = q_stride;
+  t.m = m;
+  t.d = d;
+  t.c2 = c2;
+  t.k = k;
+  t.ns_off = a.table;
+  t.off_step = 2;
+  t.chunks = a.chunks;
+  t.n_entries = n;
+  t.n_ns = static_cast<int>(m);
+  t.q_off = a.q_off;
+  t.item_off = a.item_off;
+  t.perm = a.perm;
+  t.q_pos = a.q_pos;
+  t.flag = reinterpret_cast<int32_t*>(w + L.table_flag);
+  t.tile_off = reinterpret_cast<int32_t*>(w + L.tile_off);
+  t.score_off = reinterpret_cast<int64_t*>(w + L.score_off);
+  t.scores = reinterpret_cast<float*>(w + L.scores);
+  t.max_scores = static_cast<int64_t>(table_scores(m, n));
+  t.gate = a.flags;
+  t.idx = idx;
+  t.score = score;
+  t.prob = prob;
+  t.lse = lse;
+  e = launch_topk_tables(t, stream);
   if (e != hipSuccess) return e;
   // items: tiles of 64 queries, at most ceil(m / 64) + m, in about 256 / tiles splits each
   const int64_t tiles = (m + 63) / 64 + m;
   const GroupArgs ga{a.table, a.q_off,  a.item_off, a.perm,      static_cast<int>(m), 1,
                      static_cast<uint32_t>(n * bank_stride * 2), n, 2, a.flags + 1, nullptr};
   return run_grouped(L.p, ga, tiles > 256 ? tiles : 256, bank, bank_stride, n, qbuf, m, d, c2, k, a.chunks, ws,
-                     Gate{a.flags, 1}, stream);
+                     Gate{t.flag + 1, 1}, stream);
 }
 
 hipError_t launch_topk_mfma(const Plan& p, const uint16_t* bank, int64_t bank_stride, int64_t n,

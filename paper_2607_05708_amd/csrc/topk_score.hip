@@ -110,132 +110,145 @@ struct ScoreArgs {
 constexpr int kStageBytes = 128;
 
 template <typename T, int QB, int QW, int RB, int RW>
-__global__ __launch_bounds__(256) void score_tile_kernel(ScoreArgs a) {
+struct ScoreTile {
   static_assert(QW * RW == 4, "four waves");
-  constexpr int kTileQ = 32 * QB * QW;
-  constexpr int kTileR = 32 * RB * RW;
-  constexpr int kLines = kTileR + kTileQ;         // staged rows: bank rows, then query rows
-  constexpr int kLoads = kLines / 32;             // 16-byte pieces per thread and stage
-  constexpr int kRowLoads = kTileR / 32;
-  constexpr int E = 16 / sizeof(T);               // elements per piece
-  constexpr int KE = kStageBytes / sizeof(T);     // elements per stage
-  __shared__ u32x4 st[2][kLines * 8];
+  static constexpr int kTileQ = 32 * QB * QW;
+  static constexpr int kTileR = 32 * RB * RW;
+  static constexpr int kLines = kTileR + kTileQ;  // staged rows: bank rows, then query rows
+  static constexpr int kLoads = kLines / 32;      // 16-byte pieces per thread and stage: piece
+  static constexpr int kRowLoads = kTileR / 32;   // tid % 8 of staged rows tid / 8 + 32 i
+  static constexpr int E = 16 / sizeof(T);            // elements per piece
+  static constexpr int KE = kStageBytes / sizeof(T);  // elements per stage
+
+  // acc += the tile's scores, src[i] being the thread's staged rows.  Every
+  // thread of the workgroup calls it; it may be called again at once (past
+  // its last barrier only unused fragments are read).
+  static __device__ __forceinline__ void run(u32x4 (&st)[2][kLines * 8], const T* const (&src)[kLoads], int d,
+                                             f32x16 (&acc)[QB][RB]) {
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int c = tid & 7;
+    const int n_st = (d + KE - 1) / KE;
+    // (stages past the last read the rows' last bytes again and are not used)
+    auto load = [&](int s, u32x4 (&v)[kLoads]) {
+      const int k = s * KE + c * E;
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) v[i] = load16_within<T>(src[i], k, d);
+    };
+    const int wr = c ^ ((tid >> 4) & 7);  // (32 rows on, the swizzle is the same)
+    // (the last stage's tail is mended in LDS: a use of the registers there
+    // would make the compiler copy them in every stage, and wait for them)
+    auto store = [&](int s, int buf, const u32x4 (&v)[kLoads]) {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) st[buf][((tid >> 3) + 32 * i) * 8 + wr] = v[i];
+      if ((s + 1) * KE > d && s < n_st) {
+#pragma unroll 1
+        for (int i = 0; i < kLoads; ++i) {
+          u32x4* at = &st[buf][((tid >> 3) + 32 * i) * 8 + wr];
+          *at = fix_tail<T>(*at, s * KE + c * E, d);
+        }
+      }
+    };
+    const int frow = lane & 31;
+    const int part = lane >> 5;
+    const int wq = wave % QW;                // the wave's query group
+    const int wrow = (wave / QW) * 32 * RB;  // and its first row of the tile
+    struct Frag {
+      u32x4 q[QB], r[RB];
+    };
+    auto read = [&](int buf, int step, Frag& f) {
+      const int p = (2 * step + part) ^ ((frow >> 1) & 7);
+#pragma unroll
+      for (int x = 0; x < QB; ++x) f.q[x] = st[buf][(kTileR + (wq * QB + x) * 32 + frow) * 8 + p];
+#pragma unroll
+      for (int y = 0; y < RB; ++y) f.r[y] = st[buf][(wrow + y * 32 + frow) * 8 + p];
+    };
+    auto mma = [&](const Frag& f) {
+      __builtin_amdgcn_sched_barrier(0);  // the reads before it are issued before it
+#pragma unroll
+      for (int x = 0; x < QB; ++x)
+#pragma unroll
+        for (int y = 0; y < RB; ++y) mma16(acc[x][y], f.q[x], f.r[y], T{});
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // Stage s is computed from buffer s % 2 while the loads of stages s + 2
+    // and s + 3 are in flight.  Its staging writes of stage s + 1 go first
+    // (that buffer was last read in stage s - 1, before the barrier in it),
+    // each step's fragments are read ahead of the MFMAs of the step before,
+    // and the barrier stands before the last step, whose MFMAs cover the
+    // reads of the next stage's first fragments.
+    Frag f0, f1;
+    auto stage = [&](int s, int buf, u32x4 (&v)[kLoads]) {
+      store(s + 1, buf ^ 1, v);
+      load(s + 3, v);
+      read(buf, 1, f1);
+      mma(f0);
+      read(buf, 2, f0);
+      mma(f1);
+      read(buf, 3, f1);
+      mma(f0);
+      __syncthreads();
+      read(buf ^ 1, 0, f0);
+      mma(f1);
+    };
+    u32x4 va[kLoads], vb[kLoads];
+    load(0, va);
+    load(1, vb);
+    store(0, 0, va);
+    load(2, va);
+    __syncthreads();
+    read(0, 0, f0);
+    // (no exit inside the loop: the wait counts at its head stay exact; the
+    // last stage writes a buffer that is not read)
+    int s = 0;
+    for (; s + 1 < n_st; s += 2) {
+      stage(s, 0, vb);
+      stage(s + 1, 1, va);
+    }
+    if (s < n_st) stage(s, 0, vb);
+  }
+};
+
+template <typename T, int QB, int QW, int RB, int RW>
+__global__ __launch_bounds__(256) void score_tile_kernel(ScoreArgs a) {
+  using S = ScoreTile<T, QB, QW, RB, RW>;
+  __shared__ u32x4 st[2][S::kLines * 8];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   // Workgroups b, b + 8, ... run on one XCD: the query tiles of one row tile
   // are neighbours there and share its rows through that XCD's L2.
-  const int q_tiles = static_cast<int>((a.nq + kTileQ - 1) / kTileQ);
+  const int q_tiles = static_cast<int>((a.nq + S::kTileQ - 1) / S::kTileQ);
   const int i8 = blockIdx.x >> 3;
-  const int64_t r0 = (static_cast<int64_t>(i8 / q_tiles) * 8 + (blockIdx.x & 7)) * kTileR;
-  const int64_t q0 = static_cast<int64_t>(i8 % q_tiles) * kTileQ;
+  const int64_t r0 = (static_cast<int64_t>(i8 / q_tiles) * 8 + (blockIdx.x & 7)) * S::kTileR;
+  const int64_t q0 = static_cast<int64_t>(i8 % q_tiles) * S::kTileQ;
   if (r0 >= a.rows) return;
-
-  // piece tid % 8 of staged rows tid / 8 + 32 i; rows past the block repeat
-  // its last one (their scores are not written)
-  const int c = tid & 7;
-  const T* src[kLoads];
+  // rows past the block repeat its last one (their scores are not written)
+  const T* src[S::kLoads];
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) {
+  for (int i = 0; i < S::kLoads; ++i) {
     const int line = (tid >> 3) + 32 * i;
-    src[i] = i < kRowLoads
+    src[i] = i < S::kRowLoads
                  ? static_cast<const T*>(a.bank) + min(r0 + line, a.rows - 1) * a.bank_stride
-                 : static_cast<const T*>(a.queries) + min(q0 + line - kTileR, a.nq - 1) * a.q_stride;
+                 : static_cast<const T*>(a.queries) + min(q0 + line - S::kTileR, a.nq - 1) * a.q_stride;
   }
-  const int d = a.d;
-  const int n_st = (d + KE - 1) / KE;
-  // (stages past the last read the rows' last bytes again and are not used)
-  auto load = [&](int s, u32x4 (&v)[kLoads]) {
-    const int k = s * KE + c * E;
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) v[i] = load16_within<T>(src[i], k, d);
-  };
-  const int wr = c ^ ((tid >> 4) & 7);  // (32 rows on, the swizzle is the same)
-  // (the last stage's tail is mended in LDS: a use of the registers there
-  // would make the compiler copy them in every stage, and wait for them)
-  auto store = [&](int s, int buf, const u32x4 (&v)[kLoads]) {
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) st[buf][((tid >> 3) + 32 * i) * 8 + wr] = v[i];
-    if ((s + 1) * KE > d && s < n_st) {
-#pragma unroll 1
-      for (int i = 0; i < kLoads; ++i) {
-        u32x4* at = &st[buf][((tid >> 3) + 32 * i) * 8 + wr];
-        *at = fix_tail<T>(*at, s * KE + c * E, d);
-      }
-    }
-  };
   f32x16 acc[QB][RB];
 #pragma unroll
   for (int x = 0; x < QB; ++x)
 #pragma unroll
     for (int y = 0; y < RB; ++y) acc[x][y] = f32x16{};
-  const int frow = lane & 31;
-  const int part = lane >> 5;
-  const int wq = wave % QW;                  // the wave's query group
-  const int wrow = (wave / QW) * 32 * RB;    // and its first row of the tile
-  struct Frag {
-    u32x4 q[QB], r[RB];
-  };
-  auto read = [&](int buf, int step, Frag& f) {
-    const int p = (2 * step + part) ^ ((frow >> 1) & 7);
-#pragma unroll
-    for (int x = 0; x < QB; ++x) f.q[x] = st[buf][(kTileR + (wq * QB + x) * 32 + frow) * 8 + p];
-#pragma unroll
-    for (int y = 0; y < RB; ++y) f.r[y] = st[buf][(wrow + y * 32 + frow) * 8 + p];
-  };
-  auto mma = [&](const Frag& f) {
-    __builtin_amdgcn_sched_barrier(0);  // the reads before it are issued before it
-#pragma unroll
-    for (int x = 0; x < QB; ++x)
-#pragma unroll
-      for (int y = 0; y < RB; ++y) mma16(acc[x][y], f.q[x], f.r[y], T{});
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  // Stage s is computed from buffer s % 2 while the loads of stages s + 2 and
-  // s + 3 are in flight.  Its staging writes of stage s + 1 go first (that
-  // buffer was last read in stage s - 1, before the barrier in it), each
-  // step's fragments are read ahead of the MFMAs of the step before, and the
-  // barrier stands before the last step, whose MFMAs cover the reads of the
-  // next stage's first fragments.
-  Frag f0, f1;
-  auto stage = [&](int s, int buf, u32x4 (&v)[kLoads]) {
-    store(s + 1, buf ^ 1, v);
-    load(s + 3, v);
-    read(buf, 1, f1);
-    mma(f0);
-    read(buf, 2, f0);
-    mma(f1);
-    read(buf, 3, f1);
-    mma(f0);
-    __syncthreads();
-    read(buf ^ 1, 0, f0);
-    mma(f1);
-  };
-  u32x4 va[kLoads], vb[kLoads];
-  load(0, va);
-  load(1, vb);
-  store(0, 0, va);
-  load(2, va);
-  __syncthreads();
-  read(0, 0, f0);
-  // (no exit inside the loop: the wait counts at its head stay exact; the
-  // last stage writes a buffer that is not read)
-  int s = 0;
-  for (; s + 1 < n_st; s += 2) {
-    stage(s, 0, vb);
-    stage(s + 1, 1, va);
-  }
-  if (s < n_st) stage(s, 0, vb);
-  // accumulator lane: row lane % 32 of its block, queries 8 (r / 4) + 4 part + r % 4
+  S::run(st, src, a.d, acc);
+  // accumulator lane: row lane % 32 of its block, queries 8 (r / 4) + 4 (lane / 32) + r % 4
 #pragma unroll
   for (int y = 0; y < RB; ++y) {
-    const int64_t row = r0 + wrow + y * 32 + frow;
+    const int64_t row = r0 + (wave / QW) * 32 * RB + y * 32 + (lane & 31);
     if (row < a.rows) {
 #pragma unroll
       for (int x = 0; x < QB; ++x)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int64_t q = q0 + (wq * QB + x) * 32 + 8 * (r >> 2) + 4 * part + (r & 3);
+          const int64_t q = q0 + (wave % QW * QB + x) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
           if (q < a.nq) a.out[q * a.ld + row] = acc[x][y][r];
         }
     }
@@ -329,6 +342,33 @@ struct SelectArgs {
   float* lse;
 };
 
+// Folds a step's scores into the thread's softmax state (-inf adds nothing)
+// and returns the largest order key among them; bit j of `out`: value j is no
+// candidate.
+__device__ __forceinline__ uint32_t fold_step(const float (&v)[kSelPer], uint32_t out, float c2, float& m_run,
+                                              double& s_run) {
+  float best = v[0];
+#pragma unroll
+  for (int j = 1; j < kSelPer; ++j) best = fmaxf(best, v[j]);
+  const float mx = fmaxf(m_run, best * c2);
+  double part = 0.0;
+  if (mx != -INFINITY) {
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j) part += static_cast<double>(fast_exp2(v[j] * c2 - mx));
+    s_run = s_run * static_cast<double>(fast_exp2(m_run - mx)) + part;
+    m_run = mx;
+  }
+  uint32_t top = f2ord(best);
+  // (not so where a value is no candidate or a NaN, which fmaxf passes by but
+  // the sum above does not)
+  if (out != 0 || !(best > -INFINITY) || !(part < INFINITY)) {
+    top = 0;
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j) top = max(top, ((out >> j) & 1u) ? 0u : f2ord(v[j]));
+  }
+  return top;
+}
+
 // One workgroup per (query, split): the split's scores of this block, 4,096
 // a step.  A split that an earlier block began resumes from its list and
 // softmax state (the sum in two floats, so that nothing of the double is
@@ -392,27 +432,9 @@ __global__ __launch_bounds__(kSelThreads, 4) void select_kernel(SelectArgs a) {
         }
       }
     }
-    float best = v[0];
-#pragma unroll
-    for (int j = 1; j < kSelPer; ++j) best = fmaxf(best, v[j]);
-    const float mx = fmaxf(m_run, best * a.c2);
-    double part = 0.0;
-    if (mx != -INFINITY) {
-#pragma unroll
-      for (int j = 0; j < kSelPer; ++j) part += static_cast<double>(fast_exp2(v[j] * a.c2 - mx));
-      s_run = s_run * static_cast<double>(fast_exp2(m_run - mx)) + part;
-      m_run = mx;
-    }
     auto hi = [&](int j) { return ((out >> j) & 1u) ? 0u : f2ord(v[j]); };
     const uint32_t low = 0xFFFFFFFFu - static_cast<uint32_t>(base) - 4 * tid;
-    uint32_t top = f2ord(best);
-    // (not so where a value is no candidate or a NaN, which fmaxf passes by
-    // but the sum above does not)
-    if (out != 0 || !(best > -INFINITY) || !(part < INFINITY)) {
-      top = 0;
-#pragma unroll
-      for (int j = 0; j < kSelPer; ++j) top = max(top, hi(j));
-    }
+    const uint32_t top = fold_step(v, out, a.c2, m_run, s_run);
     cur = select_step<true>(
         L, hi,
         [&](int j) {
@@ -469,6 +491,221 @@ __global__ __launch_bounds__(kSelThreads, 4) void select_kernel(SelectArgs a) {
   }
 }
 
+// ---------------------------------------------------------------- chunk tables
+
+// The same two steps over chunk tables: every query against the rows its
+// own namespace's table lists.  One workgroup plans: the tiles of each
+// namespace (32 of its queries x 128 of its rows), where its scores go (a row
+// of the table's length per query), and whether it is done this way at all:
+// the scores have to fit their room and no table may be so long that one
+// workgroup's selection from it would be waited for.  Otherwise the fused
+// grouped pass does it; the losing side's launches return at once.
+//
+// The fused pass takes a whole table per workgroup: with 256 tables of 5 to
+// 11 of its 512-row tiles the longest set the time, and lists that start
+// empty take most of their first tile's time.  1,024 queries over 256 tables
+// of about 3,700 x 1024 rows, k = 5: 578 us, k = 32: 690 + 65 us (sample);
+// this way 380 us of scores (5.0 TB/s of bank rows) and 24-26 us of selection.
+constexpr int kTablePlanThreads = 1024;
+constexpr int kTablePlanPer = static_cast<int>(kTableMaxNs) / kTablePlanThreads;
+
+__device__ __forceinline__ int64_t table_first(const TableArgs& a, int u) {
+  return min(max(static_cast<int64_t>(a.ns_off[static_cast<int64_t>(u) * a.off_step]), int64_t{0}), a.n_entries);
+}
+// (offsets are clamped so a malformed table cannot send reads past it)
+__device__ __forceinline__ int table_length(const TableArgs& a, int u) {
+  const int64_t lo = table_first(a, u);
+  const int64_t hi = min(static_cast<int64_t>(a.ns_off[static_cast<int64_t>(u) * a.off_step + 1]), a.n_entries);
+  return static_cast<int>(max(hi - lo, int64_t{0}));
+}
+
+__global__ __launch_bounds__(kTablePlanThreads) void table_plan_kernel(TableArgs a) {
+  __shared__ int64_t red[2][kTablePlanThreads / 64];
+  __shared__ int longest;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  if (a.gate != nullptr && *a.gate == 0) {  // (uniform) no tables
+    if (tid == 0) {
+      a.flag[0] = a.flag[1] = 0;
+      a.tile_off[a.n_ns] = 0;
+    }
+    return;
+  }
+  if (tid == 0) longest = 0;
+  __syncthreads();
+  int64_t tiles[kTablePlanPer], room[kTablePlanPer], sum_t = 0, sum_r = 0;
+#pragma unroll
+  for (int j = 0; j < kTablePlanPer; ++j) {
+    const int u = tid * kTablePlanPer + j;
+    tiles[j] = room[j] = 0;
+    if (u < a.n_ns) {
+      const int64_t nq = a.q_off[u + 1] - a.q_off[u];
+      if (nq > 0) {
+        const int len = table_length(a, u);
+        tiles[j] = (nq + 31) / 32 * ((len + 127) / 128);
+        room[j] = nq * ((len + 3) / 4 * 4);
+        atomicMax(&longest, len);
+      }
+    }
+    sum_t += tiles[j];
+    sum_r += room[j];
+  }
+  int64_t inc_t = sum_t, inc_r = sum_r;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int64_t t = __shfl_up(inc_t, off), r = __shfl_up(inc_r, off);
+    if (lane >= off) {
+      inc_t += t;
+      inc_r += r;
+    }
+  }
+  if (lane == 63) {
+    red[0][wave] = inc_t;
+    red[1][wave] = inc_r;
+  }
+  __syncthreads();
+  int64_t at_t = inc_t - sum_t, at_r = inc_r - sum_r, all_t = 0, all_r = 0;
+  for (int w = 0; w < kTablePlanThreads / 64; ++w) {
+    at_t += w < wave ? red[0][w] : 0;
+    at_r += w < wave ? red[1][w] : 0;
+    all_t += red[0][w];
+    all_r += red[1][w];
+  }
+  const bool use = all_r <= a.max_scores && longest <= kTableMaxRows;
+#pragma unroll
+  for (int j = 0; j < kTablePlanPer; ++j) {
+    const int u = tid * kTablePlanPer + j;
+    if (u < a.n_ns) {
+      a.tile_off[u] = use ? static_cast<int32_t>(at_t) : 0;
+      a.score_off[u] = at_r;
+    }
+    at_t += tiles[j];
+    at_r += room[j];
+  }
+  if (tid == 0) {
+    a.flag[0] = use ? 1 : 0;
+    a.flag[1] = use ? 0 : 1;
+    a.tile_off[a.n_ns] = use ? static_cast<int32_t>(all_t) : 0;
+    if (use) a.item_off[a.n_ns] = 0;  // no work item for the fused pass
+  }
+}
+
+// The last of off[0 .. n) that is <= x (off ascends from 0, n <= 4096): two
+// loads per lane instead of a chain of twelve.
+template <typename I>
+__device__ __forceinline__ int find_last(const I* off, int n, I x) {
+  const int lane = threadIdx.x & 63;
+  const I a = 64 * lane < n ? off[64 * lane] : x + 1;
+  const int hi = __builtin_popcountll(__ballot(a <= x)) - 1;
+  const I b = 64 * hi + lane < n ? off[64 * hi + lane] : x + 1;
+  return __builtin_amdgcn_readfirstlane(64 * hi + __builtin_popcountll(__ballot(b <= x)) - 1);
+}
+
+__global__ __launch_bounds__(256) void score_tables_kernel(TableArgs a) {
+  using S = ScoreTile<uint16_t, 1, 1, 1, 4>;
+  __shared__ u32x4 st[2][S::kLines * 8];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int total = a.tile_off[a.n_ns];
+  for (int item = blockIdx.x; item < total; item += gridDim.x) {
+    const int u = find_last(a.tile_off, a.n_ns, item);
+    const int local = item - a.tile_off[u];
+    const int len = table_length(a, u);
+    const int row_tiles = (len + 127) / 128;
+    const int r0 = local % row_tiles * 128;
+    const int q0 = local / row_tiles * 32;
+    const int64_t q_first = a.q_off[u];
+    const int nq = static_cast<int>(a.q_off[u + 1] - q_first);
+    const int32_t* rows = a.chunks + table_first(a, u);
+    const uint16_t* src[S::kLoads];
+#pragma unroll
+    for (int i = 0; i < S::kLoads; ++i) {
+      const int line = (tid >> 3) + 32 * i;
+      if (i < S::kRowLoads) {
+        // an entry outside the bank reads row 0 (and is no candidate)
+        const int32_t r = rows[min(r0 + line, len - 1)];
+        src[i] = a.bank + (r >= 0 && r < a.n ? r : 0) * a.bank_stride;
+      } else {
+        src[i] = a.queries + a.perm[q_first + min(q0 + line - S::kTileR, nq - 1)] * a.q_stride;
+      }
+    }
+    f32x16 acc[1][1] = {{f32x16{}}};
+    S::run(st, src, a.d, acc);
+    const int row = r0 + wave * 32 + (lane & 31);
+    const int64_t pitch = (len + 3) / 4 * 4;
+    float* out = a.scores + a.score_off[u] + row;
+    if (row < len) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int q = q0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        if (q < nq) out[q * pitch] = acc[0][0][r];
+      }
+    }
+  }
+}
+
+// One workgroup per query: the selection over its table's scores.
+__global__ __launch_bounds__(kSelThreads, 4) void select_tables_kernel(TableArgs a) {
+  if (a.flag[0] == 0) return;
+  __shared__ SelectLds L;
+  const int tid = threadIdx.x;
+  const int64_t q = blockIdx.x;
+  const int32_t pos = a.q_pos[q];
+  int cur = 0;
+  if (tid < kMaxK) L.list[0][tid] = 0;
+  float m_run = -INFINITY;
+  double s_run = 0.0;
+  __syncthreads();
+  if (pos >= 0) {  // (uniform: a query without a namespace has no candidates)
+    const int u = find_last(a.q_off, a.n_ns, static_cast<int64_t>(pos));
+    const int len = table_length(a, u);
+    const int32_t* rows = a.chunks + table_first(a, u);
+    const float* row = a.scores + a.score_off[u] + (pos - a.q_off[u]) * static_cast<int64_t>((len + 3) / 4 * 4);
+    auto at = [&](int j) { return 1024 * (j >> 2) + 4 * tid + (j & 3); };
+    for (int base = 0; base < len; base += kSelStep) {
+      const int left = min(len - base, kSelStep);
+      float v[kSelPer];
+      int32_t id[kSelPer];
+#pragma unroll
+      for (int j = 0; j < kSelPer; j += 4) {
+        const int e = at(j);
+        // (a row's room is a multiple of 4 scores)
+        const f32x4 x = e < left ? *reinterpret_cast<const f32x4*>(row + base + e) : f32x4{};
+        v[j] = x.x, v[j + 1] = x.y, v[j + 2] = x.z, v[j + 3] = x.w;
+        if (e + 4 <= left) {
+          __builtin_memcpy(&id[j], rows + base + e, 16);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) id[j + i] = e + i < left ? rows[base + e + i] : -1;
+        }
+      }
+      uint32_t out = 0;  // an entry outside the bank is no candidate
+#pragma unroll
+      for (int j = 0; j < kSelPer; ++j) {
+        if (id[j] < 0 || id[j] >= a.n) {
+          out |= 1u << j;
+          v[j] = -INFINITY;
+        }
+      }
+      const uint32_t top = fold_step(v, out, a.c2, m_run, s_run);
+      auto hi = [&](int j) { return ((out >> j) & 1u) ? 0u : f2ord(v[j]); };
+      // (ids ascend within a table)
+      cur = select_step<true>(
+          L, hi,
+          [&](int j) {
+            const uint32_t h = hi(j);
+            return h ? (static_cast<uint64_t>(h) << 32) | (0xFFFFFFFFu - static_cast<uint32_t>(id[j])) : uint64_t{0};
+          },
+          top, a.k, cur);
+    }
+  }
+  const SoftmaxSum all = block_softmax(L, m_run, s_run);
+  const float lse2 = all.max + static_cast<float>(log2(all.sum));
+  if (tid < a.k) write_selected(L.list[cur][tid], a.c2, lse2, q * a.k + tid, a.idx, a.score, a.prob);
+  if (tid == 0 && a.lse) a.lse[q] = lse2 * kLn2;
+}
+
 int64_t tile_queries(int64_t nq) { return nq <= 32 ? 32 : (nq <= 64 ? 64 : 128); }
 
 // Whether the whole call (not one block of it, so that scores do not depend
@@ -506,6 +743,13 @@ hipError_t launch_score(const ScoreArgs& a, bool small, hipStream_t stream) {
 }
 
 }  // namespace
+
+hipError_t launch_topk_tables(const TableArgs& a, hipStream_t stream) {
+  table_plan_kernel<<<1, kTablePlanThreads, 0, stream>>>(a);
+  score_tables_kernel<<<1024, 256, 0, stream>>>(a);  // four workgroups per CU, each taking every 1,024th tile
+  select_tables_kernel<<<dim3(static_cast<unsigned>(a.m)), kSelThreads, 0, stream>>>(a);
+  return hipGetLastError();
+}
 
 hipError_t launch_topk_score(const Plan& p, const void* bank, int64_t bank_stride, int64_t n, const void* queries,
                              int64_t q_stride, int64_t m, int32_t d, int32_t dtype, float c2, int64_t self_base,

@@ -65,7 +65,9 @@ __global__ __launch_bounds__(256) void topk_merge_rank_kernel(const uint64_t* __
                                                               int32_t* __restrict__ idx, float* __restrict__ score,
                                                               float* __restrict__ prob, float* __restrict__ lse,
                                                               float* __restrict__ lse2_out, float* __restrict__ full,
-                                                              int64_t n_full, int64_t self_base) {
+                                                              int64_t n_full, int64_t self_base,
+                                                              const int32_t* done) {
+  if (done != nullptr && *done != 0) return;
   extern __shared__ uint64_t rank_smem[];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -138,6 +140,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_merge_select_kernel(
     const uint64_t* __restrict__ part_keys, const float2* __restrict__ part_ms, int n_parts, int kcap, int k, int kk,
     float c2, int32_t* __restrict__ idx, float* __restrict__ score, float* __restrict__ prob, float* __restrict__ lse,
     float* __restrict__ lse2_out, MergeAlt alt) {
+  if (alt.done != nullptr && *alt.done != 0) return;
   __shared__ SelectLds L;
   const int tid = threadIdx.x;
   const int64_t q = blockIdx.x;
@@ -220,7 +223,7 @@ hipError_t launch_topk_merge(const Plan& p, int64_t m, int32_t k, float c2, int3
     const bool fused = fp.full != nullptr && fp.n <= kRankFullMax;
     topk_merge_rank_kernel<<<dim3(static_cast<unsigned>((m + 3) / 4)), 256, rank_lds_bytes(p.n_parts, k), stream>>>(
         keys, ms, m, p.n_parts, kcap_eff, k, c2, idx, score, prob, lse, lse2, fused ? fp.full : nullptr, fp.n,
-        fp.self_base);
+        fp.self_base, alt.done);
     return fused ? hipGetLastError() : finish(hipGetLastError());
   }
   int kk = 1;

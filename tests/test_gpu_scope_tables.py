@@ -32,7 +32,8 @@ def check(name, b, q, rns, live, kns, out, k, seed):
     torch.cuda.synchronize()
     g = dict(zip(("idx", "score", "prob", "lse"), (t.cpu().numpy() for t in out)))
     m = q.shape[0]
-    rows = np.unique(np.concatenate([[0, 63, 64, m - 1], np.random.default_rng(seed).choice(m, 16, replace=False)]))
+    some = np.random.default_rng(seed).choice(m, min(m, 16), replace=False)
+    rows = np.unique(np.concatenate([[0, min(63, m - 1), min(64, m - 1), m - 1], some]))
     check_topk_scoped(name, q, b, rows, {key: v[rows] for key, v in g.items()}, k, 1.0, rns, live, kns)
     return g
 
@@ -91,3 +92,36 @@ def test_captured_call_follows_the_namespaces():
         ws.fill_(255)
         graph.replay()
         check(f"replay-{rep}", b, q, rns, live, kns, out, k, rep)
+
+
+def grouped_check(lengths, counts, d, k, seed, n_extra=0):
+    """Grouped retrieval with tables of these lengths and these many queries each (interleaved rows and queries)."""
+    n = sum(lengths) + n_extra
+    m = sum(counts)
+    rng = np.random.default_rng(seed)
+    bt, b = bank_of(seed, n, d)
+    qt, q = bank_of(seed + 100, m, d)
+    rns = np.concatenate([np.repeat(np.arange(len(lengths)), lengths), np.full(n_extra, -1)]).astype(np.int32)
+    rng.shuffle(rns)
+    kns = np.repeat(np.arange(len(counts)), counts).astype(np.int32)
+    rng.shuffle(kns)
+    offsets = np.zeros(len(lengths) + 1, np.int32)
+    offsets[1:] = np.cumsum(lengths)
+    live = np.nonzero(rns >= 0)[0]
+    chunks = live[np.argsort(rns[live], kind="stable")].astype(np.int32)
+    out = pm.mem_retrieve_topk_grouped(bt, up(offsets), up(chunks), qt, up(kns), k, 1.0)
+    check(f"grouped-{seed}", b, q, rns, (rns >= 0).astype(np.uint8), kns, out, k, seed)
+
+
+@pytest.mark.parametrize("d,k", [(96, 32), (160, 7), (1024, 16)])
+def test_grouped_tile_and_step_edges(d, k):
+    # tables around the 128-row tile and the 4,096-score step, queries around the tile of 32
+    lengths = [0, 1, 2, 127, 128, 129, 4095, 4096, 4097, 5, 8193]
+    counts = [3, 1, 33, 32, 31, 65, 2, 1, 40, 0, 3]
+    grouped_check(lengths, counts, d, k, 80, n_extra=11)
+
+
+@pytest.mark.parametrize("length,queries", [(24576, 512), (24577, 512), (32768, 4), (32769, 4)])
+def test_both_sides_of_the_table_rule(length, queries):
+    # 12 * 2^20 scores and tables of 32,768 rows are the most that are scored first and selected from after
+    grouped_check([length, 300], [queries, 0], 96, 10, 90 + queries % 7)

@@ -236,8 +236,7 @@ struct FullProb {
   int64_t self_base = -1;
 };
 // Merge split partials into the final top-k, probabilities and lse, and
-// finish the full probability rows if requested (in the merge's own launch
-// for a rank merge over a small bank, else with launch_full_prob after it).
+// finish the full probability rows if requested (launch_full_prob).
 hipError_t launch_topk_merge(const Plan& p, int64_t m, int32_t k, float c2, int32_t* idx, float* score, float* prob,
                              float* lse, void* ws, hipStream_t stream, const FullProb& fp = FullProb{},
                              const MergeAlt& alt = MergeAlt{});

@@ -9,9 +9,9 @@ namespace memattn {
 
 namespace {
 
-// Softmax partials of one query (at most 64), combined by one wave: lse2 =
-// log2 of the normaliser in the scaled log2 domain (max, then the rescaled sum
-// in fp64).
+// Softmax partials of one query (at most 64: lists of at most 512 keys in
+// all, 8 or more each), combined by one wave: lse2 = log2 of the normaliser in
+// the scaled log2 domain (max, then the rescaled sum in fp64).
 __device__ __forceinline__ float wave_lse2(const float2* __restrict__ ms, int n_parts, int lane) {
   const float2 v = lane < n_parts ? ms[lane] : make_float2(-INFINITY, 0.f);
   float m = v.x;
@@ -21,83 +21,75 @@ __device__ __forceinline__ float wave_lse2(const float2* __restrict__ ms, int n_
   return m + static_cast<float>(log2(s));
 }
 
-// Copy the first k keys of lists [l0, l0 + nl) (list l at keys + l * kcap)
-// into dst[(l - l0) * k + j] with one wave, 16 loads in flight per lane.
-__device__ __forceinline__ void stage_list_heads(uint64_t* dst, const uint64_t* __restrict__ keys, int l0, int nl,
-                                                 int k, int kcap, int lane) {
-  constexpr int kU = 16;
-  const int total = nl * k;
-  for (int base = 0; base < total; base += 64 * kU) {
-    uint64_t v[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int i = base + u * 64 + lane;
-      v[u] = i < total ? keys[static_cast<int64_t>(l0 + i / k) * kcap + i % k] : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int i = base + u * 64 + lane;
-      if (i < total) dst[i] = v[u];
-    }
-  }
-}
-
-// One wave per key, four keys per workgroup, for few partial lists
-// (S * k <= kRankMaxKeys): the first k keys of every list are staged in LDS
-// and each staged key finds its rank in the union by a binary search in
-// every (descending) list; keys are unique (except empty slots, which rank
-// below every real key), so the keys of rank < k are exactly the top-k and
-// each lands in its own output slot.
-// LDS is sized per launch (rank_lds_bytes): four waves' staged keys and
-// chosen keys, so that short rows leave room for more workgroups per CU.
-// With `full` set (a bank of at most kRankFullMax rows) the wave also turns
-// its query's row of raw scores there into probabilities, saving the
-// separate launch of full_prob_kernel (same arithmetic).
-constexpr int kRankMaxKeys = 1024;
-constexpr int64_t kRankFullMax = 4096;
-size_t rank_lds_bytes(int n_parts, int k) {
-  return 4 * (static_cast<size_t>(n_parts) * k + kMaxK) * sizeof(uint64_t);
-}
-
-__global__ __launch_bounds__(256) void topk_merge_rank_kernel(const uint64_t* __restrict__ part_keys,
+// One wave per key, four keys per workgroup, for lists of at most 64 * PER
+// keys in all (PER <= 8) and k <= 32: lane l's j-th key is rank (l + j) % kk of
+// list j * (64 / kk) + l / kk (kk: k rounded up to a power of two), so that
+// each lane gets every rank in turn.  As in select.h the k-th largest of the
+// lanes' own largest upper halves bounds the candidates, which are compacted
+// by ballots and ranked by counting, here without a workgroup barrier.
+// Against a rank by binary search in every other list (few lists) and a
+// k-step tournament over the list heads (more), whole calls: relation builds
+// of 12,288 keys (5 lists of 32) 402 -> 366 us, of 8,192 (8 of 32) 245 -> 222
+// us, 8,000 queries (8 of 32) 669 -> 645 us, 4,096 (16 of 32) 693 -> 685 us.
+template <int PER>
+__global__ __launch_bounds__(256) void topk_merge_wave_kernel(const uint64_t* __restrict__ part_keys,
                                                               const float2* __restrict__ part_ms, int64_t m,
-                                                              int n_parts, int kcap, int k, float c2,
+                                                              int n_parts, int kcap, int k, int kk, float c2,
                                                               int32_t* __restrict__ idx, float* __restrict__ score,
                                                               float* __restrict__ prob, float* __restrict__ lse,
-                                                              float* __restrict__ lse2_out, float* __restrict__ full,
-                                                              int64_t n_full, int64_t self_base,
-                                                              const int32_t* done) {
+                                                              float* __restrict__ lse2_out,
+                                                              const int32_t* __restrict__ done) {
   if (done != nullptr && *done != 0) return;
-  extern __shared__ uint64_t rank_smem[];
+  typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+  __shared__ __attribute__((aligned(16))) uint64_t all_cand[4][64 * PER + 2];
+  __shared__ uint64_t all_chosen[4][32];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + wave;
   if (q >= m) return;  // whole waves only; no workgroup barrier below
-  const int total = n_parts * k;
-  uint64_t* st = rank_smem + static_cast<int64_t>(wave) * (total + kMaxK);
-  uint64_t* chosen = st + total;
+  uint64_t* cand = all_cand[wave];
+  uint64_t* chosen = all_chosen[wave];
   const uint64_t* keys = part_keys + q * static_cast<int64_t>(n_parts) * kcap;
-  // ranks that no key takes (fewer than k candidates) stay empty
-  if (lane < k) chosen[lane] = 0;
+  const int per = 64 / kk;  // lists read at a time
+  uint64_t x[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int s = j * per + lane / kk;
+    const int r = (lane + j) & (kk - 1);
+    x[j] = (s < n_parts && r < k) ? keys[static_cast<int64_t>(s) * kcap + r] : 0;
+  }
   const float lse2 = wave_lse2(part_ms + q * n_parts, n_parts, lane);
-  stage_list_heads(st, keys, 0, n_parts, k, kcap, lane);
+  if (lane < k) chosen[lane] = 0;  // ranks that no key takes (fewer than k candidates) stay empty
+  uint32_t top = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) top = max(top, static_cast<uint32_t>(x[j] >> 32));
+  uint32_t least = 0;
+  for (int b = 31; b >= 32 - kBoundBits; --b) {
+    const uint32_t c = least | (1u << b);
+    if (__builtin_popcountll(__ballot(top >= c)) >= k) least = c;
+  }
+  least = least < 1u ? 1u : least;
+  int total = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const bool in = static_cast<uint32_t>(x[j] >> 32) >= least;
+    const uint64_t bal = __ballot(in);
+    if (in) cand[total + __popcll(bal & ((uint64_t{1} << lane) - 1))] = x[j];
+    total += __popcll(bal);
+  }
+  if (lane == 0) cand[total] = 0;
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   for (int i = lane; i < total; i += 64) {
-    const uint64_t x = st[i];
-    if (x == 0) continue;
-    int rank = 0;
-    for (int s = 0; s < n_parts; ++s) {
-      // number of keys > x in list s: first position holding a key <= x
-      const uint64_t* l = st + s * k;
-      int lo = 0, hi = k;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (l[mid] > x) lo = mid + 1; else hi = mid;
-      }
-      rank += lo;
+    const uint64_t y = cand[i];
+    const u64x2* c = reinterpret_cast<const u64x2*>(cand);
+    int r = 0;
+#pragma unroll 8
+    for (int e = 0; e < (total + 1) / 2; ++e) {
+      const u64x2 v = c[e];
+      r += (v.x > y ? 1 : 0) + (v.y > y ? 1 : 0);
     }
-    if (rank < k) chosen[rank] = x;
+    if (r < k) chosen[r] = y;
   }
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -105,25 +97,6 @@ __global__ __launch_bounds__(256) void topk_merge_rank_kernel(const uint64_t* __
   if (lane == 0) {
     if (lse) lse[q] = lse2 * kLn2;
     lse2_out[q] = lse2;
-  }
-  if (full != nullptr) {
-    // 16 values per lane in flight at a time (n_full <= kRankFullMax)
-    float* row = full + q * n_full;
-    constexpr int kU = 16;
-    for (int64_t base = 0; base < n_full; base += 64 * kU) {
-      float v[kU];
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int64_t j = base + u * 64 + lane;
-        v[u] = j < n_full ? row[j] : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int64_t j = base + u * 64 + lane;
-        if (j < n_full)
-          row[j] = ((self_base >= 0 && j == self_base + q) || lse2 == -INFINITY) ? 0.f : fast_exp2(v[u] * c2 - lse2);
-      }
-    }
   }
 }
 
@@ -207,30 +180,35 @@ __global__ __launch_bounds__(256) void full_prob_kernel(float* __restrict__ full
 
 hipError_t launch_topk_merge(const Plan& p, int64_t m, int32_t k, float c2, int32_t* idx, float* score, float* prob,
                              float* lse, void* ws, hipStream_t stream, const FullProb& fp, const MergeAlt& alt) {
-  // every merge but the fused rank merge leaves the full rows to full_prob_kernel
-  auto finish = [&](hipError_t e) -> hipError_t {
-    if (e != hipSuccess || fp.full == nullptr) return e;
-    return launch_full_prob(p, m, fp.n, c2, fp.self_base, fp.full, ws, stream);
-  };
   char* w = static_cast<char*>(ws);
   const auto* keys = reinterpret_cast<const uint64_t*>(w + p.ws_part_keys);
   const auto* ms = reinterpret_cast<const float2*>(w + p.ws_part_ms);
   auto* lse2 = reinterpret_cast<float*>(w + p.ws_lse2);
-  const int64_t S = p.n_parts;
   // consecutive lists of a key start kcap_eff keys apart (every part_stride-th slot)
   const int kcap_eff = p.kcap * p.part_stride;
-  if (S * k <= kRankMaxKeys && S <= 4 && alt.flag == nullptr) {
-    const bool fused = fp.full != nullptr && fp.n <= kRankFullMax;
-    topk_merge_rank_kernel<<<dim3(static_cast<unsigned>((m + 3) / 4)), 256, rank_lds_bytes(p.n_parts, k), stream>>>(
-        keys, ms, m, p.n_parts, kcap_eff, k, c2, idx, score, prob, lse, lse2, fused ? fp.full : nullptr, fp.n,
-        fp.self_base, alt.done);
-    return fused ? hipGetLastError() : finish(hipGetLastError());
-  }
-  int kk = 1;
+  int kk = 8;
   while (kk < k) kk <<= 1;
-  topk_merge_select_kernel<<<dim3(static_cast<unsigned>(m)), kSelThreads, 0, stream>>>(
-      keys, ms, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob, lse, lse2, alt);
-  return finish(hipGetLastError());
+  const int64_t total = static_cast<int64_t>(p.n_parts) * kk;
+  // One wave up to 512 keys; a workgroup is sooner done with more (100
+  // queries with 128 lists of 8: 344 against 352 us for the whole call).
+  if (k <= 32 && total <= 512 && alt.flag == nullptr) {
+    const dim3 grid(static_cast<unsigned>((m + 3) / 4));
+    if (total <= 64)
+      topk_merge_wave_kernel<1><<<grid, 256, 0, stream>>>(keys, ms, m, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob,
+                                                          lse, lse2, alt.done);
+    else if (total <= 256)
+      topk_merge_wave_kernel<4><<<grid, 256, 0, stream>>>(keys, ms, m, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob,
+                                                          lse, lse2, alt.done);
+    else
+      topk_merge_wave_kernel<8><<<grid, 256, 0, stream>>>(keys, ms, m, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob,
+                                                          lse, lse2, alt.done);
+  } else {
+    topk_merge_select_kernel<<<dim3(static_cast<unsigned>(m)), kSelThreads, 0, stream>>>(
+        keys, ms, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob, lse, lse2, alt);
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || fp.full == nullptr) return e;
+  return launch_full_prob(p, m, fp.n, c2, fp.self_base, fp.full, ws, stream);
 }
 
 hipError_t launch_full_prob(const Plan& p, int64_t m, int64_t n, float c2, int64_t self_base, float* full, void* ws,

@@ -52,4 +52,43 @@ struct SoftmaxState {
   float sum;
 };
 
+// Reductions over a fully active wave, the same value in every lane: DPP steps
+// combine each 16-lane row (lane ^ 1, lane ^ 2, then the half row and row
+// mirrors), and the four rows' results are read out as scalars -- a few vector
+// instructions instead of six dependent permutes through the LDS unit.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float lane_f32(float x, int lane) {
+  return __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(x)), lane)));
+}
+__device__ __forceinline__ float wave_max_f32(float x) {
+  x = fmaxf(x, __uint_as_float(dpp_u32<0xB1>(__float_as_uint(x))));
+  x = fmaxf(x, __uint_as_float(dpp_u32<0x4E>(__float_as_uint(x))));
+  x = fmaxf(x, __uint_as_float(dpp_u32<0x141>(__float_as_uint(x))));
+  x = fmaxf(x, __uint_as_float(dpp_u32<0x140>(__float_as_uint(x))));
+  return fmaxf(fmaxf(lane_f32(x, 0), lane_f32(x, 16)), fmaxf(lane_f32(x, 32), lane_f32(x, 48)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint64_t lo = dpp_u32<CTRL>(static_cast<uint32_t>(u)), hi = dpp_u32<CTRL>(static_cast<uint32_t>(u >> 32));
+  return __builtin_bit_cast(double, (hi << 32) | lo);
+}
+__device__ __forceinline__ double lane_f64(double x, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(u)), lane));
+  const uint64_t hi =
+      static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(u >> 32)), lane));
+  return __builtin_bit_cast(double, (hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum_f64(double x) {
+  x += dpp_f64<0xB1>(x);
+  x += dpp_f64<0x4E>(x);
+  x += dpp_f64<0x141>(x);
+  x += dpp_f64<0x140>(x);
+  return (lane_f64(x, 0) + lane_f64(x, 16)) + (lane_f64(x, 32) + lane_f64(x, 48));
+}
+
 }  // namespace memattn

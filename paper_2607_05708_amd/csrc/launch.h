@@ -63,7 +63,7 @@ constexpr int64_t kOrderSampleFloor = 1024;  // fewest sampled rows of a relatio
 // a tile, so a split keeps tile_rows / 128 partials while the kernel runs.
 constexpr int kSelectRows = 4096;  // scores per step of the general path's select kernel
 constexpr int64_t kSelectOneSplit = 16384;  // banks of at most so many rows take one split per query there
-constexpr size_t kScoreBlock = size_t{64} << 20;  // most bytes of scores it holds at a time
+constexpr size_t kScoreBlock = size_t{96} << 20;  // most bytes of scores it holds at a time
 constexpr int kMaxK = 64;
 constexpr int kMaxD = 8192;
 

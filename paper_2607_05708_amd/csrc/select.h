@@ -10,8 +10,8 @@ namespace memattn {
 namespace {
 
 constexpr int kSelThreads = 256;
-constexpr int kSelPer = 16;                          // keys per thread and step
-constexpr int kSelStep = kSelThreads * kSelPer;      // keys per step
+constexpr int kSelPer = 16;                          // most keys per thread and step
+constexpr int kSelStep = kSelThreads * kSelPer;      // and keys per step
 constexpr int kSelCand = kMaxK * kSelPer;            // most candidates of a step
 constexpr int kSelDirect = 160;                      // up to so many are ranked without a better bound
 
@@ -27,14 +27,14 @@ struct SelectLds {
   double red_s[4];
 };
 
-// Counts, over the workgroup, the in(j), j < kSelPer, of every thread (only
+// Counts, over the workgroup, the in(j), j < PER, of every thread (only
 // those with `any` have one); every wave's own count stays in wcount.
-template <class In>
+template <int PER, class In>
 __device__ __forceinline__ int select_count(SelectLds& L, const In& in, bool any) {
   int mine = 0;
   if (__ballot(any) != 0) {
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) mine += __builtin_popcountll(__ballot(in(j)));
+    for (int j = 0; j < PER; ++j) mine += __builtin_popcountll(__ballot(in(j)));
   }
   if ((threadIdx.x & 63) == 0) L.wcount[threadIdx.x >> 6] = mine;
   __syncthreads();
@@ -54,7 +54,7 @@ __device__ __forceinline__ int count_above(const SelectLds& L, int total, uint64
   return r;
 }
 
-// Offers a step's keys to the list: key(j), j < kSelPer, are this thread's
+// Offers a step's keys to the list: key(j), j < PER, are this thread's
 // (0 = none; all keys distinct), hi(j) their upper halves and top the largest
 // of those.  Only keys above the list's k-th matter; with RISING (every key is
 // of a later row than the list's) those with a larger upper half.  If many are
@@ -70,7 +70,7 @@ __device__ __forceinline__ int count_above(const SelectLds& L, int total, uint64
 // A step without candidates costs one barrier and touches no key; every
 // thread of the workgroup calls it, in every step.
 constexpr int kBoundBits = 22;  // (the rest, 2^-13 of a score, lets few more in)
-template <bool RISING, class Hi, class Key>
+template <bool RISING, int PER, class Hi, class Key>
 __device__ __forceinline__ int select_step(SelectLds& L, const Hi& hi, const Key& key, uint32_t top, int k, int cur) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -82,7 +82,7 @@ __device__ __forceinline__ int select_step(SelectLds& L, const Hi& hi, const Key
   int total = 0;
   if (last != 0) {
     if (!__syncthreads_or(top >= least)) return cur;
-    total = select_count(L, above, top >= least);
+    total = select_count<PER>(L, above, top >= least);
   }
   bool whole = false;  // the bound is a whole key
   uint64_t least64 = 0;
@@ -106,13 +106,13 @@ __device__ __forceinline__ int select_step(SelectLds& L, const Hi& hi, const Key
     __syncthreads();
     const uint32_t t = static_cast<uint32_t>(L.thr);
     least = t > least ? t : least;
-    total = select_count(L, above, top >= least);
+    total = select_count<PER>(L, above, top >= least);
     if (total > kSelCand) {
       // (more than kSelCand: over k threads hold a candidate, so the k-th
       // largest of their largest keys is one thread's)
       uint64_t best = 0;
 #pragma unroll
-      for (int j = 0; j < kSelPer; ++j) {
+      for (int j = 0; j < PER; ++j) {
         const uint64_t x = key(j);
         best = x > best ? x : best;
       }
@@ -122,14 +122,14 @@ __device__ __forceinline__ int select_step(SelectLds& L, const Hi& hi, const Key
       __syncthreads();
       least64 = L.thr;
       whole = true;
-      total = select_count(L, [&](int j) { return key(j) >= least64; }, true);
+      total = select_count<PER>(L, [&](int j) { return key(j) >= least64; }, true);
     }
   }
   int at = 0;
   for (int w = 0; w < wave; ++w) at += L.wcount[w];
   if (L.wcount[wave] != 0) {
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
       const bool in = whole ? key(j) >= least64 : above(j);
       const uint64_t bal = __ballot(in);
       if (in) L.cand[at + __popcll(bal & ((uint64_t{1} << lane) - 1))] = key(j);
@@ -171,13 +171,11 @@ struct SoftmaxSum {
 __device__ __forceinline__ SoftmaxSum block_softmax(SelectLds& L, float m_run, double s_run) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  float m_w = m_run;
-  for (int off = 32; off > 0; off >>= 1) m_w = fmaxf(m_w, __shfl_xor(m_w, off));
+  const float m_w = wave_max_f32(m_run);
   if (lane == 0) L.red_m[wave] = m_w;
   __syncthreads();
   const float m_all = fmaxf(fmaxf(L.red_m[0], L.red_m[1]), fmaxf(L.red_m[2], L.red_m[3]));
-  double s_w = (m_run == -INFINITY) ? 0.0 : s_run * static_cast<double>(fast_exp2(m_run - m_all));
-  for (int off = 32; off > 0; off >>= 1) s_w += __shfl_xor(s_w, off);
+  const double s_w = wave_sum_f64((m_run == -INFINITY) ? 0.0 : s_run * static_cast<double>(fast_exp2(m_run - m_all)));
   if (lane == 0) L.red_s[wave] = s_w;
   __syncthreads();
   return SoftmaxSum{m_all, (L.red_s[0] + L.red_s[1]) + (L.red_s[2] + L.red_s[3])};

@@ -7,7 +7,7 @@
 // (fp32 inputs on the fp32 MFMA, bf16 inputs on the bf16 MFMA, fp32
 // accumulation) and writes a block of scores [queries, rows]; a select kernel
 // folds each query's scores into its softmax state and sorted top-k list.
-// The block is at most 64 MiB (kScoreBlock), so that it stays in the last
+// The block is at most 96 MiB (kScoreBlock), so that it stays in the last
 // level cache between the two, and larger problems run block by block, the
 // select kernel resuming each list.  Where a query has one split, its last
 // select writes the final results (and its full probability row), else the
@@ -15,11 +15,11 @@
 //
 // A thread-per-row fp32 kernel did this before (3.8 TFLOP/s whatever the
 // type, every query re-reading the bank).  64 fp32 queries against 65,536 x
-// 768 rows, k = 16: 1,706 -> 79 us (scores 66 us, 98 TFLOP/s; select 12 us);
-// 200 bf16 queries against 100,003 x 1024, k = 64: 12.2 -> 0.16 ms (scores 95
-// us, 430 TFLOP/s, bound by the 8 TB/s that the 128 x 128 tiles draw from L2;
-// select 59 us); 16 fp32 queries against 1,024 x 256 with full probabilities:
-// 20.9 -> 15.5 us.
+// 768 rows, k = 16: 1,706 -> 75 us (scores 66 us, 98 TFLOP/s); 200 bf16
+// queries against 100,003 x 1024, k = 64: 12.2 -> 0.136 ms (430 TFLOP/s, bound
+// by the 8 TB/s that the 128 x 128 tiles draw from L2); 16 fp32 queries against
+// 1,024 x 256 with full probabilities: 20.9 -> 11.3 us, half of it the launches
+// and the caller's own time.
 //
 // Dense-only relevance of the paper's Section 5.5 applied to LLMSelect of
 // Algorithm 1.
@@ -345,16 +345,17 @@ struct SelectArgs {
 // Folds a step's scores into the thread's softmax state (-inf adds nothing)
 // and returns the largest order key among them; bit j of `out`: value j is no
 // candidate.
-__device__ __forceinline__ uint32_t fold_step(const float (&v)[kSelPer], uint32_t out, float c2, float& m_run,
+template <int PER>
+__device__ __forceinline__ uint32_t fold_step(const float (&v)[PER], uint32_t out, float c2, float& m_run,
                                               double& s_run) {
   float best = v[0];
 #pragma unroll
-  for (int j = 1; j < kSelPer; ++j) best = fmaxf(best, v[j]);
+  for (int j = 1; j < PER; ++j) best = fmaxf(best, v[j]);
   const float mx = fmaxf(m_run, best * c2);
   double part = 0.0;
   if (mx != -INFINITY) {
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) part += static_cast<double>(fast_exp2(v[j] * c2 - mx));
+    for (int j = 0; j < PER; ++j) part += static_cast<double>(fast_exp2(v[j] * c2 - mx));
     s_run = s_run * static_cast<double>(fast_exp2(m_run - mx)) + part;
     m_run = mx;
   }
@@ -364,7 +365,7 @@ __device__ __forceinline__ uint32_t fold_step(const float (&v)[kSelPer], uint32_
   if (out != 0 || !(best > -INFINITY) || !(part < INFINITY)) {
     top = 0;
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) top = max(top, ((out >> j) & 1u) ? 0u : f2ord(v[j]));
+    for (int j = 0; j < PER; ++j) top = max(top, ((out >> j) & 1u) ? 0u : f2ord(v[j]));
   }
   return top;
 }
@@ -372,8 +373,12 @@ __device__ __forceinline__ uint32_t fold_step(const float (&v)[kSelPer], uint32_
 // One workgroup per (query, split): the split's scores of this block, 4,096
 // a step.  A split that an earlier block began resumes from its list and
 // softmax state (the sum in two floats, so that nothing of the double is
-// lost between blocks).
+// lost between blocks).  PER: scores per thread and step, 16 but for banks of
+// at most 1,024 (4) or 2,048 rows (8), whose one step has no more (16 queries
+// x 1,024 rows: 9.7 -> 6.7 us, the reductions by DPP included).
+template <int PER>
 __global__ __launch_bounds__(kSelThreads, 4) void select_kernel(SelectArgs a) {
+  constexpr int kStep = kSelThreads * PER;
   __shared__ SelectLds L;
   const int tid = threadIdx.x;
   const int64_t ql = blockIdx.x / a.block_splits;
@@ -401,26 +406,26 @@ __global__ __launch_bounds__(kSelThreads, 4) void select_kernel(SelectArgs a) {
   // 16-byte loads where the rows allow it
   const bool vec = (reinterpret_cast<uintptr_t>(a.scores) % 16 | a.ld % 4 | (row0 - a.c0) % 4) == 0;
   auto at = [&](int j) { return 1024 * (j >> 2) + 4 * tid + (j & 3); };
-  float v[kSelPer];  // a step's scores, -inf where no candidate
+  float v[PER];  // a step's scores, -inf where no candidate
   uint32_t out = 0;  // bit j: value j is no candidate
-  for (int64_t base = row0; base < row1; base += kSelStep) {
-    const int left = static_cast<int>(min(row1 - base, static_cast<int64_t>(kSelStep)));
+  for (int64_t base = row0; base < row1; base += kStep) {
+    const int left = static_cast<int>(min(row1 - base, static_cast<int64_t>(kStep)));
     float* src = row + (base - a.c0);
-    if (vec && left == kSelStep) {
+    if (vec && left == kStep) {
 #pragma unroll
-      for (int j = 0; j < kSelPer; j += 4) {
+      for (int j = 0; j < PER; j += 4) {
         const f32x4 x = *reinterpret_cast<const f32x4*>(src + at(j));
         v[j] = x.x, v[j + 1] = x.y, v[j + 2] = x.z, v[j + 3] = x.w;
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < kSelPer; ++j) v[j] = at(j) < left ? src[at(j)] : -INFINITY;
+      for (int j = 0; j < PER; ++j) v[j] = at(j) < left ? src[at(j)] : -INFINITY;
     }
     out = 0;
-    if (left < kSelStep || a.row_ns || (self_row >= base && self_row < base + left)) {  // (uniform)
+    if (left < kStep || a.row_ns || (self_row >= base && self_row < base + left)) {  // (uniform)
       const int64_t self = self_row - base;
 #pragma unroll
-      for (int j = 0; j < kSelPer; ++j) {
+      for (int j = 0; j < PER; ++j) {
         const int e = at(j);
         bool cand = e < left && e != self;
         if (a.row_ns && cand) cand = my_ns >= 0 && a.row_ns[base + e] == my_ns;
@@ -435,7 +440,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void select_kernel(SelectArgs a) {
     auto hi = [&](int j) { return ((out >> j) & 1u) ? 0u : f2ord(v[j]); };
     const uint32_t low = 0xFFFFFFFFu - static_cast<uint32_t>(base) - 4 * tid;
     const uint32_t top = fold_step(v, out, a.c2, m_run, s_run);
-    cur = select_step<true>(
+    cur = select_step<true, PER>(
         L, hi,
         [&](int j) {
           const uint32_t h = hi(j);
@@ -459,33 +464,33 @@ __global__ __launch_bounds__(kSelThreads, 4) void select_kernel(SelectArgs a) {
   if (tid == 0 && a.lse) a.lse[q] = lse2 * kLn2;
   if (!a.full) return;
   const bool none = lse2 == -INFINITY;
-  const bool one = row1 - row0 <= kSelStep;  // the only step's scores are still here
-  for (int64_t base = row0; base < row1; base += kSelStep) {
-    const int left = static_cast<int>(min(row1 - base, static_cast<int64_t>(kSelStep)));
+  const bool one = row1 - row0 <= kStep;  // the only step's scores are still here
+  for (int64_t base = row0; base < row1; base += kStep) {
+    const int left = static_cast<int>(min(row1 - base, static_cast<int64_t>(kStep)));
     float* src = row + (base - a.c0);
-    const bool wide = vec && left == kSelStep;
+    const bool wide = vec && left == kStep;
     if (!one) {
       // (the writes of -inf above were this thread's own)
       if (wide) {
 #pragma unroll
-        for (int j = 0; j < kSelPer; j += 4) {
+        for (int j = 0; j < PER; j += 4) {
           const f32x4 x = *reinterpret_cast<const f32x4*>(src + at(j));
           v[j] = x.x, v[j + 1] = x.y, v[j + 2] = x.z, v[j + 3] = x.w;
         }
       } else {
 #pragma unroll
-        for (int j = 0; j < kSelPer; ++j) v[j] = at(j) < left ? src[at(j)] : 0.f;
+        for (int j = 0; j < PER; ++j) v[j] = at(j) < left ? src[at(j)] : 0.f;
       }
     }
 #pragma unroll
-    for (int j = 0; j < kSelPer; ++j) v[j] = none ? 0.f : fast_exp2(v[j] * a.c2 - lse2);
+    for (int j = 0; j < PER; ++j) v[j] = none ? 0.f : fast_exp2(v[j] * a.c2 - lse2);
     if (wide) {
 #pragma unroll
-      for (int j = 0; j < kSelPer; j += 4)
+      for (int j = 0; j < PER; j += 4)
         *reinterpret_cast<f32x4*>(src + at(j)) = f32x4{v[j], v[j + 1], v[j + 2], v[j + 3]};
     } else {
 #pragma unroll
-      for (int j = 0; j < kSelPer; ++j)
+      for (int j = 0; j < PER; ++j)
         if (at(j) < left) src[at(j)] = v[j];
     }
   }
@@ -691,7 +696,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void select_tables_kernel(TableArgs
       const uint32_t top = fold_step(v, out, a.c2, m_run, s_run);
       auto hi = [&](int j) { return ((out >> j) & 1u) ? 0u : f2ord(v[j]); };
       // (ids ascend within a table)
-      cur = select_step<true>(
+      cur = select_step<true, kSelPer>(
           L, hi,
           [&](int j) {
             const uint32_t h = hi(j);
@@ -804,7 +809,13 @@ hipError_t launch_topk_score(const Plan& p, const void* bank, int64_t bank_strid
         a.prob = prob;
         a.lse = lse;
       }
-      select_kernel<<<dim3(static_cast<unsigned>(nq * a.block_splits)), kSelThreads, 0, stream>>>(a);
+      const dim3 grid(static_cast<unsigned>(nq * a.block_splits));
+      if (n <= 1024)
+        select_kernel<4><<<grid, kSelThreads, 0, stream>>>(a);
+      else if (n <= 2048)
+        select_kernel<8><<<grid, kSelThreads, 0, stream>>>(a);
+      else
+        select_kernel<16><<<grid, kSelThreads, 0, stream>>>(a);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

@@ -14,10 +14,9 @@ namespace {
 // the scaled log2 domain (max, then the rescaled sum in fp64).
 __device__ __forceinline__ float wave_lse2(const float2* __restrict__ ms, int n_parts, int lane) {
   const float2 v = lane < n_parts ? ms[lane] : make_float2(-INFINITY, 0.f);
-  float m = v.x;
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  double s = v.x != -INFINITY ? static_cast<double>(v.y) * static_cast<double>(fast_exp2(v.x - m)) : 0.0;
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  const float m = wave_max_f32(v.x);
+  const double s =
+      wave_sum_f64(v.x != -INFINITY ? static_cast<double>(v.y) * static_cast<double>(fast_exp2(v.x - m)) : 0.0);
   return m + static_cast<float>(log2(s));
 }
 
@@ -151,7 +150,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_merge_select_kernel(
     uint32_t top = 0;
 #pragma unroll
     for (int j = 0; j < kSelPer; ++j) top = max(top, static_cast<uint32_t>(x[j] >> 32));
-    cur = select_step<false>(
+    cur = select_step<false, kSelPer>(
         L, [&](int j) { return static_cast<uint32_t>(x[j] >> 32); }, [&](int j) { return x[j]; }, top, k, cur);
   }
   const SoftmaxSum all = block_softmax(L, m_run, s_run);

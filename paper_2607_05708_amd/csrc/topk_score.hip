@@ -108,8 +108,19 @@ struct ScoreArgs {
 // against 902 us), both at about 2.1 GHz with the matrix cores 80-86 % busy;
 // tiles of other sizes and more waves per SIMD change nothing.
 constexpr int kStageBytes = 128;
+// STREAM: bank rows, 16-byte aligned, are loaded non-temporally (a stage takes
+// whole lines, which no other workgroup reads).  It pays for tiles of 32
+// queries over long rows of a bank that the last level cache cannot hold: one
+// query over 1M x 1024 rows 367 -> 350 us, 1,024 over 256 tables of them 474 ->
+// 463 us; shorter rows lose (1M x 256: 233 -> 245 us), and so do 400 MB banks,
+// parts of which stay cached from call to call (193 -> 224 us).
+constexpr int64_t kStreamRowBytes = 1536;
+constexpr int64_t kStreamBankBytes = int64_t{1} << 30;
+bool streams(int64_t rows, int64_t row_bytes) {
+  return row_bytes >= kStreamRowBytes && rows * row_bytes >= kStreamBankBytes;
+}
 
-template <typename T, int QB, int QW, int RB, int RW>
+template <typename T, int QB, int QW, int RB, int RW, bool STREAM = false>
 struct ScoreTile {
   static_assert(QW * RW == 4, "four waves");
   static constexpr int kTileQ = 32 * QB * QW;
@@ -134,7 +145,14 @@ struct ScoreTile {
     auto load = [&](int s, u32x4 (&v)[kLoads]) {
       const int k = s * KE + c * E;
 #pragma unroll
-      for (int i = 0; i < kLoads; ++i) v[i] = load16_within<T>(src[i], k, d);
+      for (int i = 0; i < kRowLoads; ++i) {
+        if constexpr (STREAM)
+          v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src[i] + min(k, d - E)));
+        else
+          v[i] = load16_within<T>(src[i], k, d);
+      }
+#pragma unroll
+      for (int i = kRowLoads; i < kLoads; ++i) v[i] = load16_within<T>(src[i], k, d);
     };
     const int wr = c ^ ((tid >> 4) & 7);  // (32 rows on, the swizzle is the same)
     // (the last stage's tail is mended in LDS: a use of the registers there
@@ -210,9 +228,9 @@ struct ScoreTile {
   }
 };
 
-template <typename T, int QB, int QW, int RB, int RW>
+template <typename T, int QB, int QW, int RB, int RW, bool STREAM>
 __global__ __launch_bounds__(256) void score_tile_kernel(ScoreArgs a) {
-  using S = ScoreTile<T, QB, QW, RB, RW>;
+  using S = ScoreTile<T, QB, QW, RB, RW, STREAM>;
   __shared__ u32x4 st[2][S::kLines * 8];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -606,8 +624,9 @@ __device__ __forceinline__ int find_last(const I* off, int n, I x) {
   return __builtin_amdgcn_readfirstlane(64 * hi + __builtin_popcountll(__ballot(b <= x)) - 1);
 }
 
+template <bool STREAM>
 __global__ __launch_bounds__(256) void score_tables_kernel(TableArgs a) {
-  using S = ScoreTile<uint16_t, 1, 1, 1, 4>;
+  using S = ScoreTile<uint16_t, 1, 1, 1, 4, STREAM>;
   __shared__ u32x4 st[2][S::kLines * 8];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -723,12 +742,12 @@ bool small_scores(int64_t m, int64_t n, int64_t row_bytes) {
   return (n + 127) / 128 * ((m + tq - 1) / tq) < 256;
 }
 
-template <typename T, int QB, int QW, int RB, int RW>
+template <typename T, int QB, int QW, int RB, int RW, bool STREAM = false>
 void launch_tiles(const ScoreArgs& a, hipStream_t stream) {
   const int64_t row_tiles = (a.rows + 32 * RB * RW - 1) / (32 * RB * RW);
   const int64_t q_tiles = (a.nq + 32 * QB * QW - 1) / (32 * QB * QW);
   const dim3 grid(static_cast<unsigned>((row_tiles + 7) / 8 * 8 * q_tiles));
-  score_tile_kernel<T, QB, QW, RB, RW><<<grid, 256, 0, stream>>>(a);
+  score_tile_kernel<T, QB, QW, RB, RW, STREAM><<<grid, 256, 0, stream>>>(a);
 }
 
 template <typename T>
@@ -738,7 +757,12 @@ hipError_t launch_score(const ScoreArgs& a, bool small, hipStream_t stream) {
     const int64_t wgs = (a.rows + 31) / 32 * ((a.nq + 31) / 32);
     score_small_kernel<T><<<dim3(static_cast<unsigned>(wgs)), 256, 0, stream>>>(a);
   } else if (tq == 32) {
-    launch_tiles<T, 1, 1, 1, 4>(a, stream);
+    const uintptr_t place = reinterpret_cast<uintptr_t>(a.bank) | static_cast<uintptr_t>(a.bank_stride * sizeof(T)) |
+                            static_cast<uintptr_t>(a.d * sizeof(T));
+    if (a.nq <= 32 && place % 16 == 0 && streams(a.rows, a.d * sizeof(T)))
+      launch_tiles<T, 1, 1, 1, 4, true>(a, stream);
+    else
+      launch_tiles<T, 1, 1, 1, 4>(a, stream);
   } else if (tq == 64) {
     launch_tiles<T, 2, 1, 1, 4>(a, stream);
   } else {
@@ -751,7 +775,11 @@ hipError_t launch_score(const ScoreArgs& a, bool small, hipStream_t stream) {
 
 hipError_t launch_topk_tables(const TableArgs& a, hipStream_t stream) {
   table_plan_kernel<<<1, kTablePlanThreads, 0, stream>>>(a);
-  score_tables_kernel<<<1024, 256, 0, stream>>>(a);  // four workgroups per CU, each taking every 1,024th tile
+  // four workgroups per CU, each taking every 1,024th tile
+  if (streams(a.n, a.d * 2))
+    score_tables_kernel<true><<<1024, 256, 0, stream>>>(a);
+  else
+    score_tables_kernel<false><<<1024, 256, 0, stream>>>(a);
   select_tables_kernel<<<dim3(static_cast<unsigned>(a.m)), kSelThreads, 0, stream>>>(a);
   return hipGetLastError();
 }

@@ -155,3 +155,20 @@ def test_both_sides_of_the_path_rule_for_relations(n, k):
     g = host(pm.mem_build_relations(up(b), k, 1.0, True))
     rows = pick(n, most=24)
     check_topk(f"rule-rel-{n}", b, b, rows, {key: v[rows] for key, v in g.items()}, k, 1.0, self_idx=np.arange(n))
+
+
+@pytest.mark.parametrize("d,k", [(776, 40), (800, 8)])
+def test_long_rows_of_a_large_bank(d, k):
+    # over 1 GiB of rows of 1.5 KiB or more: loaded non-temporally, the last stage not a whole one
+    n, m = 700001, 3
+    g = torch.Generator(device="cuda").manual_seed(97)
+    b = torch.nn.functional.normalize(torch.randn((n, d), generator=g, device="cuda"), dim=1).bfloat16()
+    q = torch.nn.functional.normalize(torch.randn((m, d), generator=g, device="cuda"), dim=1).bfloat16()
+    idx, score, prob, lse = pm.mem_retrieve_topk(b, q, k, 1.0)
+    s = torch.cat([q.double() @ part.double().T for part in b.split(100000)], 1)
+    eps = 2.0 * d * 2.0 ** -24 * 1.02  # norms after rounding to bf16
+    best = torch.topk(s, k, 1).values
+    assert (score.double() - best).abs().max() <= eps
+    assert (torch.gather(s, 1, idx.long()) - score.double()).abs().max() <= eps
+    assert all(len(set(row)) == k for row in idx.tolist())
+    assert (lse.double() - torch.logsumexp(s, 1)).abs().max() <= eps + 1e-5 * 14

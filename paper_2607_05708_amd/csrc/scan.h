@@ -1,7 +1,7 @@
 // Device exclusive scan (three launches: per-workgroup sums, one workgroup
-// scanning those sums, per-workgroup scans plus offsets) and a fill kernel,
-// shared by the kernels that lay out variable-sized work on the device.
-// Internal to the library.
+// scanning those sums, per-workgroup scans plus offsets), shared by the
+// kernels that lay out variable-sized work on the device.  Internal to the
+// library.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -13,11 +13,6 @@ namespace {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 4;
 constexpr int kScanBlock = kScanThreads * kScanItems;  // elements per scan workgroup
-
-__global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i < n) p[i] = v;
-}
 
 // Exclusive scan of the 1024 values of workgroup `blk` (v[j] for thread t =
 // element blk*1024 + t*4 + j); returns this thread's exclusive prefix and

@@ -1421,6 +1421,11 @@ __global__ __launch_bounds__(256) void band_bound_kernel(const uint16_t* __restr
   if (part == 0 && kp < m && t >= 0x0080u) t0[q] = fmaxf(t0[q], ord2f(t << 16));
 }
 
+__global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i < n) p[i] = v;
+}
+
 // Grouped selection, preparation.  Queries are counted per namespace,
 // their offsets and the work items per namespace (64-query tiles x S splits)
 // come from two scans, and the queries are scattered to grouped positions

@@ -165,3 +165,16 @@ def test_colocate_benchmark_geometry_device_pool(dev):
     torch.cuda.synchronize()
     exp = oracle.expected_blocks(key, sample.astype(np.int32), oracle.ORDER_RANK, 1, ppc, page)
     assert np.array_equal(out.cpu().numpy().view(np.uint64).reshape(exp.shape), exp)
+
+
+@pytest.mark.parametrize("m", [1, 1024, 1025, 4096, 4097])
+def test_colocate_scan_edges(dev, m):
+    # the keys' scan by one workgroup (up to 4,096, 1,024 at a time) and by three launches
+    say(f"case: relocation with {m} keys")
+    g = np.random.default_rng(m)
+    n, k = 3000, 4
+    table = np.arange(2 * n, dtype=np.int32).reshape(n, 2)
+    pool = g.integers(0, 256, size=(4 * n + 64, 64), dtype=np.uint8)
+    ids = g.integers(0, n, size=(m, k)).astype(np.int32)
+    sc = g.uniform(0.2, 1.0, size=(m, k)).astype(np.float32)
+    run_both(pool, table, ids, sc, 0.6, 2, 2 * n)

@@ -159,3 +159,17 @@ def test_compact_rejects_malformed_tables(dev, flaw):
         pm.mem_compact_blocks(gp, gt, up(offsets), up(chunks), P, 0.3, nf)
     torch.cuda.synchronize()
     assert np.array_equal(gt.cpu().numpy(), table) and np.array_equal(gp.cpu().numpy(), pool)
+
+
+@pytest.mark.parametrize("n_ns", [1, 1024, 1025, 4096, 4097])
+def test_compact_scan_edges(dev, n_ns):
+    # the namespaces' scan by one workgroup (up to 4,096, 1,024 at a time) and by three launches
+    say(f"case: compaction with {n_ns} namespaces")
+    P, ppc = 8, 2
+    table, nf = inputs.compaction_layout(n_ns, TAG_COMPACT, 300, P, ppc)
+    rns = np.random.default_rng(n_ns).integers(0, n_ns, size=table.shape[0]).astype(np.int32)
+    rns[-1] = n_ns - 1
+    offsets, chunks = inputs.chunk_tables(rns)
+    n_pages = 300 * P + min(n_ns, table.shape[0]) * P + table.size
+    pool = np.random.default_rng(1).integers(0, 256, size=(n_pages, 64), dtype=np.uint8)
+    check(*run_both(pool, table, offsets, chunks, P, 0.3, nf))

@@ -122,7 +122,7 @@ mem_status select_topk(const mem_bank* bank, const void* queries, int64_t m, int
   const bool relation = queries == bank->emb && q_stride == bank->row_stride && m == bank->n;
   // (a scoped relation build keeps the bank order, so its sample as well)
   const Plan p = make_plan(m, bank->n, bank->d, k, bank->dtype, mfma_ok, relation && scope.row_ns == nullptr,
-                           use_scratch ? kScratchBytes : SIZE_MAX);
+                           scope.row_ns != nullptr, use_scratch ? kScratchBytes : SIZE_MAX);
   if (static_cast<int64_t>(p.n_splits) * (p.mfma ? p.q_tiles : m) > INT32_MAX)
     return fail(MEM_ERR_UNSUPPORTED, "problem too large for one launch");
   if (m > INT32_MAX) return fail(MEM_ERR_UNSUPPORTED, "m too large");
@@ -243,7 +243,8 @@ Plan make_scope_plan(int64_t m, int64_t n, int32_t k) {
   return grouped_plan(m, k, kScopeMaxSplits, k > 16 || (k > 8 && n >= 256 * 4 * 512));
 }
 
-Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, size_t limit) {
+Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, bool scoped,
+               size_t limit) {
   Plan p{};
   // The workspace is sized for the most splits any bank of at most n rows
   // can get (min(tiles, split target)), so that the size never decreases
@@ -357,11 +358,16 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
   // k = 32 74/63 and 191/158, k = 5 48/58 and 161/154; 64 x 131,072, k = 5
   // 39/42 and 91/80; 512 x 65,536, k = 32 88/110 and 151/167.  Without a
   // threshold sample the fused pass starts from empty lists (1,024 x 32,768,
-  // k = 32: 410/111 and 442/165), and a small relation build has its key
-  // order to pay (4,000 keys, k = 5 121/64; 8,000 keys 180/235).
+  // k = 32: 410/111 and 442/165), except where it scores few of the pairs:
+  // a scoped call skips tiles by namespace (1,000 x 30,000, k = 22, mixed
+  // rows of 128 namespaces, d = 96 and 1,024: 84/144 and 133/194), and a
+  // relation build of more than 4,096 keys gains from the fused pass as the
+  // general one's select takes two steps (5,400 keys, k = 5, d = 768
+  // 116/235; 4,000 keys 121/64).
   if (p.mfma) {
-    const int64_t most = (p.ns == 0 || relation) ? int64_t{1} << 25 : (p.kcap > 8 ? int64_t{1} << 24 : int64_t{6} << 20);
-    if (m * n < most) return make_plan(m, n, d, k, dtype, false, relation, limit);
+    int64_t most = p.kcap > 8 || p.ns == 0 ? int64_t{1} << 24 : int64_t{6} << 20;
+    if (p.ns == 0 && !relation && !scoped) most = int64_t{1} << 25;
+    if (m * n < most) return make_plan(m, n, d, k, dtype, false, relation, scoped, limit);
   }
   // The matrix-core kernel keeps one partial per bank part while it runs and
   // leaves one per split (in part 0's slot); the merge reads every

@@ -76,10 +76,11 @@ struct Scope {
 
 // mfma_ok: caller allows the matrix-core path (bf16, d % 32 == 0, k <= 32,
 // no full probability output).  relation: the queries are the bank's own
-// rows (only the sample size depends on it, never the workspace size).
+// rows, scoped: it takes namespaces (the sample size and the path depend on
+// them, never the workspace size).
 // limit: the workspace at hand; the general path scores smaller blocks to fit.
 Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation = false,
-               size_t limit = SIZE_MAX);
+               bool scoped = false, size_t limit = SIZE_MAX);
 // Grouped selection over per-namespace chunk tables: the narrow matrix-core
 // shape, S splits per namespace (S from the mean table size), no sample.
 Plan make_grouped_plan(int64_t m, int32_t n_ns, int64_t n_entries, int32_t k);

@@ -114,7 +114,9 @@ typedef struct {
  * capacity serves it as it grows; 0 on invalid sizes.  The workspace holds per-split partial
  * top-k lists and softmax partial sums (and, for m >= 4,096 bf16 queries, a
  * reordered copy of the queries: a relation build scores them grouped by
- * region of the bank) and is fully rewritten by each call;
+ * region of the bank; for the calls that the general path takes, a block of
+ * scores of at most 96 MiB; for large scoped retrievals, chunk tables) and is
+ * fully rewritten by each call;
  * calls that share a workspace must not overlap (enqueue them on one stream).
  */
 MEMATTN_API size_t mem_workspace_bytes(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype);
@@ -146,7 +148,8 @@ MEMATTN_API mem_status mem_retrieve_topk(const mem_bank* bank, const void* queri
  * (128 MiB) that the library holds in every GPU it runs on until the
  * process ends.  Calls whose workspace (mem_workspace_bytes) exceeds it
  * fail with MEM_ERR_WORKSPACE before anything is enqueued (up to 1,024
- * queries fit at any bank size and k).  The first call on a device
+ * queries fit at any bank size and k; the general path's block of scores
+ * shrinks to what is left of the array).  The first call on a device
  * looks up the array's address there (make that first call outside graph
  * capture); later calls only enqueue kernels.  Every call on one GPU shares
  * that GPU's array, which keeps the last call's contents (the kernels

@@ -360,13 +360,12 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
   // threshold sample the fused pass starts from empty lists (1,024 x 32,768,
   // k = 32: 410/111 and 442/165), except where it scores few of the pairs:
   // a scoped call skips tiles by namespace (1,000 x 30,000, k = 22, mixed
-  // rows of 128 namespaces, d = 96 and 1,024: 84/144 and 133/194), and a
-  // relation build of more than 4,096 keys gains from the fused pass as the
-  // general one's select takes two steps (5,400 keys, k = 5, d = 768
-  // 116/235; 4,000 keys 121/64).
+  // rows of 128 namespaces, d = 96 and 1,024: 84/144 and 133/194).  Relation
+  // builds up to 5,792 keys take the general path: 4,000 keys, k = 5 121/64,
+  // but above 4,096 keys lists of 8 lose there (5,400 keys 116/235).
   if (p.mfma) {
     int64_t most = p.kcap > 8 || p.ns == 0 ? int64_t{1} << 24 : int64_t{6} << 20;
-    if (p.ns == 0 && !relation && !scoped) most = int64_t{1} << 25;
+    if (relation || (p.ns == 0 && !scoped)) most = int64_t{1} << 25;
     if (m * n < most) return make_plan(m, n, d, k, dtype, false, relation, scoped, limit);
   }
   // The matrix-core kernel keeps one partial per bank part while it runs and

@@ -1471,7 +1471,9 @@ __global__ __launch_bounds__(256) void group_scatter_kernel(const int32_t* __res
 // The same preparation in one workgroup for up to kPrepNs namespaces and
 // kPrepM queries (counts and fill positions in LDS): count, both exclusive
 // scans, scatter, empty partials for queries without a namespace and the
-// shared bounds, in one launch instead of nine.
+// shared bounds, in one launch instead of nine.  q_pos (each query's grouped
+// position, -1 = none) has memory of its own or is NULL: only the selection
+// over scored tables reads it.
 constexpr int kPrepNs = 4096;
 constexpr int64_t kPrepM = 16384;
 __global__ __launch_bounds__(256) void group_prep_kernel(const int32_t* __restrict__ key_ns, int64_t m, int n_ns,
@@ -1526,9 +1528,9 @@ __global__ __launch_bounds__(256) void group_prep_kernel(const int32_t* __restri
     if (u >= 0 && u < n_ns) {
       const int32_t at = atomicAdd(&pos[u], 1);
       perm[at] = static_cast<int32_t>(i);
-      q_pos[i] = at;
+      if (q_pos != nullptr) q_pos[i] = at;
     } else {
-      q_pos[i] = -1;
+      if (q_pos != nullptr) q_pos[i] = -1;
       for (int64_t j = 0; j < nl; ++j) part_keys[i * nl + j] = 0;
       for (int s = 0; s < S; ++s) part_ms[i * S + s] = make_float2(-INFINITY, 0.f);
     }
@@ -1657,7 +1659,7 @@ hipError_t launch_topk_grouped(const Plan& p, const GroupLayout& G, const uint16
   auto* flag = reinterpret_cast<int32_t*>(w + G.flag);
   Gate gate;
   if (n_ns <= kPrepNs && m <= kPrepM) {
-    auto* q_pos = reinterpret_cast<int32_t*>(w + (G.tables ? G.q_pos : G.perm));
+    auto* q_pos = G.tables ? reinterpret_cast<int32_t*>(w + G.q_pos) : nullptr;
     group_prep_kernel<<<1, 256, 0, stream>>>(key_ns, m, n_ns, S, q_off, item_off, perm, keys, ms, p.part_stride,
                                              p.kcap, thr, q_pos);
     if (G.tables) {

@@ -125,3 +125,28 @@ def test_grouped_tile_and_step_edges(d, k):
 def test_both_sides_of_the_table_rule(length, queries):
     # 12 * 2^20 scores and tables of 32,768 rows are the most that are scored first and selected from after
     grouped_check([length, 300], [queries, 0], 96, 10, 90 + queries % 7)
+
+
+# (queries, namespaces, rows, d, k): on either side of the size (24 * 2^20 scores of average tables) up to which the
+# tables are given room to be scored first; past it the fused pass alone runs, over queries put in grouped order
+@pytest.mark.parametrize("m,n_ns,n,d,k", [(1024, 16, 393000, 96, 12), (1024, 16, 393400, 96, 12), (300, 2, 180001, 128, 32),
+                                          (250, 8, 810000, 96, 5)])
+def test_grouped_few_long_tables(m, n_ns, n, d, k):
+    print(f"case: grouped m={m} namespaces={n_ns} n={n} d={d} k={k}", flush=True)
+    bt, b = bank_of(120 + n_ns, n, d)
+    qt, q = bank_of(220 + n_ns, m, d)
+    rng = np.random.default_rng(n)
+    rns = rng.integers(0, n_ns, n).astype(np.int32)
+    kns = rng.integers(0, n_ns, m).astype(np.int32)
+    kns[::31] = -1           # no namespace
+    kns[7::53] = n_ns + 5    # one past the tables
+    offsets = np.zeros(n_ns + 1, np.int32)
+    offsets[1:] = np.cumsum(np.bincount(rns, minlength=n_ns))
+    chunks = np.argsort(rns, kind="stable").astype(np.int32)
+    out = pm.mem_retrieve_topk_grouped(bt, up(offsets), up(chunks), qt, up(kns), k, 1.0)
+    g = check(f"few-{n}", b, q, rns, np.ones(n, np.uint8), kns, out, k, n_ns)
+    none = (kns < 0) | (kns >= n_ns)
+    assert np.all(g["idx"][none] == -1) and np.all(g["lse"][none] == -np.inf)
+    # every other query was scored: k distinct rows, all of its own namespace
+    assert np.all(rns[g["idx"][~none]] == kns[~none, None])
+    assert all(len(set(r)) == k for r in g["idx"][~none].tolist())

@@ -108,8 +108,9 @@ typedef struct {
 } mem_pages;
 
 /*
- * Device workspace needed by mem_retrieve_topk (m queries) or
- * mem_build_relations (m = n) for these sizes.  Depends only on the
+ * Device workspace needed by mem_retrieve_topk and mem_retrieve_topk_scoped (m
+ * queries) or mem_build_relations and mem_build_relations_scoped (m = n) for
+ * these sizes, whichever path a call's options lead it to.  Depends only on the
  * arguments and never decreases with n, so a workspace sized for a bank's
  * capacity serves it as it grows; 0 on invalid sizes.  The workspace holds per-split partial
  * top-k lists and softmax partial sums (and, for m >= 4,096 bf16 queries, a

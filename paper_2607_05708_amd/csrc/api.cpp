@@ -243,166 +243,99 @@ Plan make_scope_plan(int64_t m, int64_t n, int32_t k) {
   return grouped_plan(m, k, kScopeMaxSplits, k > 16 || (k > 8 && n >= 256 * 4 * 512));
 }
 
-Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, bool scoped,
-               size_t limit) {
+namespace {
+
+// Whether the fused matrix-core pass can take a call of this shape.
+bool fused_shape(int32_t d, int32_t k, int32_t dtype) { return dtype == MEM_BF16 && d % 32 == 0 && k <= kMfmaMaxK; }
+
+// The fused pass.  Its workspace depends on m, n, d and k alone and never
+// decreases with n: it is sized for the most splits any bank of at most n
+// rows can get (min(tiles, split target)).
+Plan fused_plan(int64_t m, int64_t n, int32_t d, int32_t k, bool relation) {
   Plan p{};
-  // The workspace is sized for the most splits any bank of at most n rows
-  // can get (min(tiles, split target)), so that the size never decreases
-  // with n: a workspace sized for a bank also serves every smaller one.
-  int64_t splits_cap = 1;
-  const bool mfma = mfma_ok && dtype == MEM_BF16 && d % 32 == 0 && k <= kMfmaMaxK;
   // Whether the workspace holds the clustered query order (m and d only).
-  const bool room =
-      mfma && m >= kOrderMinQueries && static_cast<size_t>(m) * static_cast<size_t>(d) * 2 <= kOrderMaxQueryBytes;
-  if (mfma) {
-    p.mfma = true;
-    p.qw = m <= 64 ? 1 : (m <= 128 ? 2 : 4);
-    p.tile_rows = p.qw == 1 ? 512 : 256;
-    p.tile_queries = 64 * p.qw;
-    p.kcap = k <= 8 ? 8 : (k <= 16 ? 16 : 32);
-    p.q_tiles = static_cast<int>(ceil_div(m, p.tile_queries));
-    const int64_t nt = ceil_div(n, p.tile_rows);
-    // One workgroup fills a CU, so the grid runs in rounds of 256.  Of the
-    // split counts up to s_max, take the fewest that minimise rounds x tiles
-    // per split: ceil(256 / q_tiles) splits of a tile count that does not
-    // divide 256 overshoot into a second, nearly empty round (48 query tiles
-    // x 6 splits = 288 workgroups; 5 splits take one round).  With more
-    // than 64 query tiles s_max allows up to four rounds: one split of 157
-    // query tiles leaves 99 CUs idle, three take two full rounds.  s_max
-    // sizes the workspace (it depends on m, and on n only through nt).
-    int64_t s_max = ceil_div(p.q_tiles > 64 ? 1024 : 256, p.q_tiles);
-    s_max = s_max < 1 ? 1 : (s_max > nt ? nt : s_max);
-    splits_cap = s_max;
-    int64_t s = s_max, best = INT64_MAX;
-    for (int64_t c = 1; c <= s_max; ++c) {
-      const int64_t cost = ceil_div(p.q_tiles * c, 256) * ceil_div(nt, c);
-      if (cost < best) {
-        best = cost;
-        s = c;
-      }
+  const bool room = m >= kOrderMinQueries && static_cast<size_t>(m) * static_cast<size_t>(d) * 2 <= kOrderMaxQueryBytes;
+  p.mfma = true;
+  p.qw = m <= 64 ? 1 : (m <= 128 ? 2 : 4);
+  p.tile_rows = p.qw == 1 ? 512 : 256;
+  p.tile_queries = 64 * p.qw;
+  p.kcap = k <= 8 ? 8 : (k <= 16 ? 16 : 32);
+  p.q_tiles = static_cast<int>(ceil_div(m > 0 ? m : 1, p.tile_queries));
+  const int64_t nt = ceil_div(n, p.tile_rows);
+  // One workgroup fills a CU, so the grid runs in rounds of 256.  Of the
+  // split counts up to s_max, take the fewest that minimise rounds x tiles
+  // per split: ceil(256 / q_tiles) splits of a tile count that does not
+  // divide 256 overshoot into a second, nearly empty round (48 query tiles
+  // x 6 splits = 288 workgroups; 5 splits take one round).  With more
+  // than 64 query tiles s_max allows up to four rounds: one split of 157
+  // query tiles leaves 99 CUs idle, three take two full rounds.  s_max
+  // sizes the workspace (it depends on m, and on n only through nt).
+  int64_t s_max = ceil_div(p.q_tiles > 64 ? 1024 : 256, p.q_tiles);
+  s_max = s_max < 1 ? 1 : (s_max > nt ? nt : s_max);
+  int64_t s = s_max, best = INT64_MAX;
+  for (int64_t c = 1; c <= s_max; ++c) {
+    const int64_t cost = ceil_div(p.q_tiles * c, 256) * ceil_div(nt, c);
+    if (cost < best) {
+      best = cost;
+      s = c;
     }
-    const int64_t tps = ceil_div(nt, s);
-    p.tiles_per_split = static_cast<int>(tps);
-    p.n_splits = static_cast<int>(ceil_div(nt, tps));
-    p.rows_per_split = tps * p.tile_rows;
-    // Threshold sample: about n/32 rows per query (4096 to 32768, and never
-    // more than sample_cap(m), which sizes the workspace), taken as whole
-    // tiles at the start of every samp_stride-th split, ns tiles each.  The
-    // sample's k-th best is a lower bound on the query's k-th best.  Skipped
-    // when it would cost more than 1/16 of the bank (small banks: each
-    // partial's own list then tightens its threshold about as fast), or
-    // more than 1/32 with lists of 8, whose merges are cheap.  A relation
-    // build in clustered order takes n/32 rows down to 1,024: its keys'
-    // neighbours bound them as well, and the coarser sample groups them
-    // into fewer, larger clusters (1.8 instead of 2.5 labels per wave on
-    // the 32,768-chunk build, 0.09 ms less).  With lists of 16 or 32 such a
-    // build takes its sample up to a quarter of the bank: the order then
-    // reaches builds of 4,096 to 32,767 keys, which it makes 1.4 to 1.8
-    // times faster (lists of 8 gain nothing from it).
-    {
-      const int64_t floor_rows = (relation && room) ? kOrderSampleFloor : 4096;
-      int64_t target = n / 32;
-      target = target < floor_rows ? floor_rows : (target > 32768 ? 32768 : target);
-      const int64_t cap_tiles = sample_cap(m) / p.tile_rows;
-      int64_t want = ceil_div(target, p.tile_rows);
-      want = want > cap_tiles ? cap_tiles : want;
-      // the sample costs at most 1/max_share of the bank
-      const int64_t max_share = (relation && room && p.kcap > 8) ? 4 : (p.kcap == 8 ? 32 : 16);
-      if (want >= 1 && want * max_share <= nt) {
-        int64_t stride = 1, ns = 1;
-        if (want <= p.n_splits) {
-          stride = p.n_splits / want;
-        } else {
-          ns = want / p.n_splits;
-          ns = ns > tps ? tps : ns;
-        }
-        const int64_t sampled = ceil_div(p.n_splits, stride);
-        if (sampled * ns <= cap_tiles) {
-          p.ns = static_cast<int>(ns);
-          p.samp_stride = static_cast<int>(stride);
-          p.n_samp_splits = static_cast<int>(sampled);
-          p.n_samp = sampled * ns * p.tile_rows;
-        }
-      }
-    }
-  } else {
-    p.mfma = false;
-    p.kcap = pow2_at_least(k);
-    // One workgroup selects for a (query, split), and four fit a CU: of the
-    // split counts up to about 2,048 workgroups, the fewest that minimise
-    // rounds of 1,024 x steps per split.  One split where the bank is small
-    // (the select kernel then writes the final results and no merge follows).
-    // 200 queries x 100,003 rows, k = 64: 5 splits 136 us, 11 144 us.
-    const int64_t nt = ceil_div(n, kSelectRows);
-    int64_t s_max = ceil_div(2048, m > 0 ? m : 1);
-    s_max = s_max > nt ? nt : s_max;
-    splits_cap = s_max;
-    int64_t s = 1, best = INT64_MAX;
-    for (int64_t c = 1; c <= s_max && n > kSelectOneSplit; ++c) {
-      const int64_t cost = ceil_div(m * c, 1024) * ceil_div(nt, c);
-      if (cost < best) {
-        best = cost;
-        s = c;
-      }
-    }
-    p.rows_per_split = ceil_div(nt, s) * kSelectRows;
-    p.n_splits = static_cast<int>(ceil_div(n, p.rows_per_split));
-    p.q_tiles = 0;
-    p.tiles_per_split = 0;
   }
-  // Scoring a block and selecting from it costs 8 bytes of cache traffic and
-  // a few instructions per pair that the fused pass saves, but keeps every
-  // CU busy at any size and has no lists to warm up: it takes the smaller
-  // calls.  Fused / general, us, d = 64 and 1,024: 8 queries x 8,192 rows,
-  // k = 5 46/15 and 68/18; 64 x 65,536, k = 32 56/32 and 95/45; 64 x 262,144,
-  // k = 32 74/63 and 191/158, k = 5 48/58 and 161/154; 64 x 131,072, k = 5
-  // 39/42 and 91/80; 512 x 65,536, k = 32 88/110 and 151/167.  Without a
-  // threshold sample the fused pass starts from empty lists (1,024 x 32,768,
-  // k = 32: 410/111 and 442/165), except where it scores few of the pairs:
-  // a scoped call skips tiles by namespace (1,000 x 30,000, k = 22, mixed
-  // rows of 128 namespaces, d = 96 and 1,024: 84/144 and 133/194).  Relation
-  // builds up to 5,792 keys take the general path: 4,000 keys, k = 5 121/64,
-  // but above 4,096 keys lists of 8 lose there (5,400 keys 116/235).
-  if (p.mfma) {
-    int64_t most = p.kcap > 8 || p.ns == 0 ? int64_t{1} << 24 : int64_t{6} << 20;
-    if (relation || (p.ns == 0 && !scoped)) most = int64_t{1} << 25;
-    if (m * n < most) return make_plan(m, n, d, k, dtype, false, relation, scoped, limit);
+  const int64_t tps = ceil_div(nt, s);
+  p.tiles_per_split = static_cast<int>(tps);
+  p.n_splits = static_cast<int>(ceil_div(nt, tps));
+  p.rows_per_split = tps * p.tile_rows;
+  // Threshold sample: about n/32 rows per query (4096 to 32768, and never
+  // more than sample_cap(m), which sizes the workspace), taken as whole
+  // tiles at the start of every samp_stride-th split, ns tiles each.  The
+  // sample's k-th best is a lower bound on the query's k-th best.  Skipped
+  // when it would cost more than 1/16 of the bank (small banks: each
+  // partial's own list then tightens its threshold about as fast), or
+  // more than 1/32 with lists of 8, whose merges are cheap.  A relation
+  // build in clustered order takes n/32 rows down to 1,024: its keys'
+  // neighbours bound them as well, and the coarser sample groups them
+  // into fewer, larger clusters (1.8 instead of 2.5 labels per wave on
+  // the 32,768-chunk build, 0.09 ms less).  With lists of 16 or 32 such a
+  // build takes its sample up to a quarter of the bank: the order then
+  // reaches builds of 4,096 to 32,767 keys, which it makes 1.4 to 1.8
+  // times faster (lists of 8 gain nothing from it).
+  {
+    const int64_t floor_rows = (relation && room) ? kOrderSampleFloor : 4096;
+    int64_t target = n / 32;
+    target = target < floor_rows ? floor_rows : (target > 32768 ? 32768 : target);
+    const int64_t cap_tiles = sample_cap(m) / p.tile_rows;
+    int64_t want = ceil_div(target, p.tile_rows);
+    want = want > cap_tiles ? cap_tiles : want;
+    // the sample costs at most 1/max_share of the bank
+    const int64_t max_share = (relation && room && p.kcap > 8) ? 4 : (p.kcap == 8 ? 32 : 16);
+    if (want >= 1 && want * max_share <= nt) {
+      int64_t stride = 1, ns = 1;
+      if (want <= p.n_splits) {
+        stride = p.n_splits / want;
+      } else {
+        ns = want / p.n_splits;
+        ns = ns > tps ? tps : ns;
+      }
+      const int64_t sampled = ceil_div(p.n_splits, stride);
+      if (sampled * ns <= cap_tiles) {
+        p.ns = static_cast<int>(ns);
+        p.samp_stride = static_cast<int>(stride);
+        p.n_samp_splits = static_cast<int>(sampled);
+        p.n_samp = sampled * ns * p.tile_rows;
+      }
+    }
   }
   // The matrix-core kernel keeps one partial per bank part while it runs and
   // leaves one per split (in part 0's slot); the merge reads every
   // part_stride-th slot.
   p.n_parts = p.n_splits;
-  p.part_stride = p.mfma ? p.tile_rows / 128 : 1;
-  const size_t slots = static_cast<size_t>(splits_cap > p.n_splits ? splits_cap : p.n_splits) * p.part_stride;
+  p.part_stride = p.tile_rows / 128;
+  const size_t slots = static_cast<size_t>(s_max > p.n_splits ? s_max : p.n_splits) * p.part_stride;
   const size_t mm = static_cast<size_t>(m > 0 ? m : 0);
   p.ws_part_keys = 0;
   p.ws_part_ms = align256(mm * slots * p.kcap * sizeof(uint64_t));
   p.ws_lse2 = p.ws_part_ms + align256(mm * slots * 2 * sizeof(float));
-  if (!p.mfma) {
-    p.ws_part_lo = p.ws_lse2 + align256(mm * sizeof(float));
-    p.ws_scores = p.ws_part_lo + align256(mm * slots * sizeof(float));
-    p.blk_queries = m < 4096 ? (m > 0 ? m : 1) : 4096;
-    const int64_t wide = static_cast<int64_t>(kScoreBlock / sizeof(float)) / p.blk_queries / kSelectRows * kSelectRows;
-    p.blk_rows = ceil_div(n, 32) * 32;
-    if (p.blk_rows > wide) p.blk_rows = wide > kSelectRows ? wide : kSelectRows;
-    const int64_t room = limit > p.ws_scores ? static_cast<int64_t>((limit - p.ws_scores) / sizeof(float)) : 0;
-    if (p.blk_queries * p.blk_rows > room) {
-      if (p.blk_rows > kSelectRows) p.blk_rows = kSelectRows;
-      if (p.blk_queries > room / p.blk_rows) p.blk_queries = room / p.blk_rows;
-      if (p.blk_queries < 1) {
-        p.blk_queries = 1;
-        p.blk_rows = room >= 32 ? room / 32 * 32 : 32;
-      }
-    }
-    p.ws_bytes = p.ws_scores + align256(static_cast<size_t>(p.blk_queries * p.blk_rows) * sizeof(float));
-    // as many blocks, of about the same size (a short last one would leave
-    // most of the GPU idle)
-    const int64_t even = ceil_div(ceil_div(n, ceil_div(n, p.blk_rows)), 128) * 128;
-    if (even < p.blk_rows) p.blk_rows = even;
-    return p;
-  }
   p.ws_samp = p.ws_lse2 + align256(mm * sizeof(float));
-  p.ws_t0 = p.ws_samp + (p.mfma ? align256(mm * static_cast<size_t>(sample_cap(m)) * sizeof(uint16_t)) : 0);
+  p.ws_t0 = p.ws_samp + align256(mm * static_cast<size_t>(sample_cap(m)) * sizeof(uint16_t));
   p.ws_thr = p.ws_t0 + align256(mm * sizeof(float));
   // Two launches per split where a threshold sample is taken and a split
   // spans at least 32 tiles: its first quarter, then the rest, bounded by
@@ -411,9 +344,9 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
   // retrieval the two launches take 0.60 + 1.60 ms against 2.37 ms for one;
   // with shorter splits the extra launch and bound search cost more than
   // the tighter bound saves.
-  p.ph_split = (p.mfma && p.ns > 0 && p.tiles_per_split >= 32) ? p.tiles_per_split / 4 : 0;
+  p.ph_split = (p.ns > 0 && p.tiles_per_split >= 32) ? p.tiles_per_split / 4 : 0;
   p.ws_lane_ms = p.ws_thr + align256(mm * sizeof(uint32_t));
-  size_t o = p.ws_lane_ms + (p.mfma ? align256(mm * slots * sizeof(float) * 2) : 0);
+  size_t o = p.ws_lane_ms + align256(mm * slots * sizeof(float) * 2);
   // Clustered query order (a relation build whose queries are many): each
   // query's best sampled position, the order, and the queries copied in it.
   // The room depends on m and d only, so the size still never decreases
@@ -440,6 +373,102 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
   return p;
 }
 
+// The general path: blocks of scores, as large as `limit` leaves room for.
+// Its workspace depends on m, n, k and the limit alone and never decreases
+// with n.
+Plan general_plan(int64_t m, int64_t n, int32_t k, size_t limit) {
+  Plan p{};
+  p.mfma = false;
+  p.kcap = pow2_at_least(k);
+  // One workgroup selects for a (query, split), and four fit a CU: of the
+  // split counts up to about 2,048 workgroups, the fewest that minimise
+  // rounds of 1,024 x steps per split.  One split where the bank is small
+  // (the select kernel then writes the final results and no merge follows).
+  // 200 queries x 100,003 rows, k = 64: 5 splits 136 us, 11 144 us.
+  const int64_t nt = ceil_div(n, kSelectRows);
+  int64_t s_max = ceil_div(2048, m > 0 ? m : 1);
+  s_max = s_max > nt ? nt : s_max;
+  int64_t s = 1, best = INT64_MAX;
+  for (int64_t c = 1; c <= s_max && n > kSelectOneSplit; ++c) {
+    const int64_t cost = ceil_div(m * c, 1024) * ceil_div(nt, c);
+    if (cost < best) {
+      best = cost;
+      s = c;
+    }
+  }
+  p.rows_per_split = ceil_div(nt, s) * kSelectRows;
+  p.n_splits = static_cast<int>(ceil_div(n, p.rows_per_split));
+  p.n_parts = p.n_splits;
+  p.part_stride = 1;
+  const size_t slots = static_cast<size_t>(s_max > p.n_splits ? s_max : p.n_splits);
+  const size_t mm = static_cast<size_t>(m > 0 ? m : 0);
+  p.ws_part_keys = 0;
+  p.ws_part_ms = align256(mm * slots * p.kcap * sizeof(uint64_t));
+  p.ws_lse2 = p.ws_part_ms + align256(mm * slots * 2 * sizeof(float));
+  p.ws_part_lo = p.ws_lse2 + align256(mm * sizeof(float));
+  p.ws_scores = p.ws_part_lo + align256(mm * slots * sizeof(float));
+  p.blk_queries = m < 4096 ? (m > 0 ? m : 1) : 4096;
+  const int64_t wide = static_cast<int64_t>(kScoreBlock / sizeof(float)) / p.blk_queries / kSelectRows * kSelectRows;
+  p.blk_rows = ceil_div(n, 32) * 32;
+  if (p.blk_rows > wide) p.blk_rows = wide > kSelectRows ? wide : kSelectRows;
+  const int64_t room = limit > p.ws_scores ? static_cast<int64_t>((limit - p.ws_scores) / sizeof(float)) : 0;
+  if (p.blk_queries * p.blk_rows > room) {
+    if (p.blk_rows > kSelectRows) p.blk_rows = kSelectRows;
+    if (p.blk_queries > room / p.blk_rows) p.blk_queries = room / p.blk_rows;
+    if (p.blk_queries < 1) {
+      p.blk_queries = 1;
+      p.blk_rows = room >= 32 ? room / 32 * 32 : 32;
+    }
+  }
+  p.ws_bytes = p.ws_scores + align256(static_cast<size_t>(p.blk_queries * p.blk_rows) * sizeof(float));
+  // as many blocks, of about the same size (a short last one would leave
+  // most of the GPU idle)
+  const int64_t even = ceil_div(ceil_div(n, ceil_div(n, p.blk_rows)), 128) * 128;
+  if (even < p.blk_rows) p.blk_rows = even;
+  return p;
+}
+
+// What the selection calls of these sizes need at most, whichever path their
+// options, namespaces and alignment lead them to.
+size_t plan_bytes(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype) {
+  const size_t general = general_plan(m, n, k, SIZE_MAX).ws_bytes;
+  if (!fused_shape(d, k, dtype)) return general;
+  const size_t fused = fused_plan(m, n, d, k, false).ws_bytes;
+  size_t most = general > fused ? general : fused;
+  // a scoped retrieval's chunk tables (of the largest bank up to n rows that
+  // takes them), which only calls of the fused pass try
+  const int64_t n_fit = m > 0 && n > scope_max_rows(m) ? scope_max_rows(m) : n;
+  if (scope_tables_fit(m, n_fit, d, k)) {
+    const size_t tables = scope_layout(m, n_fit, d, k, fused).end;
+    most = most > tables ? most : tables;
+  }
+  return most;
+}
+
+}  // namespace
+
+Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, bool scoped,
+               size_t limit) {
+  if (!mfma_ok || !fused_shape(d, k, dtype)) return general_plan(m, n, k, limit);
+  const Plan p = fused_plan(m, n, d, k, relation);
+  // Scoring a block and selecting from it costs 8 bytes of cache traffic and
+  // a few instructions per pair that the fused pass saves, but keeps every
+  // CU busy at any size and has no lists to warm up: it takes the smaller
+  // calls.  Fused / general, us, d = 64 and 1,024: 8 queries x 8,192 rows,
+  // k = 5 46/15 and 68/18; 64 x 65,536, k = 32 56/32 and 95/45; 64 x 262,144,
+  // k = 32 74/63 and 191/158, k = 5 48/58 and 161/154; 64 x 131,072, k = 5
+  // 39/42 and 91/80; 512 x 65,536, k = 32 88/110 and 151/167.  Without a
+  // threshold sample the fused pass starts from empty lists (1,024 x 32,768,
+  // k = 32: 410/111 and 442/165), except where it scores few of the pairs:
+  // a scoped call skips tiles by namespace (1,000 x 30,000, k = 22, mixed
+  // rows of 128 namespaces, d = 96 and 1,024: 84/144 and 133/194).  Relation
+  // builds up to 5,792 keys take the general path: 4,000 keys, k = 5 121/64,
+  // but above 4,096 keys lists of 8 lose there (5,400 keys 116/235).
+  int64_t most = p.kcap > 8 || p.ns == 0 ? int64_t{1} << 24 : int64_t{6} << 20;
+  if (relation || (p.ns == 0 && !scoped)) most = int64_t{1} << 25;
+  return m * n < most ? general_plan(m, n, k, limit) : p;
+}
+
 }  // namespace memattn
 
 using namespace memattn;
@@ -449,14 +478,7 @@ extern "C" {
 size_t mem_workspace_bytes(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype) {
   if (m < 0 || n < 1 || d < 1 || d > kMaxD || k < 1 || k > kMaxK || (dtype != MEM_F32 && dtype != MEM_BF16))
     return 0;
-  const size_t a = make_plan(m, n, d, k, dtype, true).ws_bytes;
-  const size_t b = make_plan(m, n, d, k, dtype, false).ws_bytes;
-  // a scoped retrieval's chunk tables (of the largest bank up to n rows that
-  // takes them)
-  const int64_t n_fit = m > 0 && n > scope_max_rows(m) ? scope_max_rows(m) : n;
-  const size_t c = dtype == MEM_BF16 && scope_tables_fit(m, n_fit, d, k) ? scope_layout(m, n_fit, d, k, a).end : 0;
-  const size_t ab = a > b ? a : b;
-  return ab > c ? ab : c;
+  return plan_bytes(m, n, d, k, dtype);
 }
 
 mem_status mem_retrieve_topk(const mem_bank* bank, const void* queries, int64_t m, int64_t q_stride, int32_t k,

@@ -76,8 +76,9 @@ struct Scope {
 
 // mfma_ok: caller allows the matrix-core path (bf16, d % 32 == 0, k <= 32,
 // no full probability output).  relation: the queries are the bank's own
-// rows, scoped: it takes namespaces (the sample size and the path depend on
-// them, never the workspace size).
+// rows, scoped: it takes namespaces (the sample size and the path, and with
+// the path the plan's ws_bytes, depend on them; mem_workspace_bytes covers
+// every path).
 // limit: the workspace at hand; the general path scores smaller blocks to fit.
 Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation = false,
                bool scoped = false, size_t limit = SIZE_MAX);

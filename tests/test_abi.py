@@ -404,3 +404,56 @@ def test_workspace_size_never_decreases_with_the_bank():
                 w = L.mem_workspace_bytes(m, n, d, k, dt)
                 assert w >= prev, (m, d, k, dt, n)
                 prev = w
+
+
+def _needed(call):
+    """Bytes a call asks for when it is offered one (0: none)."""
+    st = call()
+    text = pm.lib().mem_last_error().decode()
+    found = re.search(r"workspace of 1 bytes < (\d+) needed", text)
+    assert st == -3 and found, (st, text)
+    return int(found.group(1))
+
+
+def _random_call(rng):
+    """(m, n, d, k, dtype) over the paths' ranges, many of them next to a line between two paths."""
+    d, dt = rng.choice([3, 32, 64, 96, 128, 768, 1024, 8192]), rng.choice([pm.MEM_F32, pm.MEM_BF16, pm.MEM_BF16, pm.MEM_BF16])
+    k = rng.randint(1, 64) if rng.random() < 0.3 else rng.randint(1, 32)
+    m, n = int(2 ** rng.uniform(0, 17)), int(2 ** rng.uniform(7, 22))
+    if rng.random() < 0.6:  # products at which a path or the chunk tables begin
+        line = rng.choice([6 << 20, 1 << 24, 1 << 25, (1 << 38) // d])
+        n = max(128, int(line / m * rng.uniform(0.7, 1.4)))
+    return m, min(n, 1 << 26), d, k, dt
+
+
+@needs_lib
+def test_calls_need_no_more_than_the_workspace_size():
+    import random
+    L, rng = pm.lib(), random.Random(5)
+    for i in range(4000):
+        m, n, d, k, dt = _random_call(rng)
+        b = _bank(n=n, d=d, dtype=dt, stride=d)
+        size = L.mem_workspace_bytes(m, n, d, k, dt)
+        for full in (None, FAKE):
+            assert _needed(lambda: L.mem_retrieve_topk(C.byref(b), 2 * FAKE, m, d, k, 1.0, _out(), full, FAKE, 1,
+                                                       None)) <= size, (m, n, d, k, dt)
+            assert _needed(lambda: L.mem_retrieve_topk_scoped(C.byref(b), FAKE, 2 * FAKE, FAKE, m, d, k, 1.0, _out(),
+                                                              full, FAKE, 1, None)) <= size, (m, n, d, k, dt)
+        n = rng.choice([rng.randint(65, 2100), rng.randint(2000, 6500), int(2 ** rng.uniform(12, 17))])
+        b = _bank(n=n, d=d, dtype=dt, stride=d)
+        size = L.mem_workspace_bytes(n, n, d, k, dt)
+        for own in (0, 1):
+            assert _needed(lambda: L.mem_build_relations(C.byref(b), k, 1.0, own, _out(), FAKE, 1, None)) <= size, (n, d, k)
+            assert _needed(lambda: L.mem_build_relations_scoped(C.byref(b), FAKE, k, 1.0, own, _out(), FAKE, 1,
+                                                                None)) <= size, (n, d, k)
+
+
+@needs_lib
+def test_workspace_size_never_decreases_next_to_a_path_rule():
+    import random
+    L, rng = pm.lib(), random.Random(6)
+    assert L.mem_workspace_bytes(0, 1024, 256, 8, pm.MEM_BF16) >= 0
+    for i in range(3000):
+        m, n, d, k, dt = _random_call(rng)
+        sizes = [L.mem_workspace_bytes(m, x, d, k, dt) for x in sorted({n, n + 1, n + 255, n + n // 40 + 1, n + n // 5})]
+        assert sizes == sorted(sizes), (m, n, d, k, dt, sizes)

@@ -303,3 +303,29 @@ def test_grouped_offsets_are_clamped_to_the_table(dev):
     ok = host(pm.mem_retrieve_topk_grouped(up(cb.emb), up(offsets), up(chunks), up(cb.queries), up(kns), 8, 1.0))
     for key in g:
         assert np.array_equal(g[key], ok[key]), key
+
+
+# ------------------------------------------------------------------ sizes at which scoped and unscoped calls part ways
+
+@pytest.mark.parametrize("m,n,d,k", [(1000, 30000, 64, 22), (1024, 20000, 96, 10), (2000, 10000, 32, 32)])
+@pytest.mark.parametrize("run", [1, 64])
+def test_scoped_retrieval_between_the_paths(dev, m, n, d, k, run):
+    # 2^24 to 2^25 pairs without a threshold sample, in a workspace of the size the library names
+    say(f"case: scoped bf16 m={m} n={n} d={d} k={k} run={run}")
+    cb = inputs.clustered_bank(50, TAG_SCOPED, n, d, 64, 0.3, "bf16", m_queries=m)
+    rns, live, kns = inputs.namespaces(50, TAG_SCOPED, n, 30, 0.1, run=run, m=m)
+    g = run_scoped(cb.emb, cb.queries, rns, live, kns, k, 2.0)
+    rows = np.unique(np.concatenate([[0, 255, 256, m - 1], np.random.default_rng(m).choice(m, 40, replace=False)]))
+    check_topk_scoped(f"between-{m}", cb.queries, cb.emb, rows, {key: v[rows] for key, v in g.items()}, k, 2.0, rns, live, kns)
+
+
+@pytest.mark.parametrize("n,d,k", [(4097, 32, 16), (4200, 128, 8), (5000, 64, 32), (5792, 96, 5)])
+def test_scoped_relation_build_between_the_paths(dev, n, d, k):
+    say(f"case: scoped relation build bf16 n={n} d={d} k={k}")
+    cb = inputs.clustered_bank(51, TAG_SCOPED, n, d, 40, 0.3, "bf16")
+    rns, live, _ = inputs.namespaces(51, TAG_SCOPED, n, 12, 0.1, run=16)
+    abi = inputs.scoped_row_ns(rns, live)
+    g = host(pm.mem_build_relations_scoped(up(cb.emb), up(abi), k, 3.0, True))
+    rows = np.unique(np.concatenate([[0, 4095, 4096, n - 1], np.random.default_rng(n).choice(n, 60, replace=False)]))
+    check_topk_scoped(f"between-rel-{n}", cb.emb, cb.emb, rows, {key: v[rows] for key, v in g.items()}, k, 3.0, rns, live,
+                      abi, self_idx=np.arange(n))

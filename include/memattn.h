@@ -217,7 +217,9 @@ typedef struct {
   int64_t n_entries;      /* = offsets[n_ns] */
 } mem_chunk_tables;
 
-/* Workspace for mem_retrieve_topk_grouped (0 on invalid sizes). */
+/* Workspace for mem_retrieve_topk_grouped (0 on invalid sizes).  Never
+ * decreases with n_entries, so a workspace sized for the most entries the
+ * tables will hold serves them while they are smaller. */
 MEMATTN_API size_t mem_workspace_bytes_grouped(int64_t m, int32_t n_ns, int64_t n_entries, int32_t d, int32_t k);
 
 /*

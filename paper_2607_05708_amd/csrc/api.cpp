@@ -535,7 +535,7 @@ mem_status mem_build_relations_scoped(const mem_bank* bank, const int32_t* row_n
 size_t mem_workspace_bytes_grouped(int64_t m, int32_t n_ns, int64_t n_entries, int32_t d, int32_t k) {
   if (m < 0 || n_ns < 0 || n_entries < 0 || d < 1 || d > kMaxD || k < 1 || k > kMfmaMaxK) return 0;
   const Plan p = make_grouped_plan(m, n_ns, n_entries, k);
-  return group_layout(m, n_ns, n_entries, d, p.ws_bytes).bytes;
+  return group_layout(m, n_ns, n_entries, d, p.ws_bytes).room;
 }
 
 mem_status mem_retrieve_topk_grouped(const mem_bank* bank, const mem_chunk_tables* tables, const void* queries,

@@ -112,7 +112,9 @@ hipError_t launch_topk_mfma(const Plan& p, const uint16_t* bank, int64_t bank_st
 // pass; the merge follows with launch_topk_merge).  The plan must be the
 // narrow matrix-core shape with n_splits = S splits per namespace.
 struct GroupLayout {
-  size_t q_cnt, fill, q_off, item_off, bsum, perm, qbuf, q_pos, flag, tile_off, score_off, scores, bytes;
+  size_t q_cnt, fill, q_off, item_off, bsum, perm, qbuf, q_pos, flag, tile_off, score_off, scores;
+  size_t bytes;  // what a call of these sizes uses
+  size_t room;   // and what callers are asked for: no less, and never less for larger tables
   bool tables;  // few enough queries and namespaces for launch_topk_tables to be tried
 };
 GroupLayout group_layout(int64_t m, int32_t n_ns, int64_t n_entries, int32_t d, size_t base);

@@ -1567,6 +1567,17 @@ static size_t table_scores(int64_t m, int64_t n_entries) {
   return static_cast<size_t>(row >= kTableScores / m ? kTableScores : m * row);
 }
 
+// Regions of a selection over scored tables, from byte o on; returns their end.
+static size_t table_regions(GroupLayout& L, size_t o, int64_t m, int32_t n_ns, int64_t n_entries) {
+  auto al = [](size_t x) { return (x + 255) & ~static_cast<size_t>(255); };
+  L.q_pos = o;     o += al(static_cast<size_t>(m) * 4);
+  L.flag = o;      o += al(8);
+  L.tile_off = o;  o += al(static_cast<size_t>(n_ns + 1) * 4);
+  L.score_off = o; o += al(static_cast<size_t>(n_ns) * 8);
+  L.scores = o;    o += al(table_scores(m, n_entries) * 4);
+  return o;
+}
+
 GroupLayout group_layout(int64_t m, int32_t n_ns, int64_t n_entries, int32_t d, size_t base) {
   auto al = [](size_t x) { return (x + 255) & ~static_cast<size_t>(255); };
   GroupLayout L{};
@@ -1581,13 +1592,13 @@ GroupLayout group_layout(int64_t m, int32_t n_ns, int64_t n_entries, int32_t d, 
   L.qbuf = o;     o += al(static_cast<size_t>(m > 0 ? m : 1) * d * 2);
   // (not tried where an average table would already need twice the room)
   L.tables = m > 0 && m <= kPrepM && n_ns > 0 && n_ns <= kPrepNs && n_entries / n_ns <= 2 * kTableScores / m;
-  if (L.tables) {
-    L.q_pos = o;     o += al(static_cast<size_t>(m) * 4);
-    L.flag = o;      o += al(8);
-    L.tile_off = o;  o += al(static_cast<size_t>(n_ns + 1) * 4);
-    L.score_off = o; o += al(static_cast<size_t>(n_ns) * 8);
-    L.scores = o;    o += al(table_scores(m, n_entries) * 4);
-  }
+  // What callers are asked for does not tell whether these tables are tried:
+  // it has room for as many of the queries as could, so that it grows with
+  // the tables.
+  GroupLayout most{};
+  const int64_t m_most = m < kPrepM ? m : kPrepM;
+  L.room = m > 0 && n_ns > 0 && n_ns <= kPrepNs ? table_regions(most, o, m_most, n_ns, n_entries) : o;
+  if (L.tables) o = table_regions(L, o, m, n_ns, n_entries);
   L.bytes = o;
   return L;
 }

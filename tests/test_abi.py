@@ -457,3 +457,23 @@ def test_workspace_size_never_decreases_next_to_a_path_rule():
         m, n, d, k, dt = _random_call(rng)
         sizes = [L.mem_workspace_bytes(m, x, d, k, dt) for x in sorted({n, n + 1, n + 255, n + n // 40 + 1, n + n // 5})]
         assert sizes == sorted(sizes), (m, n, d, k, dt, sizes)
+
+
+@needs_lib
+def test_grouped_workspace_size_covers_and_never_decreases_with_the_entries():
+    import random
+    L, rng = pm.lib(), random.Random(7)
+    for i in range(1500):
+        m, n_ns = int(2 ** rng.uniform(0, 15)), int(2 ** rng.uniform(0, 13))
+        d, k = rng.choice([96, 128, 1024]), rng.randint(1, 32)
+        # entries at which an average table takes 24 * 2^20 scores, and others
+        line = (24 << 20) // m * n_ns
+        counts = sorted({0, 1, int(2 ** rng.uniform(0, 21)), int(2 ** rng.uniform(0, 21)), line - n_ns, line + n_ns, 2 * line})
+        prev = 0
+        for e in (min(max(c, 0), (1 << 31) - 1) for c in counts):
+            size = L.mem_workspace_bytes_grouped(m, n_ns, e, d, k)
+            assert size >= prev, (m, n_ns, e, d, k)
+            prev = size
+            b, t = _bank(n=1 << 20, d=d, stride=d), pm.MemChunkTables(FAKE, FAKE, n_ns, e)
+            assert _needed(lambda: L.mem_retrieve_topk_grouped(C.byref(b), C.byref(t), FAKE, FAKE, m, d, k, 1.0, _out(), FAKE,
+                                                               1, None)) <= size, (m, n_ns, e, d, k)

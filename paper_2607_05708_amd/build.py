@@ -44,10 +44,11 @@ def _compile(src: str) -> str:
     return obj
 
 
-def device_asm(src: str) -> str:
+def device_asm(src: str, *flags: str) -> str:
     """gfx950 assembly of one source file (device code only), built with the
-    library's flags; used by host-side code-generation checks."""
-    cmd = [HIPCC, *DEVICE_FLAGS, "-I", os.path.join(ROOT, "include"), "--cuda-device-only", "-S",
+    library's flags and any others given; used by host-side code-generation
+    checks."""
+    cmd = [HIPCC, *DEVICE_FLAGS, *flags, "-I", os.path.join(ROOT, "include"), "--cuda-device-only", "-S",
            os.path.join(HERE, src), "-o", "-"]
     if src.endswith(".cpp"):
         cmd[1:1] = ["-x", "hip"]

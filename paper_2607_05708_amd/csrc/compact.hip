@@ -393,11 +393,10 @@ __global__ __launch_bounds__(64) void totals_kernel(TotalsSrc t) {
 
 // The exclusive scan of op over n elements and the totals after it: by one
 // workgroup in one launch for up to 4,096 elements (a namespace or key each),
-// four launches otherwise.
+// four launches otherwise.  (`out` is not __restrict__: the totals read out[n].)
 constexpr int64_t kShortScan = 4096;
 template <class Op>
-__global__ __launch_bounds__(kScanThreads) void short_scan_kernel(Op op, int64_t n, int64_t* __restrict__ out,
-                                                                  TotalsSrc t) {
+__global__ __launch_bounds__(kScanThreads) void short_scan_kernel(Op op, int64_t n, int64_t* out, TotalsSrc t) {
   __shared__ int64_t red[4];
   int64_t carry = 0;
   for (int64_t b0 = 0; b0 < n; b0 += kScanBlock) {

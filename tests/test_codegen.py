@@ -126,3 +126,13 @@ def test_scoped_namespaces_use_scalar_loads(asm):
         assert count(body, r"\ts_load_dwordx16") >= 1, name
         pairs += 1
     assert pairs == 18   # 3 list sizes x 3 shapes x (sample, full)
+
+
+def test_short_scan_totals_may_read_its_output():
+    # The scan's last thread reads the total back through another pointer, so
+    # the compiler must not be told that nothing else points at the output.
+    ir = build.device_asm("csrc/compact.hip", "-emit-llvm")
+    heads = [l for l in ir.splitlines() if l.startswith("define") and "short_scan_kernel" in l]
+    assert len(heads) == 2
+    for head in heads:
+        assert "noalias" not in head, head[:300]

@@ -55,8 +55,8 @@ __device__ __forceinline__ int count_above(const SelectLds& L, int total, uint64
 }
 
 // Offers a step's keys to the list: key(j), j < PER, are this thread's
-// (0 = none; all keys distinct), hi(j) their upper halves and top the largest
-// of those.  Only keys above the list's k-th matter; with RISING (every key is
+// (0 = none; all distinct, or equal ones may be lost), hi(j) their upper halves
+// and top the largest of those.  Only keys above the list's k-th matter; with RISING (every key is
 // of a later row than the list's) those with a larger upper half.  If many are
 // (as in the first step), the k-th largest of the threads' tops is a better
 // bound: k keys lie at or above it, so none below can be among the k best,
@@ -109,7 +109,9 @@ __device__ __forceinline__ int select_step(SelectLds& L, const Hi& hi, const Key
     total = select_count<PER>(L, above, top >= least);
     if (total > kSelCand) {
       // (more than kSelCand: over k threads hold a candidate, so the k-th
-      // largest of their largest keys is one thread's)
+      // largest of their largest keys is one thread's.  Fewer than k threads
+      // hold keys above it, also where a chunk table repeats a row and keys
+      // are equal: those and one copy of it are the candidates.)
       uint64_t best = 0;
 #pragma unroll
       for (int j = 0; j < PER; ++j) {
@@ -118,19 +120,20 @@ __device__ __forceinline__ int select_step(SelectLds& L, const Hi& hi, const Key
       }
       L.cand[tid] = best;
       __syncthreads();
-      if (best != 0 && count_above(L, kSelThreads, best) == k - 1) L.thr = best;
+      if (best != 0 && count_above(L, kSelThreads, best) < k && count_above(L, kSelThreads, best - 1) >= k) L.thr = best;
       __syncthreads();
       least64 = L.thr;
       whole = true;
-      total = select_count<PER>(L, [&](int j) { return key(j) >= least64; }, true);
+      if (tid == 0) L.cand[0] = least64;
+      total = 1 + select_count<PER>(L, [&](int j) { return key(j) > least64; }, true);
     }
   }
-  int at = 0;
+  int at = whole ? 1 : 0;
   for (int w = 0; w < wave; ++w) at += L.wcount[w];
   if (L.wcount[wave] != 0) {
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-      const bool in = whole ? key(j) >= least64 : above(j);
+      const bool in = whole ? key(j) > least64 : above(j);
       const uint64_t bal = __ballot(in);
       if (in) L.cand[at + __popcll(bal & ((uint64_t{1} << lane) - 1))] = key(j);
       at += __popcll(bal);

@@ -150,3 +150,28 @@ def test_grouped_few_long_tables(m, n_ns, n, d, k):
     # every other query was scored: k distinct rows, all of its own namespace
     assert np.all(rns[g["idx"][~none]] == kns[~none, None])
     assert all(len(set(r)) == k for r in g["idx"][~none].tolist())
+
+
+@pytest.mark.parametrize("repeats,k", [(1500, 5), (3000, 32), (6000, 16)])
+def test_table_that_repeats_a_row(repeats, k):
+    # outside the contract (a table lists distinct rows): more equal keys than a selection step holds stay within its
+    # memory, the row still comes first, and the other namespaces' results are right
+    print(f"case: grouped table with {repeats} equal entries k={k}", flush=True)
+    n, d, m = 9000, 96, 40
+    bt, b = bank_of(130, n, d)
+    q = b[4000:4001].repeat(m, 0)           # row 4,000 scores highest for every query
+    q[1::2] = b[5000 + np.arange(1, m, 2)]  # (odd queries ask in the other namespace)
+    kns = (np.arange(m) % 2).astype(np.int32)
+    mine = np.sort(np.concatenate([np.full(repeats, 4000), np.arange(100, 400)])).astype(np.int32)
+    other = np.arange(4500, 9000).astype(np.int32)
+    offsets = np.array([0, len(mine), len(mine) + len(other)], np.int32)
+    out = pm.mem_retrieve_topk_grouped(bt, up(offsets), up(np.concatenate([mine, other])), up(q), up(kns), k, 1.0)
+    torch.cuda.synchronize()
+    g = dict(zip(("idx", "score", "prob", "lse"), (t.cpu().numpy() for t in out)))
+    assert np.all(g["idx"][0::2, 0] == 4000)
+    assert set(np.unique(g["idx"][0::2])) <= {-1, 4000} | set(range(100, 400))
+    assert np.all(np.isfinite(g["lse"]))
+    rows = np.arange(1, m, 2)
+    rns = np.where(np.arange(n) >= 4500, 1, 0).astype(np.int32)
+    check_topk_scoped(f"repeats-{repeats}", q, b, rows, {key: v[rows] for key, v in g.items()}, k, 1.0, rns,
+                      np.ones(n, np.uint8), kns)

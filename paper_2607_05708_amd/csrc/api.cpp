@@ -459,13 +459,14 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
   // k = 32 74/63 and 191/158, k = 5 48/58 and 161/154; 64 x 131,072, k = 5
   // 39/42 and 91/80; 512 x 65,536, k = 32 88/110 and 151/167.  Without a
   // threshold sample the fused pass starts from empty lists (1,024 x 32,768,
-  // k = 32: 410/111 and 442/165), except where it scores few of the pairs:
-  // a scoped call skips tiles by namespace (1,000 x 30,000, k = 22, mixed
-  // rows of 128 namespaces, d = 96 and 1,024: 84/144 and 133/194).  Relation
-  // builds up to 5,792 keys take the general path: 4,000 keys, k = 5 121/64,
-  // but above 4,096 keys lists of 8 lose there (5,400 keys 116/235).
+  // k = 32: 410/111 and 442/165), but not in a relation build: 4,000 keys,
+  // k = 5 121/64, above 4,096 keys (5,400, d = 64 and 768) 82/177 and 116/236,
+  // k = 20 and 30 156/190 and 223/245.  A scoped call without one keeps to the
+  // line of the others: with mixed rows the fused pass is the faster one above
+  // it, with rows in runs the general path (1,000 x 30,000 in 128 namespaces,
+  // k = 22, d = 1,024: mixed 133/194, runs of 16 309/183, of 64 403/189).
   int64_t most = p.kcap > 8 || p.ns == 0 ? int64_t{1} << 24 : int64_t{6} << 20;
-  if (relation || (p.ns == 0 && !scoped)) most = int64_t{1} << 25;
+  if (p.ns == 0 && !scoped && !relation) most = int64_t{1} << 25;
   return m * n < most ? general_plan(m, n, k, limit) : p;
 }
 

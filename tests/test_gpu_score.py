@@ -149,7 +149,7 @@ def test_both_sides_of_the_path_rule(m, n, k):
     check_topk(f"rule-{m}-{n}", cb.queries, cb.emb, rows, {key: v[rows] for key, v in g.items()}, k, 1.0)
 
 
-@pytest.mark.parametrize("n,k", [(5700, 5), (5700, 32), (5900, 32)])
+@pytest.mark.parametrize("n,k", [(4096, 5), (4097, 5), (5400, 20), (5700, 5), (5700, 32), (5900, 5), (5900, 32)])
 def test_both_sides_of_the_path_rule_for_relations(n, k):
     b = inputs.clustered_bank(96, 98, n, 64, 32, 0.3, "bf16").emb
     g = host(pm.mem_build_relations(up(b), k, 1.0, True))

@@ -730,16 +730,25 @@ __global__ __launch_bounds__(kSelThreads, 4) void select_tables_kernel(TableArgs
   if (tid == 0 && a.lse) a.lse[q] = lse2 * kLn2;
 }
 
-int64_t tile_queries(int64_t nq) { return nq <= 32 ? 32 : (nq <= 64 ? 64 : 128); }
+// Queries per tile: 128, 64 or 32, no more than the queries need, and fewer
+// while that leaves fewer tiles than CUs.  128 queries x 30,000 rows (235 tiles
+// of 128 queries, so the small kernel before, against 470 of 64), d = 64, 256
+// and 1,024: 30 -> 29, 37 -> 29 and 86 -> 34 us; 200 x 6,000 (tiles of 32): 21
+// -> 20, 24 -> 21 and 42 -> 27 us; fp32, d = 1,024: 183 -> 88 and 79 -> 54 us.
+int64_t tiles_of(int64_t nq, int64_t n, int64_t tq) { return (n + 127) / 128 * ((nq + tq - 1) / tq); }
+int64_t tile_queries(int64_t nq, int64_t n) {
+  int64_t tq = nq <= 32 ? 32 : (nq <= 64 ? 64 : 128);
+  while (tq > 32 && tiles_of(nq, n, tq) < 256) tq /= 2;
+  return tq;
+}
 
 // Whether the whole call (not one block of it, so that scores do not depend
-// on how it is cut into blocks) takes the small kernel: fewer tiles than CUs,
-// which smaller ones spread over four times as many, or rows shorter than the
-// 16 bytes the tiles read at a time.
+// on how it is cut into blocks: tiles of all sizes sum alike) takes the small
+// kernel: fewer tiles than CUs whatever their size, which smaller ones spread
+// over four times as many, or rows shorter than the 16 bytes the tiles read at
+// a time.
 bool small_scores(int64_t m, int64_t n, int64_t row_bytes) {
-  if (row_bytes < 16) return true;
-  const int64_t tq = tile_queries(m);
-  return (n + 127) / 128 * ((m + tq - 1) / tq) < 256;
+  return row_bytes < 16 || tiles_of(m, n, tile_queries(m, n)) < 256;
 }
 
 template <typename T, int QB, int QW, int RB, int RW, bool STREAM = false>
@@ -752,7 +761,7 @@ void launch_tiles(const ScoreArgs& a, hipStream_t stream) {
 
 template <typename T>
 hipError_t launch_score(const ScoreArgs& a, bool small, hipStream_t stream) {
-  const int64_t tq = tile_queries(a.nq);
+  const int64_t tq = tile_queries(a.nq, a.rows);
   if (small) {
     const int64_t wgs = (a.rows + 31) / 32 * ((a.nq + 31) / 32);
     score_small_kernel<T><<<dim3(static_cast<unsigned>(wgs)), 256, 0, stream>>>(a);

@@ -172,3 +172,16 @@ def test_long_rows_of_a_large_bank(d, k):
     assert (torch.gather(s, 1, idx.long()) - score.double()).abs().max() <= eps
     assert all(len(set(row)) == k for row in idx.tolist())
     assert (lse.double() - torch.logsumexp(s, 1)).abs().max() <= eps + 1e-5 * 14
+
+
+# (dtype, m, n, d): tiles of 32 and 64 queries for more queries than one of them holds, next to the tile counts (256) at
+# which they begin, the last tile with one query or row
+@pytest.mark.parametrize("dtype,m,n,d", [("bf16", 33, 16257, 40), ("bf16", 64, 16385, 200), ("f32", 65, 10881, 20),
+                                         ("f32", 97, 8100, 70), ("bf16", 129, 10880, 24), ("bf16", 129, 10881, 72),
+                                         ("bf16", 200, 4607, 64), ("f32", 257, 6530, 36), ("bf16", 1025, 1921, 96)])
+def test_tiles_of_fewer_queries(dtype, m, n, d):
+    print(f"case: {dtype} m={m} n={n} d={d}", flush=True)
+    b, q = inputs.iid_unit(99, 98, 0, n, d, dtype), inputs.iid_unit(99, 98, 4, m, d, dtype)
+    g = host(pm.mem_retrieve_topk(up(b), up(q), 12, 2.0))
+    rows = np.unique(np.concatenate([[0, 31, 32, m - 2, m - 1], pick(m, n)]))
+    check_topk(f"tiles-{m}-{n}", q, b, rows, {key: v[rows] for key, v in g.items()}, 12, 2.0)

@@ -9,9 +9,9 @@ namespace memattn {
 
 namespace {
 
-// Softmax partials of one query (at most 64: lists of at most 512 keys in
-// all, 8 or more each), combined by one wave: lse2 = log2 of the normaliser in
-// the scaled log2 domain (max, then the rescaled sum in fp64).
+// Softmax partials of one query (at most 64), combined by one wave: lse2 =
+// log2 of the normaliser in the scaled log2 domain (max, then the rescaled sum
+// in fp64).
 __device__ __forceinline__ float wave_lse2(const float2* __restrict__ ms, int n_parts, int lane) {
   const float2 v = lane < n_parts ? ms[lane] : make_float2(-INFINITY, 0.f);
   const float m = wave_max_f32(v.x);
@@ -20,10 +20,10 @@ __device__ __forceinline__ float wave_lse2(const float2* __restrict__ ms, int n_
   return m + static_cast<float>(log2(s));
 }
 
-// One wave per key, four keys per workgroup, for lists of at most 64 * PER
-// keys in all (PER <= 8) and k <= 32: lane l's j-th key is rank (l + j) % kk of
-// list j * (64 / kk) + l / kk (kk: k rounded up to a power of two), so that
-// each lane gets every rank in turn.  As in select.h the k-th largest of the
+// One wave per key, four keys per workgroup, for at most 64 lists of at most
+// 64 * PER keys in all (PER <= 16) and k <= 32: lane l's j-th key is rank
+// (l + j) % kk of list j * (64 / kk) + l / kk (kk: k rounded up to a power of
+// two), so that each lane gets every rank in turn.  As in select.h the k-th largest of the
 // lanes' own largest upper halves bounds the candidates, which are compacted
 // by ballots and ranked by counting, here without a workgroup barrier.
 // Against a rank by binary search in every other list (few lists) and a
@@ -188,9 +188,11 @@ hipError_t launch_topk_merge(const Plan& p, int64_t m, int32_t k, float c2, int3
   int kk = 8;
   while (kk < k) kk <<= 1;
   const int64_t total = static_cast<int64_t>(p.n_parts) * kk;
-  // One wave up to 512 keys; a workgroup is sooner done with more (100
-  // queries with 128 lists of 8: 344 against 352 us for the whole call).
-  if (k <= 32 && total <= 512 && alt.flag == nullptr) {
+  // One wave up to 64 lists of 1,024 keys in all (1,000 queries with 59 lists
+  // of 16: 124 us for the whole call, 132 by workgroups; 2,000 with 30 of 32:
+  // 346 and 360); a workgroup is sooner done with more lists (100 queries with
+  // 128 lists of 8: 344 against 352 us).
+  if (k <= 32 && total <= 1024 && p.n_parts <= 64 && alt.flag == nullptr) {
     const dim3 grid(static_cast<unsigned>((m + 3) / 4));
     if (total <= 64)
       topk_merge_wave_kernel<1><<<grid, 256, 0, stream>>>(keys, ms, m, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob,
@@ -198,9 +200,12 @@ hipError_t launch_topk_merge(const Plan& p, int64_t m, int32_t k, float c2, int3
     else if (total <= 256)
       topk_merge_wave_kernel<4><<<grid, 256, 0, stream>>>(keys, ms, m, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob,
                                                           lse, lse2, alt.done);
-    else
+    else if (total <= 512)
       topk_merge_wave_kernel<8><<<grid, 256, 0, stream>>>(keys, ms, m, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob,
                                                           lse, lse2, alt.done);
+    else
+      topk_merge_wave_kernel<16><<<grid, 256, 0, stream>>>(keys, ms, m, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob,
+                                                           lse, lse2, alt.done);
   } else {
     topk_merge_select_kernel<<<dim3(static_cast<unsigned>(m)), kSelThreads, 0, stream>>>(
         keys, ms, p.n_parts, kcap_eff, k, kk, c2, idx, score, prob, lse, lse2, alt);

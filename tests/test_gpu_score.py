@@ -185,3 +185,22 @@ def test_tiles_of_fewer_queries(dtype, m, n, d):
     g = host(pm.mem_retrieve_topk(up(b), up(q), 12, 2.0))
     rows = np.unique(np.concatenate([[0, 31, 32, m - 2, m - 1], pick(m, n)]))
     check_topk(f"tiles-{m}-{n}", q, b, rows, {key: v[rows] for key, v in g.items()}, 12, 2.0)
+
+
+# (m, n, k): 17, 31 and 32 lists of 32 and 33 and 64 of 16 per query, which one wave merges (up to 64 lists of 1,024 keys
+# in all), then 33 of 32 and 68 of 8
+@pytest.mark.parametrize("m,n,k", [(60, 69632, 17), (33, 126976, 31), (32, 131072, 32), (31, 135000, 9), (16, 262144, 16),
+                                   (31, 135168, 32), (15, 278528, 8)])
+@pytest.mark.parametrize("scoped", [False, True])
+def test_merges_around_1024_keys(m, n, k, scoped):
+    print(f"case: f32 m={m} n={n} k={k} scoped={scoped}", flush=True)
+    b, q = inputs.iid_unit(100, 98, 0, n, 8, "f32"), inputs.iid_unit(100, 98, 4, m, 8, "f32")
+    rows = np.arange(0, m, 3)
+    if not scoped:
+        g = host(pm.mem_retrieve_topk(up(b), up(q), k, 2.0))
+        check_topk(f"merge-{m}", q, b, rows, {key: v[rows] for key, v in g.items()}, k, 2.0)
+        return
+    # most namespaces hold fewer rows than there are lists, some fewer than k
+    rns, live, kns = inputs.namespaces(100, 98, n, 9000, 0.1, run=3, m=m)
+    g = host(pm.mem_retrieve_topk_scoped(up(b), up(inputs.scoped_row_ns(rns, live)), up(q), up(kns), k, 2.0))
+    check_topk_scoped(f"merge-scoped-{m}", q, b, rows, {key: v[rows] for key, v in g.items()}, k, 2.0, rns, live, kns)

@@ -120,9 +120,8 @@ mem_status select_topk(const mem_bank* bank, const void* queries, int64_t m, int
                        bank->row_stride % 8 == 0 && q_stride % 8 == 0 && bank->row_stride <= 65536 &&
                        q_stride <= 65536 && aligned16(bank->emb) && aligned16(queries);
   const bool relation = queries == bank->emb && q_stride == bank->row_stride && m == bank->n;
-  // (a scoped relation build keeps the bank order, so its sample as well)
-  const Plan p = make_plan(m, bank->n, bank->d, k, bank->dtype, mfma_ok, relation && scope.row_ns == nullptr,
-                           scope.row_ns != nullptr, use_scratch ? kScratchBytes : SIZE_MAX);
+  const Plan p = make_plan(m, bank->n, bank->d, k, bank->dtype, mfma_ok, relation, scope.row_ns != nullptr,
+                           use_scratch ? kScratchBytes : SIZE_MAX);
   if (static_cast<int64_t>(p.n_splits) * (p.mfma ? p.q_tiles : m) > INT32_MAX)
     return fail(MEM_ERR_UNSUPPORTED, "problem too large for one launch");
   if (m > INT32_MAX) return fail(MEM_ERR_UNSUPPORTED, "m too large");
@@ -450,7 +449,8 @@ size_t plan_bytes(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype) {
 Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, bool scoped,
                size_t limit) {
   if (!mfma_ok || !fused_shape(d, k, dtype)) return general_plan(m, n, k, limit);
-  const Plan p = fused_plan(m, n, d, k, relation);
+  // (a scoped relation build keeps the bank order, so its sample as well)
+  const Plan p = fused_plan(m, n, d, k, relation && !scoped);
   // Scoring a block and selecting from it costs 8 bytes of cache traffic and
   // a few instructions per pair that the fused pass saves, but keeps every
   // CU busy at any size and has no lists to warm up: it takes the smaller
@@ -461,12 +461,18 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
   // threshold sample the fused pass starts from empty lists (1,024 x 32,768,
   // k = 32: 410/111 and 442/165), but not in a relation build: 4,000 keys,
   // k = 5 121/64, above 4,096 keys (5,400, d = 64 and 768) 82/177 and 116/236,
-  // k = 20 and 30 156/190 and 223/245.  A scoped call without one keeps to the
-  // line of the others: with mixed rows the fused pass is the faster one above
-  // it, with rows in runs the general path (1,000 x 30,000 in 128 namespaces,
-  // k = 22, d = 1,024: mixed 133/194, runs of 16 309/183, of 64 403/189).
+  // k = 20 and 30 156/190 and 223/245.  A scoped call's fused pass skips tiles
+  // by namespace, so rows in runs, which sessions append, and mixed rows part:
+  // 1,000 x 30,000 in 128 namespaces, k = 22, d = 1,024, mixed 133/194, runs of
+  // 16 309/183, of 64 403/189; 300 x 30,000, k = 5, d = 64, mixed 33/55, runs of
+  // 16 and 64 113/55 and 77/53.  It keeps to the others' line, which is the
+  // better one for runs below it and for mixed rows above.  Lists of 8 in a
+  // scoped relation build are sooner done by the fused pass from 2,049 keys on
+  // (d = 64, k = 5, runs of 16 and mixed: 2,048 keys 52/34 and 34/34, 4,090 keys
+  // 58/77 and 40/77), longer ones not (k = 16 110/79 and 57/79).
   int64_t most = p.kcap > 8 || p.ns == 0 ? int64_t{1} << 24 : int64_t{6} << 20;
   if (p.ns == 0 && !scoped && !relation) most = int64_t{1} << 25;
+  if (relation && scoped && p.kcap == 8) most = (int64_t{1} << 22) + 1;
   return m * n < most ? general_plan(m, n, k, limit) : p;
 }
 

@@ -319,13 +319,14 @@ def test_scoped_retrieval_between_the_paths(dev, m, n, d, k, run):
     check_topk_scoped(f"between-{m}", cb.queries, cb.emb, rows, {key: v[rows] for key, v in g.items()}, k, 2.0, rns, live, kns)
 
 
-@pytest.mark.parametrize("n,d,k", [(4097, 32, 16), (4200, 128, 8), (5000, 64, 32), (5792, 96, 5)])
+@pytest.mark.parametrize("n,d,k", [(2048, 64, 8), (2049, 64, 8), (3000, 96, 5), (4095, 64, 9), (4097, 32, 16), (4200, 128, 8),
+                                   (5000, 64, 32), (5792, 96, 5)])
 def test_scoped_relation_build_between_the_paths(dev, n, d, k):
     say(f"case: scoped relation build bf16 n={n} d={d} k={k}")
     cb = inputs.clustered_bank(51, TAG_SCOPED, n, d, 40, 0.3, "bf16")
     rns, live, _ = inputs.namespaces(51, TAG_SCOPED, n, 12, 0.1, run=16)
     abi = inputs.scoped_row_ns(rns, live)
     g = host(pm.mem_build_relations_scoped(up(cb.emb), up(abi), k, 3.0, True))
-    rows = np.unique(np.concatenate([[0, 4095, 4096, n - 1], np.random.default_rng(n).choice(n, 60, replace=False)]))
+    rows = np.unique(np.concatenate([[0, 255, 256, n - 1], np.random.default_rng(n).choice(n, 60, replace=False)]))
     check_topk_scoped(f"between-rel-{n}", cb.emb, cb.emb, rows, {key: v[rows] for key, v in g.items()}, k, 3.0, rns, live,
                       abi, self_idx=np.arange(n))

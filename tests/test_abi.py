@@ -466,8 +466,8 @@ def test_grouped_workspace_size_covers_and_never_decreases_with_the_entries():
     for i in range(1500):
         m, n_ns = int(2 ** rng.uniform(0, 15)), int(2 ** rng.uniform(0, 13))
         d, k = rng.choice([96, 128, 1024]), rng.randint(1, 32)
-        # entries at which an average table takes 24 * 2^20 scores, and others
-        line = (24 << 20) // m * n_ns
+        # entries at which average tables take 12 * 2^20 scores, and others
+        line = (12 << 20) // m * n_ns
         counts = sorted({0, 1, int(2 ** rng.uniform(0, 21)), int(2 ** rng.uniform(0, 21)), line - n_ns, line + n_ns, 2 * line})
         prev = 0
         for e in (min(max(c, 0), (1 << 31) - 1) for c in counts):

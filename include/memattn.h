@@ -147,10 +147,10 @@ MEMATTN_API mem_status mem_retrieve_topk(const mem_bank* bank, const void* queri
  * arguments, kernels, results and errors as mem_retrieve_topk; the
  * workspace is instead a fixed scratch array of mem_scratch_bytes() bytes
  * (128 MiB) that the library holds in every GPU it runs on until the
- * process ends.  Calls whose workspace (mem_workspace_bytes) exceeds it
- * fail with MEM_ERR_WORKSPACE before anything is enqueued (up to 1,024
- * queries fit at any bank size and k; the general path's block of scores
- * shrinks to what is left of the array).  The first call on a device
+ * process ends.  Calls that need more fail with MEM_ERR_WORKSPACE before
+ * anything is enqueued: up to 1,024 queries fit at any bank size and k, and
+ * every call that the general path takes (at most 100 MiB: a block of scores
+ * and the lists of the block's queries).  The first call on a device
  * looks up the array's address there (make that first call outside graph
  * capture); later calls only enqueue kernels.  Every call on one GPU shares
  * that GPU's array, which keeps the last call's contents (the kernels

@@ -120,8 +120,7 @@ mem_status select_topk(const mem_bank* bank, const void* queries, int64_t m, int
                        bank->row_stride % 8 == 0 && q_stride % 8 == 0 && bank->row_stride <= 65536 &&
                        q_stride <= 65536 && aligned16(bank->emb) && aligned16(queries);
   const bool relation = queries == bank->emb && q_stride == bank->row_stride && m == bank->n;
-  const Plan p = make_plan(m, bank->n, bank->d, k, bank->dtype, mfma_ok, relation, scope.row_ns != nullptr,
-                           use_scratch ? kScratchBytes : SIZE_MAX);
+  const Plan p = make_plan(m, bank->n, bank->d, k, bank->dtype, mfma_ok, relation, scope.row_ns != nullptr);
   if (static_cast<int64_t>(p.n_splits) * (p.mfma ? p.q_tiles : m) > INT32_MAX)
     return fail(MEM_ERR_UNSUPPORTED, "problem too large for one launch");
   if (m > INT32_MAX) return fail(MEM_ERR_UNSUPPORTED, "m too large");
@@ -372,10 +371,11 @@ Plan fused_plan(int64_t m, int64_t n, int32_t d, int32_t k, bool relation) {
   return p;
 }
 
-// The general path: blocks of scores, as large as `limit` leaves room for.
-// Its workspace depends on m, n, k and the limit alone and never decreases
-// with n.
-Plan general_plan(int64_t m, int64_t n, int32_t k, size_t limit) {
+// The general path.  Its workspace depends on m, n and k alone, never
+// decreases with n, and is at most 100 MiB: a block of scores and, where every
+// query has one split, the lists of a block's queries (with more splits there
+// are at most 4,095 lists in all).
+Plan general_plan(int64_t m, int64_t n, int32_t k) {
   Plan p{};
   p.mfma = false;
   p.kcap = pow2_at_least(k);
@@ -399,26 +399,17 @@ Plan general_plan(int64_t m, int64_t n, int32_t k, size_t limit) {
   p.n_splits = static_cast<int>(ceil_div(n, p.rows_per_split));
   p.n_parts = p.n_splits;
   p.part_stride = 1;
-  const size_t slots = static_cast<size_t>(s_max > p.n_splits ? s_max : p.n_splits);
-  const size_t mm = static_cast<size_t>(m > 0 ? m : 0);
-  p.ws_part_keys = 0;
-  p.ws_part_ms = align256(mm * slots * p.kcap * sizeof(uint64_t));
-  p.ws_lse2 = p.ws_part_ms + align256(mm * slots * 2 * sizeof(float));
-  p.ws_part_lo = p.ws_lse2 + align256(mm * sizeof(float));
-  p.ws_scores = p.ws_part_lo + align256(mm * slots * sizeof(float));
   p.blk_queries = m < 4096 ? (m > 0 ? m : 1) : 4096;
+  const size_t slots = static_cast<size_t>(s_max);
+  const size_t lists = slots * static_cast<size_t>(s_max == 1 ? p.blk_queries : m);
+  p.ws_part_keys = 0;
+  p.ws_part_ms = align256(lists * p.kcap * sizeof(uint64_t));
+  p.ws_lse2 = p.ws_part_ms + align256(lists * 2 * sizeof(float));
+  p.ws_part_lo = p.ws_lse2 + align256(lists * sizeof(float));
+  p.ws_scores = p.ws_part_lo + align256(lists * sizeof(float));
   const int64_t wide = static_cast<int64_t>(kScoreBlock / sizeof(float)) / p.blk_queries / kSelectRows * kSelectRows;
   p.blk_rows = ceil_div(n, 32) * 32;
-  if (p.blk_rows > wide) p.blk_rows = wide > kSelectRows ? wide : kSelectRows;
-  const int64_t room = limit > p.ws_scores ? static_cast<int64_t>((limit - p.ws_scores) / sizeof(float)) : 0;
-  if (p.blk_queries * p.blk_rows > room) {
-    if (p.blk_rows > kSelectRows) p.blk_rows = kSelectRows;
-    if (p.blk_queries > room / p.blk_rows) p.blk_queries = room / p.blk_rows;
-    if (p.blk_queries < 1) {
-      p.blk_queries = 1;
-      p.blk_rows = room >= 32 ? room / 32 * 32 : 32;
-    }
-  }
+  if (p.blk_rows > wide) p.blk_rows = wide;
   p.ws_bytes = p.ws_scores + align256(static_cast<size_t>(p.blk_queries * p.blk_rows) * sizeof(float));
   // as many blocks, of about the same size (a short last one would leave
   // most of the GPU idle)
@@ -430,7 +421,7 @@ Plan general_plan(int64_t m, int64_t n, int32_t k, size_t limit) {
 // What the selection calls of these sizes need at most, whichever path their
 // options, namespaces and alignment lead them to.
 size_t plan_bytes(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype) {
-  const size_t general = general_plan(m, n, k, SIZE_MAX).ws_bytes;
+  const size_t general = general_plan(m, n, k).ws_bytes;
   if (!fused_shape(d, k, dtype)) return general;
   const size_t fused = fused_plan(m, n, d, k, false).ws_bytes;
   size_t most = general > fused ? general : fused;
@@ -446,9 +437,8 @@ size_t plan_bytes(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype) {
 
 }  // namespace
 
-Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, bool scoped,
-               size_t limit) {
-  if (!mfma_ok || !fused_shape(d, k, dtype)) return general_plan(m, n, k, limit);
+Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, bool scoped) {
+  if (!mfma_ok || !fused_shape(d, k, dtype)) return general_plan(m, n, k);
   // (a scoped relation build keeps the bank order, so its sample as well)
   const Plan p = fused_plan(m, n, d, k, relation && !scoped);
   // Scoring a block and selecting from it costs 8 bytes of cache traffic and
@@ -473,7 +463,7 @@ Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool m
   int64_t most = p.kcap > 8 || p.ns == 0 ? int64_t{1} << 24 : int64_t{6} << 20;
   if (p.ns == 0 && !scoped && !relation) most = int64_t{1} << 25;
   if (relation && scoped && p.kcap == 8) most = (int64_t{1} << 22) + 1;
-  return m * n < most ? general_plan(m, n, k, limit) : p;
+  return m * n < most ? general_plan(m, n, k) : p;
 }
 
 }  // namespace memattn

@@ -43,7 +43,8 @@ struct Plan {
   size_t ws_qbuf;         // the queries in clustered order [m, d] (bf16)
   int64_t blk_queries;    // general path: queries and bank rows scored at a time
   int64_t blk_rows;
-  size_t ws_part_lo;      // low words of the partial softmax sums [m, n_splits] (float)
+  size_t ws_part_lo;      // low words of the partial softmax sums [m, n_splits] (float); with one split,
+                          // all partials are those of a block's queries
   size_t ws_scores;       // the block's scores [blk_queries, blk_rows] (float)
   size_t ws_bytes;        // total workspace bytes
 };
@@ -79,9 +80,7 @@ struct Scope {
 // rows, scoped: it takes namespaces (the sample size and the path, and with
 // the path the plan's ws_bytes, depend on them; mem_workspace_bytes covers
 // every path).
-// limit: the workspace at hand; the general path scores smaller blocks to fit.
-Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation = false,
-               bool scoped = false, size_t limit = SIZE_MAX);
+Plan make_plan(int64_t m, int64_t n, int32_t d, int32_t k, int32_t dtype, bool mfma_ok, bool relation, bool scoped);
 // Grouped selection over per-namespace chunk tables: the narrow matrix-core
 // shape, S splits per namespace (S from the mean table size), no sample.
 Plan make_grouped_plan(int64_t m, int32_t n_ns, int64_t n_entries, int32_t k);

@@ -348,9 +348,10 @@ struct SelectArgs {
   int64_t self_base;
   const int32_t* row_ns;
   const int32_t* key_ns;
-  uint64_t* part_keys;    // [m, n_splits, kcap]
-  float2* part_ms;        // [m, n_splits]: max, sum
-  float* part_lo;         // [m, n_splits]: what the sum's rounding left
+  int64_t part_q0;        // first query of the partials: 0, or with one split the block's
+  uint64_t* part_keys;    // [queries, n_splits, kcap]
+  float2* part_ms;        // [queries, n_splits]: max, sum
+  float* part_lo;         // [queries, n_splits]: what the sum's rounding left
   int full;               // the scores are the caller's full probability rows
   int64_t n;
   // final results (one split per query, last block), else idx is NULL
@@ -402,7 +403,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void select_kernel(SelectArgs a) {
   const int64_t ql = blockIdx.x / a.block_splits;
   const int64_t q = a.q0 + ql;
   const int split = a.split0 + static_cast<int>(blockIdx.x % a.block_splits);
-  const int64_t slot = q * a.n_splits + split;
+  const int64_t slot = (q - a.part_q0) * a.n_splits + split;
   const int64_t s0 = static_cast<int64_t>(split) * a.rows_per_split;
   const int64_t row0 = max(s0, a.c0);
   const int64_t row1 = min(min(s0 + a.rows_per_split, a.n), a.c1);
@@ -835,6 +836,7 @@ hipError_t launch_topk_score(const Plan& p, const void* bank, int64_t bank_strid
       a.self_base = self_base;
       a.row_ns = scope.row_ns;
       a.key_ns = scope.key_ns;
+      a.part_q0 = p.n_splits == 1 ? q0 : 0;
       a.part_keys = reinterpret_cast<uint64_t*>(w + p.ws_part_keys);
       a.part_ms = reinterpret_cast<float2*>(w + p.ws_part_ms);
       a.part_lo = reinterpret_cast<float*>(w + p.ws_part_lo);

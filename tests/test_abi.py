@@ -477,3 +477,13 @@ def test_grouped_workspace_size_covers_and_never_decreases_with_the_entries():
             b, t = _bank(n=1 << 20, d=d, stride=d), pm.MemChunkTables(FAKE, FAKE, n_ns, e)
             assert _needed(lambda: L.mem_retrieve_topk_grouped(C.byref(b), C.byref(t), FAKE, FAKE, m, d, k, 1.0, _out(), FAKE,
                                                                1, None)) <= size, (m, n_ns, e, d, k)
+
+
+@needs_lib
+def test_general_path_always_fits_the_scratch():
+    # fp32 and long lists take the general path, whose workspace has one bound for all sizes
+    L = pm.lib()
+    for m in (1, 2047, 2048, 4096, 4097, 252000, 1 << 21, (1 << 31) - 1):
+        for n in (64, 4096, 16385, 1 << 20, (1 << 31) - 2):
+            for k, dt in ((64, pm.MEM_BF16), (1, pm.MEM_F32), (64, pm.MEM_F32)):
+                assert 0 < L.mem_workspace_bytes(m, n, 64, k, dt) <= 100 << 20, (m, n, k)

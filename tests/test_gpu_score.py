@@ -127,9 +127,9 @@ def test_ties_and_orders(n, k):
     assert np.allclose(g["prob"][0], 1.0 / n, rtol=1e-5) and np.allclose(g["lse"][0], np.log(n) + 1e-6, rtol=1e-5)
 
 
-def test_allocation_free_call_cuts_smaller_blocks():
-    # 200,000 lists of 64 leave the 128 MiB scratch array little room for scores
-    m, n, d, k = 200000, 300, 8, 64
+@pytest.mark.parametrize("m,n,d,k", [(200000, 300, 8, 64), (252000, 4100, 8, 64), (4097, 4097, 20, 33)])
+def test_allocation_free_call_of_many_queries(m, n, d, k):
+    # (the lists of all 252,000 queries would fill the 128 MiB scratch array: it holds those of 4,096 at a time)
     b, q = up(inputs.iid_unit(94, 98, 0, n, d, "f32")), up(inputs.iid_unit(94, 98, 4, m, d, "f32"))
     want = pm.mem_retrieve_topk(b, q, k, 1.0)
     out = tuple(torch.empty_like(t) for t in want)
@@ -137,6 +137,9 @@ def test_allocation_free_call_cuts_smaller_blocks():
     torch.cuda.synchronize()
     for x, y in zip(want, out):
         assert torch.equal(x, y)
+    rows = np.unique(np.concatenate([[0, 4095, 4096, m - 1], pick(m)]))
+    g = {key: v.cpu().numpy()[rows] for key, v in zip(("idx", "score", "prob", "lse"), out)}
+    check_topk(f"noalloc-{m}", q.cpu().numpy(), b.cpu().numpy(), rows, g, k, 1.0)
 
 
 # (m, n, k): the calls next to the lines between the fused and the general path

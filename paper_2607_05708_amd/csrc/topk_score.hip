@@ -781,6 +781,24 @@ hipError_t launch_score(const ScoreArgs& a, bool small, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The block's scores, in launches of at most 2^23 workgroups even of the
+// smallest blocks: a launch has fewer than 2^32 threads, and a block with full
+// probabilities is the whole bank.
+template <typename T>
+hipError_t launch_scores(const ScoreArgs& a, bool small, hipStream_t stream) {
+  const int64_t most = (int64_t{1} << 28) / ((a.nq + 31) / 32) / 1024 * 1024;
+  const int64_t per = most > 1024 ? most : 1024;
+  for (int64_t r0 = 0; r0 < a.rows; r0 += per) {
+    ScoreArgs part = a;
+    part.bank = static_cast<const T*>(a.bank) + r0 * a.bank_stride;
+    part.rows = a.rows - r0 < per ? a.rows - r0 : per;
+    part.out = a.out + r0;
+    const hipError_t e = launch_score<T>(part, small, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 }  // namespace
 
 hipError_t launch_topk_tables(const TableArgs& a, hipStream_t stream) {
@@ -818,7 +836,7 @@ hipError_t launch_topk_score(const Plan& p, const void* bank, int64_t bank_strid
       sa.d = d;
       sa.out = full_scores ? full_scores : reinterpret_cast<float*>(w + p.ws_scores);
       sa.ld = full_scores ? n : p.blk_rows;
-      hipError_t e = dtype == 0 ? launch_score<float>(sa, small, stream) : launch_score<uint16_t>(sa, small, stream);
+      hipError_t e = dtype == 0 ? launch_scores<float>(sa, small, stream) : launch_scores<uint16_t>(sa, small, stream);
       if (e != hipSuccess) return e;
       SelectArgs a{};
       a.scores = sa.out;

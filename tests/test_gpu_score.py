@@ -207,3 +207,26 @@ def test_merges_around_1024_keys(m, n, k, scoped):
     rns, live, kns = inputs.namespaces(100, 98, n, 9000, 0.1, run=3, m=m)
     g = host(pm.mem_retrieve_topk_scoped(up(b), up(inputs.scoped_row_ns(rns, live)), up(q), up(kns), k, 2.0))
     check_topk_scoped(f"merge-scoped-{m}", q, b, rows, {key: v[rows] for key, v in g.items()}, k, 2.0, rns, live, kns)
+
+
+@pytest.mark.parametrize("d", [1, 4])
+def test_full_probabilities_of_half_a_billion_rows(d):
+    # 2^24 and more blocks of 32 rows, past the threads of one launch
+    n = (1 << 29) + 37
+    g = torch.Generator(device="cuda").manual_seed(101)
+    b = torch.randn((n, d), generator=g, device="cuda")
+    q = torch.zeros((1, d), device="cuda")
+    q[0, d - 1] = 1.0
+    s = b[:, d - 1]
+    full = torch.empty((1, n), device="cuda")
+    idx, score, prob, lse = pm.mem_retrieve_topk(b, q, 3, 1.0, full_prob=full)
+    top = max((v, -int(i) - r0) for r0 in range(0, n, 1 << 27)
+              for v, i in [tuple(x.item() for x in s[r0:r0 + (1 << 27)].max(0))])
+    assert idx[0, 0].item() == -top[1] and score[0, 0].item() == top[0]
+    assert torch.equal(s[idx[0].long()], score[0])
+    total = sum(part.double().exp().sum() for part in s.split(1 << 27)).log()
+    assert abs(lse.item() - total.item()) <= 2e-6 * total.item()
+    for r0 in (0, (1 << 28) - 50, (1 << 29) - 50, n - 100):
+        part = slice(r0, r0 + 100)
+        assert torch.allclose(full[0, part].double(), (s[part].double() - total).exp(), rtol=1e-4, atol=0)
+    assert abs(sum(part.double().sum() for part in full[0].split(1 << 27)).item() - 1.0) <= 1e-4

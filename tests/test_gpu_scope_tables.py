@@ -46,6 +46,12 @@ CASES = [
     (2048, 140000, 1024, 17, 1, 8),      # one namespace: declined
     (2048, 140000, 1024, 8, 3, 8),       # declined
     (4096, 8200, 8192, 32, 64, 8),       # the shortest tables and the largest dimension
+    # tables that are too many scores (12 * 2^20) or too long (32,768 rows) to be scored first: the fused grouped pass
+    # runs over them, in as many splits as the device plans
+    (2048, 140000, 1024, 32, 8, 16),
+    (2048, 140000, 1024, 6, 9, 1),
+    (1024, 300001, 1024, 16, 8, 64),
+    (3000, 90001, 1024, 12, 11, 300),
 ]
 
 
@@ -92,6 +98,33 @@ def test_captured_call_follows_the_namespaces():
         ws.fill_(255)
         graph.replay()
         check(f"replay-{rep}", b, q, rns, live, kns, out, k, rep)
+
+
+def test_captured_call_over_long_tables():
+    # the same for tables that the fused grouped pass takes, in turn with the other two ways
+    m, n, d, k = 2048, 140000, 1024, 10
+    bt, b = bank_of(72, n, d)
+    qt, q = bank_of(172, m, d)
+    few, many = (inputs.namespaces(72, 99, n, spaces, 0.1, run=16, m=m) for spaces in (8, 150))
+    one = (np.zeros(n, np.int32), many[1], np.zeros(m, np.int32))
+    row_ns, key_ns = up(inputs.scoped_row_ns(few[0], few[1])), up(few[2])
+    out = (torch.empty((m, k), dtype=torch.int32, device="cuda"), torch.empty((m, k), device="cuda"),
+           torch.empty((m, k), device="cuda"), torch.empty(m, device="cuda"))
+    ws = torch.empty(pm.mem_workspace_bytes(m, n, d, k, pm.MEM_BF16), dtype=torch.uint8, device="cuda")
+
+    def call():
+        pm.mem_retrieve_topk_scoped(bt, row_ns, qt, key_ns, k, 1.0, out=out, workspace=ws)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for rep, (rns, live, kns) in enumerate((few, many, few, one, few)):
+        row_ns.copy_(up(inputs.scoped_row_ns(rns, live)))
+        key_ns.copy_(up(kns))
+        ws.fill_(255)
+        graph.replay()
+        check(f"long-replay-{rep}", b, q, rns, live, kns, out, k, rep)
 
 
 def grouped_check(lengths, counts, d, k, seed, n_extra=0):

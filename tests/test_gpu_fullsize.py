@@ -186,8 +186,8 @@ def test_grouped_request_selection_1m(dev):
 
 
 def test_scoped_retrieval_1m(dev):
-    # the dense masked call at the benchmark's size: 256 namespaces in runs of
-    # 64 rows, 10 % tombstones, 1,024 queries, top-32
+    # the scoped call at the benchmark's size, through chunk tables that the
+    # device collects: 256 namespaces in runs of 64 rows, 10 % tombstones, 1,024 queries, top-32
     say("case: scoped top-32, 1,048,576 x 1024 bf16, 1,024 queries, 256 namespaces")
     n, d, m, k = 1 << 20, 1024, 1024, 32
     cb, _ = bank_1m()

@@ -78,7 +78,7 @@ def test_integer_grid_exact_with_ties(dev, d):
 
 @pytest.mark.parametrize("d,pad", [(160, 24), (32, 8), (96, 0)])
 def test_strided_rows_odd_k_blocks(dev, d, pad):
-    # rows padded to a wider row stride; d/32 odd or 1 k-blocks per tile
+    # rows padded to a wider row stride (of a call this small on the general path; test_gpu_fused.py has the fused pass)
     say(f"case: strided rows d={d} pad={pad}")
     cb = inputs.clustered_bank(13, 65, 1300, d, 8, 0.3, "bf16", m_queries=270)
     wide_b = np.zeros((1300, d + pad), np.uint16)
@@ -114,11 +114,10 @@ def test_smallest_banks_every_candidate_selected(dev, dtype, n):
 
 
 def test_largest_dimension_and_row_stride(dev):
-    # d = 8192, the largest dimension the boundary takes: on the matrix-core
-    # path (256 k-blocks per tile) with bank rows at the largest stride it
-    # takes, 65,536 elements, and on the VALU path (fp32, k = 64)
+    # d = 8192, the largest dimension the boundary takes, both on the general
+    # path: bf16 with bank rows 65,536 elements apart, and fp32 with k = 64
     d = 8192
-    say("case: bf16 d=8192 bank row stride 65536, m=70 k=32 (matrix cores)")
+    say("case: bf16 d=8192 bank row stride 65536, m=70 k=32")
     cb = inputs.clustered_bank(33, 65, 1100, d, 8, 0.3, "bf16", m_queries=70)
     wide_b = torch.zeros((1100, 65536), dtype=torch.int16, device="cuda")
     wide_b[:, :d] = torch.from_numpy(cb.emb.view(np.int16)).cuda()
@@ -130,7 +129,7 @@ def test_largest_dimension_and_row_stride(dev):
     g = {"idx": idx.cpu().numpy(), "score": score.cpu().numpy(), "prob": prob.cpu().numpy(), "lse": lse.cpu().numpy()}
     check_topk("d8192-stride65536", cb.queries, cb.emb, np.arange(70), g, 32, 1.0)
     del wide_b, b
-    say("case: f32 d=8192, m=5 k=64 (VALU path)")
+    say("case: f32 d=8192, m=5 k=64")
     bank = inputs.iid_unit(33, 66, 0, 700, d, "f32")
     q = inputs.iid_unit(33, 66, 4, 5, d, "f32")
     g = run_retrieve(bank, q, 64, 1.0)
@@ -139,8 +138,8 @@ def test_largest_dimension_and_row_stride(dev):
 
 @pytest.mark.parametrize("m", [64, 65, 128, 129])
 def test_workgroup_shape_boundaries(dev, m):
-    # 64 queries use the 64 x 512-row tile, 65..128 the 128 x 256 tile,
-    # more the 256 x 256 tile: check each side of both boundaries
+    # each side of the query counts at which the fused pass changes its shape,
+    # on the general path (test_gpu_fused.py has the shapes themselves)
     say(f"case: shape boundary m={m} n=5000 d=128 k=16")
     cb = inputs.clustered_bank(15, 67, 5000, 128, 32, 0.3, "bf16", m_queries=m)
     g = run_retrieve(cb.emb, cb.queries, 16, 1.0)
@@ -148,9 +147,9 @@ def test_workgroup_shape_boundaries(dev, m):
 
 
 def test_few_queries_many_partials(dev):
-    # 16 queries against 262,144 rows: 256 bank splits x 2 halves = 512 partial
-    # lists per query, merged in one wave with more than 64 KiB of LDS
-    say("case: m=16 n=262144 d=256 k=32 (512 partials per query)")
+    # 16 queries against 262,144 rows: 64 partial lists of 32 per query, merged
+    # by a workgroup
+    say("case: m=16 n=262144 d=256 k=32 (64 partials per query)")
     cb = inputs.clustered_bank(14, 66, 262144, 256, 512, 0.3, "bf16", m_queries=16)
     g = run_retrieve(cb.emb, cb.queries, 32, 1.0)
     check_topk("m16-512parts", cb.queries, cb.emb, np.arange(16), g, 32, 1.0)
@@ -158,10 +157,9 @@ def test_few_queries_many_partials(dev):
 
 @pytest.mark.parametrize("m", [1, 2])
 def test_generic_merge_many_long_lists(dev, m):
-    # fp32, k = 64: 586 (m = 1) or 391 (m = 2) partial lists of 64 keys per
-    # query do not fit the LDS of the list-head merges, so the one-workgroup
-    # merge inserts them 256 keys at a time
-    say(f"case: VALU path f32 n=300000 d=32 m={m} k=64, workgroup merge")
+    # fp32, k = 64: 74 partial lists of 64 keys per query, which the workgroup
+    # merge takes 4,096 keys a step
+    say(f"case: f32 n=300000 d=32 m={m} k=64, workgroup merge")
     bank = inputs.iid_unit(32, 64, 0, 300000, 32, "f32")
     q = inputs.iid_unit(32, 64, 4, m, 32, "f32")
     g = run_retrieve(bank, q, 64, 2.0)
@@ -209,8 +207,8 @@ def test_relation_build_bf16(dev):
 
 @pytest.mark.parametrize("n", [50, 100, 700])
 def test_relation_build_small_banks(dev, n):
-    # n <= 64 and <= 128 use the narrow workgroup shapes (one ragged tile,
-    # own row masked); 700 the main shape
+    # one ragged tile or a few, own row masked (test_gpu_fused.py has the fused
+    # pass, which larger builds take)
     say(f"case: relation build bf16 n={n} d=96 k=8 exclude_self")
     cb = inputs.clustered_bank(16, 68, n, 96, 4, 0.3, "bf16")
     idx, score, prob, lse = pm.mem_build_relations(up(cb.emb), 8, 20.0, True)
@@ -256,9 +254,10 @@ def test_edge_cases(dev, case):
 
 @pytest.mark.parametrize("dtype,n,k", [("f32", 6000, 10), ("bf16", 5000, 48), ("f32", 4096, 12), ("f32", 4097, 12)])
 def test_valu_path_many_splits(dev, dtype, n, k):
-    # the VALU path on banks of 16 to 24 splits of 256 rows (fp32, and bf16
-    # with k above the matrix-core limit), full probabilities for fp32
-    say(f"case: VALU path {dtype} n={n} d=64 m=20 k={k}")
+    # the general path on banks of one or two selection steps of 4,096 rows
+    # (fp32, and bf16 with k above the fused pass's limit), full probabilities
+    # for fp32
+    say(f"case: general path {dtype} n={n} d=64 m=20 k={k}")
     bank = inputs.iid_unit(30, 64, 0, n, 64, dtype)
     q = inputs.iid_unit(30, 64, 4, 20, 64, dtype)
     g = run_retrieve(bank, q, k, 2.0, full=(dtype == "f32"))
@@ -270,10 +269,9 @@ def test_valu_path_many_splits(dev, dtype, n, k):
 
 @pytest.mark.parametrize("n", [4096, 4097, 8192])
 def test_rank_merge_full_probabilities(dev, n):
-    # 300 queries split the bank 4 ways, so the rank merge combines them; it
-    # writes the full probability rows itself up to 4,096 rows, and
-    # full_prob_kernel does after it for larger banks
-    say(f"case: rank merge with full probabilities, f32 n={n} d=64 m=300 k=8")
+    # 300 queries, one split each: the select kernel's last step writes the
+    # full probability rows, from registers (4,096 rows) or read back
+    say(f"case: full probabilities after one and two steps, f32 n={n} d=64 m=300 k=8")
     bank = inputs.iid_unit(31, 64, 0, n, 64, "f32")
     q = inputs.iid_unit(31, 64, 4, 300, 64, "f32")
     g = run_retrieve(bank, q, 8, 3.0, full=True)

@@ -55,8 +55,8 @@ def run_scoped(bank, q, row_ns, row_live, key_ns, k, scale=1.0, full=False):
 @pytest.mark.parametrize("m", [50, 100, 300])
 @pytest.mark.parametrize("run", [1, 40])
 def test_scoped_matrix_core(dev, m, run):
-    # m = 50, 100, 300 take the three workgroup shapes; run = 1 gives every
-    # half block of 16 rows mixed namespaces, run = 40 long same-namespace runs
+    # mixed namespaces (run = 1) and long same-namespace runs (40), on the
+    # general path (test_gpu_fused.py has the fused pass's shapes)
     say(f"case: scoped bf16 n=3000 d=256 m={m} k=16 run={run}")
     cb = inputs.clustered_bank(30, TAG_SCOPED, 3000, 256, 16, 0.3, "bf16", m_queries=m)
     rns, live, kns = inputs.namespaces(30, TAG_SCOPED, 3000, 6, 0.2, run=run, query_src=cb.query_src)
@@ -92,9 +92,8 @@ def test_scoped_k_above_bank_size(dev):
 
 @pytest.mark.parametrize("n,m", [(40000, 16), (600, 16), (6000, 300)])
 def test_scoped_padding_in_every_merge(dev, n, m):
-    # about 9 live rows per namespace with k = 32, so most rows are padded,
-    # through each merge kernel: 79 partials per query (multi-wave merge),
-    # 2 partials (rank merge) and 24 partials (one-wave tournament)
+    # about 9 live rows per namespace with k = 32, so most rows are padded, by
+    # the merge of several partial lists (n = 40,000) and by the select kernel
     say(f"case: scoped padding n={n} d=64 m={m} k=32")
     cb = inputs.clustered_bank(40, TAG_SCOPED, n, 64, 16, 0.3, "bf16", m_queries=m)
     rns, live, kns = inputs.namespaces(40, TAG_SCOPED, n, n // 10, 0.1, run=4, query_src=cb.query_src)
@@ -104,7 +103,7 @@ def test_scoped_padding_in_every_merge(dev, n, m):
 
 
 def test_scoped_fp32_full_probabilities(dev):
-    # VALU path: full_prob is 0 outside the scope and sums to 1 over it
+    # general path: full_prob is 0 outside the scope and sums to 1 over it
     say("case: scoped fp32 n=1024 d=256 m=16 k=8 full_prob")
     bank = inputs.iid_unit(33, TAG_SCOPED, 2, 1024, 256, "f32")
     q = inputs.iid_unit(33, TAG_SCOPED, 4, 16, 256, "f32")

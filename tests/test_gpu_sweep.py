@@ -1,7 +1,7 @@
 """A seeded sweep of shapes against the oracle: query counts across the
 three workgroup shapes, ragged bank sizes (with and without a threshold
 sample and the two-launch plan), dimensions, k, scales and cluster
-structure, on the matrix-core (bf16) and VALU (fp32) paths, for retrieval
+structure, on the fused (bf16) and general paths, for retrieval
 and relation builds.  Every case checks up to 96 of its rows under the
 oracle's parity rules; calls go through the C ABI."""
 import sys

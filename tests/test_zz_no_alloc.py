@@ -71,8 +71,8 @@ def test_noalloc_matches_the_workspace_call_on_successive_calls(dev):
     c1 = inputs.clustered_bank(11, 97, 65536, 256, 64, 0.3, "bf16", m_queries=1024)
     assert pm.mem_workspace_bytes(1024, 65536, 256, 32, pm.MEM_BF16) > 90 << 20
     compare("noalloc-1024x65536", c1.emb, c1.queries, 32, 1.0)
-    # 2: a smaller call right after it (narrow 64-query shape, lists of 8,
-    #    ragged bank tail) on the array the first call left behind
+    # 2: a smaller call right after it (general path, lists of 8, ragged bank
+    #    tail) on the array the first call left behind
     c2 = inputs.clustered_bank(12, 97, 5001, 256, 16, 0.3, "bf16", m_queries=40)
     compare("noalloc-40x5001", c2.emb, c2.queries, 8, 2.0)
     # 3: smaller again, the fp32 path with full probabilities

@@ -56,11 +56,12 @@ __device__ __forceinline__ int count_above(const SelectLds& L, int total, uint64
 
 // Offers a step's keys to the list: key(j), j < PER, are this thread's
 // (0 = none; all distinct, or equal ones may be lost), hi(j) their upper halves
-// and top the largest of those.  Only keys above the list's k-th matter; with RISING (every key is
-// of a later row than the list's) those with a larger upper half.  If many are
-// (as in the first step), the k-th largest of the threads' tops is a better
-// bound: k keys lie at or above it, so none below can be among the k best,
-// and but for ties only those k threads hold candidates, at most 16 each.
+// and top the largest of those.  Only keys above the list's k-th matter; with
+// RISING (every key is of a later row than the list's) those with a larger
+// upper half.  If many are (as in the first step), the k-th largest of the
+// threads' tops is a better bound: k keys lie at or above it, so none below can
+// be among the k best, and but for ties only those k threads hold candidates,
+// at most 16 each.
 // One wave finds its upper kBoundBits bits from ballots.  (With fewer than k
 // threads holding any there is no such bound, and at most 16 (k - 1)
 // candidates.)  Where ties let in too many, the bound is found once more on

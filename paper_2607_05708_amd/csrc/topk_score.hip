@@ -736,6 +736,9 @@ __global__ __launch_bounds__(kSelThreads, 4) void select_tables_kernel(TableArgs
 // of 128 queries, so the small kernel before, against 470 of 64), d = 64, 256
 // and 1,024: 30 -> 29, 37 -> 29 and 86 -> 34 us; 200 x 6,000 (tiles of 32): 21
 // -> 20, 24 -> 21 and 42 -> 27 us; fp32, d = 1,024: 183 -> 88 and 79 -> 54 us.
+// (Tiles sum a row in one chain, as the fused pass does, the small kernel in
+// four: relative error against 64 bits at d = 1,024 3.6e-7 and 3.3e-7 in bf16,
+// 5.2e-7 and 3.4e-7 in fp32.)
 int64_t tiles_of(int64_t nq, int64_t n, int64_t tq) { return (n + 127) / 128 * ((nq + tq - 1) / tq); }
 int64_t tile_queries(int64_t nq, int64_t n) {
   int64_t tq = nq <= 32 ? 32 : (nq <= 64 ? 64 : 128);

@@ -1590,11 +1590,13 @@ GroupLayout group_layout(int64_t m, int32_t n_ns, int64_t n_entries, int32_t d, 
   L.bsum = o;     o += al(static_cast<size_t>(nb + 1) * 8);
   L.perm = o;     o += al(static_cast<size_t>(m > 0 ? m : 1) * 4);
   L.qbuf = o;     o += al(static_cast<size_t>(m > 0 ? m : 1) * d * 2);
-  // Not tried where average tables would already need more than the room:
-  // queries come from the longer tables at least as often, and the launches
-  // that find it too small cost 8 to 15 us (1,024 queries over 8 tables of
-  // 22,500 x 256, k = 32, and their prefixes: 424 us tried in vain, 416 not).
-  L.tables = m > 0 && m <= kPrepM && n_ns > 0 && n_ns <= kPrepNs && n_entries / n_ns <= kTableScores / m;
+  // Not tried where average tables would already need more than the room or
+  // be too long: queries come from the longer tables at least as often, and
+  // the launches that find it so cost 5 to 15 us (1,024 queries over 8 tables of
+  // 22,500 x 256, k = 32, and their prefixes: 424 us tried in vain, 416 not; 16
+  // over one of 54,000 x 96, k = 5: 118 and 110).
+  const int64_t mean = n_ns > 0 ? n_entries / n_ns : 0;
+  L.tables = m > 0 && m <= kPrepM && n_ns > 0 && n_ns <= kPrepNs && mean <= kTableScores / m && mean <= kTableMaxRows;
   // What callers are asked for does not tell whether these tables are tried:
   // it has room for as many of the queries as could, so that it grows with
   // the tables.

@@ -160,10 +160,11 @@ def test_both_sides_of_the_table_rule(length, queries):
     grouped_check([length, 300], [queries, 0], 96, 10, 90 + queries % 7)
 
 
-# (queries, namespaces, rows, d, k): on either side of the size (12 * 2^20 scores of average tables) up to which the
-# tables are given room to be scored first; past it the fused pass alone runs, over queries put in grouped order
+# (queries, namespaces, rows, d, k): on either side of the size (12 * 2^20 scores of average tables, or their 32,768 rows)
+# up to which the tables are given room to be scored first; past it the fused pass alone runs, over queries put in grouped order
 @pytest.mark.parametrize("m,n_ns,n,d,k", [(1024, 16, 196600, 96, 12), (1024, 16, 196640, 96, 12), (1024, 16, 393400, 96, 12),
-                                          (300, 2, 180001, 128, 32), (250, 8, 410000, 96, 5)])
+                                          (300, 2, 180001, 128, 32), (250, 8, 410000, 96, 5), (70, 2, 65536, 96, 7), (70, 2, 65538, 96, 7),
+                                          (9, 1, 54000, 96, 16)])
 def test_grouped_few_long_tables(m, n_ns, n, d, k):
     print(f"case: grouped m={m} namespaces={n_ns} n={n} d={d} k={k}", flush=True)
     bt, b = bank_of(120 + n_ns, n, d)
